@@ -380,14 +380,16 @@ typedef enum {
     MG_SHAPE_SWEEP = 4,     /* the single sweeps only (five values); MG_SHAPE_STENCIL
                                sets SMOOTH, SWEEP and PROLONG together and reads SWEEP */
     MG_SHAPE_PROLONG = 5,   /* prolongation + correction + sweep only (five values) */
-    MG_SHAPE_TAIL = 6,      /* 3-D, level argument 0: {on (0|1)}.  When on (the
-                               default), the coarse end of the V-cycle -- from the
-                               first level of pitch <= 16 (<= 8 for FP64 levels)
-                               whose levels share one format, down to the base and
-                               back -- runs as one single-workgroup kernel with the
-                               levels in LDS; bitwise the same result.  The
-                               workspace copies of those levels are then not
-                               updated. */
+    MG_SHAPE_TAIL = 6,      /* finite differences, level argument 0: {on (0|1)}.  When
+                               on (the default), the coarse end of the V-cycle runs as
+                               one single-workgroup kernel with the levels in LDS:
+                               3-D from the first level of pitch <= 16, 2-D of pitch
+                               <= 64, whose levels share one accumulator format (FP64,
+                               or FP32 for the narrower ones), down to the base (one
+                               point, or up to 1024 solved by CG) and back; a finest
+                               level that small belongs to it.  Bitwise the same
+                               result, also in the workspace vectors of its levels.
+                               (Q1 handles always run theirs so.) */
     MG_SHAPE_FUSE = 7,      /* 3-D, level argument 0: {on (0|1)[, V (4), zc, xcd,
                                ty[, from_r (0|1)]]}.  When on (the default; the
                                autotuner keeps it only where it is faster), the last

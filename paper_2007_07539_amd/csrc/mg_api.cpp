@@ -401,12 +401,18 @@ hipError_t enq_restrict(mg_ctx *h, hipStream_t st, int l, const void *b) {
     return hipSuccess;
 }
 
+// Steps the CG base solver takes at most.
+int base_max_steps(const mg_ctx *h) {
+    const long N = points(h->dim, h->lv[h->nl - 1].n);
+    return h->opt.base_max_iter > 0 ? h->opt.base_max_iter : (int)std::min<long>(10000, N);
+}
+
 hipError_t enq_coarse(mg_ctx *h, hipStream_t st, int l) {
     LevelPlan &L = h->lv[l];
     if (L.n > 1) {
         // CG on a base level of more than one point (Section 4.2)
         const long N = (long)points(h->dim, L.n);
-        const int maxit = h->opt.base_max_iter > 0 ? h->opt.base_max_iter : (int)std::min<long>(10000, N);
+        const int maxit = base_max_steps(h);
         RUN(h, st, "cg_base", l, (double)N * 2 * sb(L.prec),
             launch_cg_base(h->dim, L.prec, L.n, L.P, bbuf(h, l), cbuf(h, l, 0), h->ws + L.off_cg,
                            cg_scratch_stride(L.prec, L.elems), h->opt.base_tol, maxit, h->q1 ? 1 : 0, st));
@@ -519,22 +525,37 @@ hipError_t enq_vcycle_down(mg_ctx *h, hipStream_t st, RhsMode mode, int l, const
     return enq_restrict(h, st, l, rhs);
 }
 
-// First level of the fused coarse end (see launch_tail), or nl - 1 when the
-// V-cycle has none: the first level l >= 1 of pitch <= 16 (<= 8 for FP64)
-// from which all levels above the base share one format and fit in LDS.
-int tail_level(const mg_ctx *h) {
+// The fused coarse end from level l on, without its pointers.
+TailArgs tail_args(const mg_ctx *h, int l) {
+    TailArgs t;
+    t.D = h->dim;
+    t.q1 = h->q1;
+    t.P0 = h->lv[l].P;
+    t.nlev = h->nl - 1 - l;
+    for (int j = 0; j <= t.nlev && j <= kTailLevels; ++j) t.prec[j] = h->lv[l + j].prec;
+    t.nb = h->lv[h->nl - 1].n;
+    t.nu1 = h->opt.nu1;
+    t.nu2 = t.nu2_first = h->opt.nu2;
+    t.omega = h->opt.omega;
+    t.base_tol = h->opt.base_tol;
+    t.base_maxit = base_max_steps(h);
+    return t;
+}
+
+// First level of the fused coarse end, or nl - 1 when the V-cycle has none:
+// the first level whose grid one workgroup takes (launch_tail: 3-D pitches up
+// to 16, 2-D up to 64) and from which all levels above the base share an
+// accumulator format and fit in LDS.  Up to there a level's four launches
+// take 14-24 us and its part of the fused kernel 3-5; the next larger grid
+// would take one workgroup four to eight times as long as that.
+int tail_level(const mg_ctx *h, int first) {
     const int nl = h->nl;
-    if (!h->tail_on || h->dim != 3 || nl < 3 || h->lv[nl - 1].n > 1) return nl - 1;
-    for (int l = 1; l < nl - 1; ++l) {
-        const int P = h->lv[l].P, prec = h->lv[l].prec;
-        if (P > (prec == P_F64 ? 8 : 16)) continue;
-        bool same = true;
-        for (int j = l; j < nl - 1; ++j) same = same && h->lv[j].prec == prec;
+    if (!h->tail_on || nl < 2) return nl - 1;
+    for (int l = first; l < nl - 1; ++l) {
         // the fused coarse end has no rescaled restriction inside it
-        for (int j = l + 1; j < nl; ++j) same = same && !h->lv[j].rescale;
-        if (!same) continue;
-        const size_t lds = tail_lds_bytes(prec, h->lv[nl - 1].prec, P, nl - 1 - l);
-        if (lds > 0 && lds <= 65536) return l;
+        bool plain = true;
+        for (int j = l + 1; j < nl; ++j) plain = plain && !h->lv[j].rescale;
+        if (plain && tail_ok(tail_args(h, l))) return l;
     }
     return nl - 1;
 }
@@ -547,17 +568,26 @@ hipError_t enq_vcycle(mg_ctx *h, hipStream_t st, RhsMode mode, bool warm = false
     for (int l = 0; l < nl; ++l) rhs[l] = bbuf(h, l);
     if (mode == RHS_ALIAS_R) rhs[0] = Rbuf(h);
     hipError_t e;
-    const int lt = tail_level(h);
+    const int lt = tail_level(h, warm ? 1 : 0);
     if (lt < nl - 1) {
         // levels 0 .. lt-1 as separate launches, lt .. base fused
         for (int l = 0; l < lt; ++l) {
             if ((e = enq_vcycle_down(h, st, mode, l, rhs[l], warm)) != hipSuccess) return e;
         }
-        const LevelPlan &T = h->lv[lt];
-        RUN(h, st, "coarse_tail", lt, 0.0,
-            launch_tail(T.prec, h->lv[nl - 1].prec, T.P, nl - 1 - lt, bbuf(h, lt), cbuf(h, lt, 0), h->opt.nu1,
-                        h->opt.nu2, h->opt.omega, st));
-        h->cur[lt] = 0;
+        TailArgs t = tail_args(h, lt);
+        if (lt == 0 && mode == RHS_SCALED_R) {
+            t.R = Rbuf(h);
+            t.scal = scal(h);
+        } else {
+            t.b0 = rhs[lt];
+        }
+        for (int l = lt; l < nl; ++l) {
+            t.wb[l - lt] = bbuf(h, l);
+            t.wc[l - lt] = cbuf(h, l, 0);
+            h->cur[l] = 0;
+        }
+        if (lt == 0 && skip0) --t.nu2_first;
+        RUN(h, st, "coarse_tail", lt, 0.0, launch_tail(t, st));
         for (int l = lt - 1; l >= 0; --l) {
             if ((e = enq_prolong(h, st, l, rhs[l])) != hipSuccess) return e;
             if ((e = enq_post(h, st, l, rhs[l], l == 0 && skip0)) != hipSuccess) return e;
@@ -1395,7 +1425,7 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
     h->opt = o;
     h->ascale = ascale;
     h->q1 = q1;
-    if (q1) h->tail_on = h->fuse_on = h->fuse_sr_on = false;
+    if (q1) h->fuse_on = h->fuse_sr_on = false;
     h->lv.resize(m);
     size_t off = 0;
     int nn = n;
@@ -1494,6 +1524,7 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
     h->off_scal = off;
     off += 256;
     h->ws_need = off;
+    if (tail_prepare() != hipSuccess) h->tail_on = false;
     if (m > 1) {
         // the fused update's FP64 rows need more than 64 KB of LDS at P = 512
         if (h->dim == 3 && sweep_update_prepare() != hipSuccess) h->fuse_on = false;

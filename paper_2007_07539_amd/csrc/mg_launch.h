@@ -190,13 +190,32 @@ hipError_t launch_absmax(int pa, const void *t, long n, double *part, double *rs
 hipError_t launch_scale_cast(int pa, int prec, const void *t, const double *rs, void *out, long n, hipStream_t st);
 hipError_t launch_scale_widen(int prec, int pa, const void *c, const double *rs, void *out, long n, hipStream_t st);
 
-// Fused coarse end of a 3-D V-cycle in one workgroup (LDS-resident levels):
-// nlev grids of format prec with pitches P0 = 4 * 2^(nlev-1), ..., 4, then the
-// one-point base of format pb.  b: right-hand side of the first (padded, pitch
-// P0); c: receives its corrected, post-smoothed correction.
-size_t tail_lds_bytes(int prec, int pb, int P0, int nlev);  // 0 if unsupported
-hipError_t launch_tail(int prec, int pb, int P0, int nlev, const void *b, void *c, int nu1, int nu2, double omega,
-                       hipStream_t st);
+// Fused coarse end of a V-cycle in one workgroup (LDS-resident levels): nlev
+// levels of pitches P0, P0/2, ... and the base below them, nb points per
+// dimension (one, solved exactly, or a few, solved by CG).  prec[l]: storage
+// formats (the levels' must share one accumulator format), prec[nlev] the
+// base's.  The right-hand side of the first level is b0 (its format, padded)
+// or, with R, round(R scal[1]).  wb, wc: workspace vectors of every level and
+// the base; each level's right-hand side (the first one's only with R) and
+// final correction are written there.  nu2_first: post-sweeps of the first level.
+constexpr int kTailLevels = 8;
+struct TailArgs {
+    int D = 3, P0 = 0, nlev = 0, nb = 1;
+    bool q1 = false;
+    int prec[kTailLevels + 1] = {};
+    const void *b0 = nullptr;
+    const double *R = nullptr, *scal = nullptr;
+    void *wb[kTailLevels + 1] = {}, *wc[kTailLevels + 1] = {};
+    int nu1 = 2, nu2 = 2, nu2_first = 2;
+    double omega = 0.8;
+    double base_tol = 0.0;
+    int base_maxit = 0;
+};
+bool tail_ok(const TailArgs &t);  // the levels fit (pointers are not looked at)
+// Lets the kernels allocate up to kLdsMax of LDS; call before the first
+// launch, outside a stream capture.
+hipError_t tail_prepare();
+hipError_t launch_tail(const TailArgs &t, hipStream_t st);
 
 // ---- batched instances -------------------------------------------------------
 // Per-(instance, level) arguments of one batched launch.
