@@ -404,8 +404,9 @@ typedef enum {
                                of the workspace and the two swap roles every step.
                                An FP64 finest level without residual scaling, whose
                                right-hand side is r itself, takes only from_r = 1.
-                               Default: 1 for FP32/FP64 finest levels, 0 for 2-byte
-                               ones; the autotuner times both.  Not used when nu2 < 2.
+                               Default: 1 for FP32/FP64 finest levels and 2-byte ones
+                               of n >= 511 without defer_update, else 0; the
+                               autotuner times both.  Not used when nu2 < 2.
                                Reading returns whether it is in use and its shape. */
     MG_SHAPE_FUSE_SR = 8    /* 3-D, level l below the base: {on (0|1)[, tyc, zcc[, lds16]]}.  When
                                on, the level's first pre-smoothing (two sweeps from zero)

@@ -220,24 +220,69 @@ bool alpha_code(int D, const std::vector<int> &ns, const std::vector<int> &prec,
     return true;
 }
 
-Shape pick_shape(int D, int P, int prec) {
+// Default launch shapes, by pitch, format and kernel family.  What the lines
+// weigh: a thread walks its planes one after another, each with a barrier and
+// a trip to memory (0.5-2 us), so a level too small to fill the 256 CUs wants
+// few planes per block and small blocks, and a large one wants deep tiles that
+// read their halo rows and planes once.  The values are the fastest of the
+// autotuner's candidates on MI355X, per pitch; where neighbouring candidates
+// tie, one shape serves a range.  (63^3 in FP16, refinement step: 181 us with
+// 14 rows by 8 planes everywhere, 78 us with these; 255^3 473 -> 315; 31^3
+// 134 -> 58; 127^3 235 -> 116.)
+enum { SH_UPDATE = 3 };
+
+bool stencil_fits(int P, int sb_, const Shape &s) {
+    return (P / s.V) * (s.ty + 2) <= 1024 && march_lds_bytes(P, s.ty, (size_t)sb_) <= 65536 && s.ty <= P - 1;
+}
+
+Shape pick_shape(int D, int P, int prec, int family) {
     Shape s;
     s.V = P >= 8 ? 8 : 4;
     s.bs = 256;
     s.xcd = 1;
     s.ty = 0;
+    const bool f64 = prec == P_F64, f32 = prec == P_F32;
     if (D == 3 && P >= 16) {
-        // LDS-plane kernel: full rows, as many row groups as 1024 threads and
-        // 64 KiB of LDS allow (at most 14 output rows)
-        if (prec == P_F64) s.V = 4;
-        const int TXR = P / s.V;
-        int ty = std::min(14, P - 1);
-        while (ty > 1 && (TXR * (ty + 2) > 1024 || march_lds_bytes(P, ty, prec_bytes(prec)) > 65536)) --ty;
-        if (TXR * (ty + 2) <= 1024 && march_lds_bytes(P, ty, prec_bytes(prec)) <= 65536) {
-            s.ty = ty;
-            s.zc = std::max(1, std::min(8, P - 1));
-            return s;
+        // LDS-plane kernel: {V, planes, rows} per block
+        struct {
+            int V, zc, ty;
+        } t;
+        if (P <= 64) {
+            t = {4, 2, 6};
+        } else if (P <= 128) {
+            if (f64) t = {4, 4, 6};
+            else t = {8, 2, 14};
+        } else if (family == SH_PROLONG) {
+            if (P <= 256) t = f64 ? decltype(t){4, 32, 4} : f32 ? decltype(t){8, 16, 4} : decltype(t){8, 4, 6};
+            else t = f64 ? decltype(t){4, 64, 4} : f32 ? decltype(t){8, 16, 14} : decltype(t){8, 16, 6};
+        } else if (family == SH_UPDATE) {
+            t = {4, 32, 4};
+        } else if (P <= 256) {
+            t = f64 ? decltype(t){4, 4, 6} : f32 ? decltype(t){8, 2, 6} : decltype(t){4, 16, 4};
+        } else {
+            t = f64 ? decltype(t){4, 64, 4} : f32 ? decltype(t){4, 4, 6} : decltype(t){8, 64, 6};
         }
+        s.V = t.V;
+        s.zc = std::min(t.zc, P - 1);
+        // the prolongation reads its coarse rows from memory (L2): staging
+        // them in LDS pays on FP64 levels of pitch 512 only (21 us against 6
+        // at 31^3, where the staging's prologue is most of the kernel)
+        s.sg = (family == SH_PROLONG && !(f64 && P >= 512)) ? 0 : 1;
+        for (s.ty = std::min(t.ty, P - 1); s.ty >= 1; --s.ty)
+            if (stencil_fits(P, (int)prec_bytes(prec), s)) return s;
+        s.V = 8;  // rows too long for four values per thread
+        for (s.ty = std::min(t.ty, P - 1); s.ty >= 1; --s.ty)
+            if (stencil_fits(P, (int)prec_bytes(prec), s)) return s;
+        s.ty = 0;
+        s.sg = 1;
+    }
+    if (D == 2 && P >= 512) {
+        // rows of one thread: one re-reads its neighbours' rows from L2, which
+        // only the largest grids feel (2047^2: first smoothing 16 -> 14 us)
+        s.V = 4;
+        s.zc = P <= 2048 ? 2 : 8;
+        if (family == SH_SWEEP && prec_bytes(prec) < 8 && P <= 2048) s.V = 8;
+        return s;
     }
     const long per_chunk = (long)(P / s.V) * (D == 3 ? P : 1);
     const long target = 1L << 19;  // threads in flight: about 32 waves on each of 256 CUs
@@ -252,12 +297,28 @@ RShape pick_rshape(int D, int P, int pf) {
     // eight FP64 values per thread exceed the register budget of a 1024-thread block
     r.V = (P >= 8 && pf != P_F64) ? 8 : 4;
     r.pipe = 0;
+    const bool f64 = pf == P_F64, f32 = pf == P_F32;
+    const int Pc = P / 2;
     if (D == 3 && P >= 16) {
-        const int TXR = P / r.V, Pc = P / 2;
-        const int pipe = TXR <= 64 ? 2 : 1;
+        auto fits = [&](const RShape &c) {
+            return (2 * c.tyc + 1 + (c.pipe ? 2 : 0)) * (P / c.V) <= 1024 && (c.pipe < 2 || P / c.V <= 64) &&
+                   restrict_lds_bytes(D, P, pf, c) <= 65536;
+        };
+        // {V, coarse rows, coarse planes, pipe} per block, as for pick_shape
+        RShape t;
+        if (P <= 64) t = {4, 2, 2, f64 ? 2 : 3};
+        else if (P <= 128) t = {4, 4, 2, f64 ? 2 : 3};
+        else if (P <= 256) t = f64 ? RShape{4, 2, 16, 2} : RShape{4, 4, 8, f32 ? 2 : 3};
+        else t = f64 ? RShape{4, 3, 8, 0} : f32 ? RShape{8, 4, 32, 2} : RShape{8, 2, 32, 3};
+        t.tyc = std::min(t.tyc, Pc - 1);
+        t.zcc = std::min(t.zcc, Pc - 1);
+        for (; t.tyc >= 1; --t.tyc)
+            if (fits(t)) return t;
+        // rows too long for the shuffled form
+        const int pipe = P / r.V <= 64 ? 2 : 1;
         for (int tyc = std::min(7, Pc - 1); tyc >= 1; --tyc) {
             RShape c{r.V, tyc, 1, pipe};
-            if ((2 * tyc + 3) * TXR <= 1024 && restrict_lds_bytes(D, P, pf, c) <= 65536) {
+            if (fits(c)) {
                 const int ytiles = (Pc - 1 + tyc - 1) / tyc;
                 const int nzc = std::max(1, (1024 + ytiles - 1) / ytiles);
                 c.zcc = std::max(1, (Pc - 1 + nzc - 1) / nzc);
@@ -265,7 +326,7 @@ RShape pick_rshape(int D, int P, int pf) {
             }
         }
     }
-    const int TXR = P / r.V, Pc = P / 2;
+    const int TXR = P / r.V;
     const size_t acc = pf == P_F64 ? 8 : 4;
     if (D == 3) {
         int tyc = 7;
@@ -276,8 +337,12 @@ RShape pick_rshape(int D, int P, int pf) {
         const int nzc = std::max(1, (1024 + ytiles - 1) / ytiles);
         r.zcc = std::max(1, (Pc - 1 + nzc - 1) / nzc);
     } else {
+        // a block walks its rows with a barrier each: few rows per block until
+        // the blocks alone fill the chip (2047^2: 52 us at 16 rows, 10 at two)
+        r.V = P <= 4096 || f64 ? 4 : 8;
+        if (P == 4096 && !f64) r.V = 8;
         r.tyc = 1;
-        r.zcc = std::max(1, (Pc - 1 + 63) / 64);
+        r.zcc = P <= 256 ? 1 : P <= 2048 ? 2 : f64 ? 8 : 4;
     }
     return r;
 }
@@ -678,14 +743,27 @@ bool fusion_srb_possible(mg_ctx *h, int l) {
 
 void set_fused_srb(mg_ctx *h, int l, bool on) { h->lv[l].fsr = on && fusion_srb_possible(h, l); }
 
-// A fused-kernel shape that fits level l: the most coarse rows per tile that
-// the kernel allows, 16 coarse planes per chunk (fewer on small levels).
+// Shape of the fused smoothing + restriction on level L.  A block forms
+// 2 tyc + 5 rows of 2 zcc + 3 planes for its 2 tyc by 2 zcc owned ones, one
+// plane after another with a barrier each, so the best tile is the one of the
+// cheapest march among those whose blocks fit the 256 CUs at once: planes
+// times (rows + a fixed part per plane, about 20 rows' worth).  At 255^3 that
+// gives 8 coarse rows by 8 planes, 256 blocks: a refinement step of 315 us
+// against 345 for the best tile of up to three rows, and equal to the two
+// kernels; at 511^3 three rows by 85 planes.
 RShape default_srshape(const LevelPlan &L) {
-    for (int tyc = 3; tyc >= 1; --tyc) {
-        const RShape r{8, tyc, std::max(1, std::min(16, L.P / 2 - 1)), 3};
-        if (smooth_restrict_ok(L.P, L.prec, r)) return r;
+    RShape best{8, 1, 1, 3};
+    long cost = 0;
+    const int Nc = L.P / 2 - 1;
+    for (int tyc = 1; tyc <= Nc; ++tyc) {
+        const int ytiles = (Nc + tyc - 1) / tyc;
+        const int nz = std::max(1, 256 / ytiles);
+        const RShape r{8, tyc, std::max(1, (Nc + nz - 1) / nz), 3};
+        if (!smooth_restrict_ok(L.P, L.prec, r)) continue;
+        const long c = (long)(2 * r.zcc + 6) * (2 * tyc + 25) * ((ytiles + 255) / 256);
+        if (cost == 0 || c < cost) best = r, cost = c;
     }
-    return RShape{8, 1, 1, 3};
+    return best;
 }
 
 void set_fused(mg_ctx *h, bool on) {
@@ -1446,8 +1524,8 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
         // (launch shapes of the finite-difference kernels; the Q1 kernels have
         // none, but the finest level's sizes the reduction partials)
         if (nn > 1 && (!q1 || l == 0)) {
-            L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = pick_shape(dim, L.P, L.prec);
-            L.osh = pick_shape(dim, L.P, P_F64);  // FP64 rows dominate the update's registers
+            for (int f : {SH_SMOOTH, SH_SWEEP, SH_PROLONG}) L.shs[f] = pick_shape(dim, L.P, L.prec, f);
+            L.osh = pick_shape(dim, L.P, P_F64, SH_UPDATE);  // FP64 rows dominate the update's registers
             L.rsh = pick_rshape(dim, L.P, L.prec);
         }
         nn = (nn - 1) / 2;
@@ -1488,7 +1566,8 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
     if (fusable) {
         // the fused update that forms its right-hand side from r writes the
         // new residual to a second array (FP16/BF16 maps default to reading b)
-        h->su_r = prec_bytes(prec[0]) >= 4;
+        // (unless large and updating u in place: 906 -> 862 us at 511^3)
+        h->su_r = prec_bytes(prec[0]) >= 4 || (n >= 511 && o.defer_update == 0);
         h->off_R2 = off;
         off += fin;
     }
@@ -1511,9 +1590,11 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
         const long worst = ((long)(P0 / 4) * (dim == 3 ? P0 : 1) * (P0 - 1) + 63) / 64;
         const long worst_fused = (long)(P0 - 1) * (P0 - 1);
         maxp = (int)std::max<long>(std::max<long>(h->outer_parts, worst), worst_fused);
-        // the most rows per block the fused update allows (fewer for FP64 rows)
+        // the most rows per block the fused update allows (fewer for FP64
+        // rows); planes by the level's size as in pick_shape
+        const int fz = P0 <= 64 ? 2 : P0 <= 128 ? (prec[0] == P_F64 ? 8 : 4) : P0 <= 256 && prec[0] != P_F64 ? 32 : 64;
         for (int ty = std::max(1, std::min(4, P0 - 1)); ty >= 1; --ty) {
-            h->fsh = Shape{4, std::max(1, std::min(16, P0 - 1)), 256, 1, ty};
+            h->fsh = Shape{4, std::max(1, std::min(fz, P0 - 1)), 256, 1, ty};
             if (sweep_update_ok(P0, prec[0], h->fsh)) break;
         }
     }
@@ -2151,15 +2232,22 @@ namespace {
 // Longer z marches amortise a tile's pipeline prologue; the plane chunk is
 // chosen so that a launch still has about 4096 tiles.
 Shape batched_shape(int P, int prec, int copies) {
-    Shape s = pick_shape(3, P, prec);
+    Shape s{};
+    s.xcd = 1;
+    s.V = (P >= 8 && prec != P_F64) ? 8 : 4;
+    s.bs = 256;
+    if (P >= 16) {
+        // full rows, as many row groups as 1024 threads and 64 KiB of LDS
+        // allow (at most 14 output rows)
+        for (s.ty = std::min(14, P - 1); s.ty > 0; --s.ty)
+            if (stencil_fits(P, (int)prec_bytes(prec), s)) break;
+    }
     if (s.ty > 0) {
         const long ytiles = (P - 1 + s.ty - 1) / s.ty;
         const long nch = std::max(1L, (4096 + ytiles * copies - 1) / (ytiles * copies));
         s.zc = std::max(1, std::min(32, (int)((P - 1 + nch - 1) / nch)));
         return s;
     }
-    s.V = (P >= 8 && prec != P_F64) ? 8 : 4;
-    s.bs = 256;
     const long per_chunk = (long)(P / s.V) * P;
     const long nch = ((1L << 17) + per_chunk - 1) / per_chunk;
     s.zc = std::max(1, std::min((int)((P - 1 + nch - 1) / nch), 32));
@@ -2168,8 +2256,11 @@ Shape batched_shape(int P, int prec, int copies) {
 
 RShape batched_rshape(int P, int pf, int copies) {
     if (P >= 16) {
-        RShape r = pick_rshape(3, P, pf);
-        if (r.pipe >= 1) {
+        RShape r{(P >= 8 && pf != P_F64) ? 8 : 4, 1, 1, 1};
+        if (P / r.V <= 64) r.pipe = 2;
+        for (r.tyc = std::min(7, P / 2 - 1); r.tyc >= 1; --r.tyc)
+            if ((2 * r.tyc + 3) * (P / r.V) <= 1024 && restrict_lds_bytes(3, P, pf, r) <= 65536) break;
+        if (r.tyc >= 1) {
             const long ytiles = (P / 2 - 1 + r.tyc - 1) / r.tyc;
             const long nzc = std::max(1L, (4096 + ytiles * copies - 1) / (ytiles * copies));
             r.zcc = std::max(1, std::min(16, (int)((P / 2 - 1 + nzc - 1) / nzc)));
