@@ -342,7 +342,9 @@ mg_status_t mg_level_write(mg_handle h, int level, mg_buffer_t buf, const void *
                            mg_prec_t src_prec, void *stream);
 
 /* Copy a level buffer out to a dense device array in format dst_prec
- * (rounding to nearest even if narrower).  Async. */
+ * (rounding to nearest even if narrower).  Async.  After ir_solve, level 0's
+ * correction is that before the sweeps which the fused update of the last step
+ * applied (3-D: MG_SHAPE_FUSE; 2-D: all post-smoothing). */
 mg_status_t mg_level_read(mg_handle h, int level, mg_buffer_t buf, void *dst, mg_prec_t dst_prec,
                           void *stream);
 

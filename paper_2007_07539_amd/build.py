@@ -32,7 +32,7 @@ def _stale(obj, srcs):
     return any(os.path.getmtime(s) > t for s in srcs)
 
 
-SOURCES = (("mg_kernels.hip", True), ("mg_multi.hip", True), ("mg_tail.hip", True), ("mg_sweep_update.hip", True),
+SOURCES = (("mg_kernels.hip", True), ("mg_multi.hip", True), ("mg_tail.hip", True), ("mg_tile2d.hip", True), ("mg_sweep_update.hip", True),
            ("mg_smooth_restrict.hip", True),
            ("mg_rescale.hip", True),
            ("mg_cg.hip", True),

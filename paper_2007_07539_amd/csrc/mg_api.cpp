@@ -108,6 +108,7 @@ struct mg_ctx {
     size_t off_q1r = 0;    // Q1: fine residual ahead of its restriction (any level's, accumulator format)
     bool fuse_on = true;   // allow the fused last sweep + update on the finest level
     bool fused = false;    // ... and it is in use
+    bool fused2 = false;   // 2-D: the finest level's prolongation, post-smoothing and update as one kernel
     Shape fsh{4, 16, 256, 1, 4};
     bool su_r = true;      // ... forming b from r (else reading b back); needs the second residual array
     bool fuse_sr_on = true;  // allow the fused first smoothing + restriction on the finest level
@@ -625,6 +626,71 @@ int tail_level(const mg_ctx *h, int first) {
     return nl - 1;
 }
 
+// Whether level l of a 2-D grid runs its fused tile kernels (mg_tile2d.hip).
+bool tile2(const mg_ctx *h, int l) {
+    return h->dim == 2 && l + 1 < h->nl && !h->lv[l + 1].rescale &&
+           tile2d_ok(h->lv[l].P, h->opt.nu1, h->opt.nu2);
+}
+
+Tile2dArgs tile2_args(mg_ctx *h, int l) {
+    Tile2dArgs t;
+    t.q1 = h->q1;
+    t.P = h->lv[l].P;
+    t.prec = h->lv[l].prec;
+    t.pc = h->lv[l + 1].prec;
+    t.omega = h->opt.omega;
+    return t;
+}
+
+hipError_t enq_tile2_down(mg_ctx *h, hipStream_t st, RhsMode mode, int l, const void *rhs) {
+    const LevelPlan &L = h->lv[l], &C = h->lv[l + 1];
+    const double N = (double)points(2, L.n), s = sb(L.prec);
+    Tile2dArgs t = tile2_args(h, l);
+    t.nu = h->opt.nu1;
+    const bool from_r = l == 0 && mode == RHS_SCALED_R;
+    if (from_r) {
+        t.R = Rbuf(h);
+        t.scal = scal(h);
+        t.bout = bbuf(h, 0);
+    } else {
+        t.b = rhs;
+    }
+    t.cout = cbuf(h, l, 0);
+    t.bc = bbuf(h, l + 1);
+    RUN(h, st, "smooth_restrict", l, N * (from_r ? 8 + 2 * s : 2 * s) + (double)points(2, C.n) * sb(C.prec),
+        launch_tile2d_down(t, st));
+    h->cur[l] = 0;
+    return hipSuccess;
+}
+
+hipError_t enq_tile2_up(mg_ctx *h, hipStream_t st, int l, const void *rhs) {
+    const LevelPlan &L = h->lv[l], &C = h->lv[l + 1];
+    Tile2dArgs t = tile2_args(h, l);
+    t.nu = h->opt.nu2;
+    t.b = rhs;
+    t.cin = cbuf(h, l, h->cur[l]);
+    t.ec = cbuf(h, l + 1, h->cur[l + 1]);
+    t.cout = cbuf(h, l, h->cur[l] ^ 1);
+    RUN(h, st, "prolong_smooth", l, (double)points(2, L.n) * 3 * sb(L.prec) + (double)points(2, C.n) * sb(C.prec),
+        launch_tile2d_up(t, st));
+    h->cur[l] ^= 1;
+    return hipSuccess;
+}
+
+// The level's way down and up (skip: the last sweep is left to the fused
+// update; with the tile kernels, so is the whole way up).
+hipError_t enq_down(mg_ctx *h, hipStream_t st, RhsMode mode, int l, const void *rhs, bool warm) {
+    if (tile2(h, l) && !(l == 0 && warm)) return enq_tile2_down(h, st, mode, l, rhs);
+    return enq_vcycle_down(h, st, mode, l, rhs, warm);
+}
+
+hipError_t enq_up(mg_ctx *h, hipStream_t st, int l, const void *rhs, bool skip) {
+    if (skip && h->fused2) return hipSuccess;
+    if (tile2(h, l)) return enq_tile2_up(h, st, l, rhs);
+    const hipError_t e = enq_prolong(h, st, l, rhs);
+    return e != hipSuccess ? e : enq_post(h, st, l, rhs, skip);
+}
+
 // One V-cycle.  warm: the finest level starts from its current correction;
 // skip0: its last post-sweep is left to the fused sweep + update.
 hipError_t enq_vcycle(mg_ctx *h, hipStream_t st, RhsMode mode, bool warm = false, bool skip0 = false) {
@@ -637,7 +703,7 @@ hipError_t enq_vcycle(mg_ctx *h, hipStream_t st, RhsMode mode, bool warm = false
     if (lt < nl - 1) {
         // levels 0 .. lt-1 as separate launches, lt .. base fused
         for (int l = 0; l < lt; ++l) {
-            if ((e = enq_vcycle_down(h, st, mode, l, rhs[l], warm)) != hipSuccess) return e;
+            if ((e = enq_down(h, st, mode, l, rhs[l], warm)) != hipSuccess) return e;
         }
         TailArgs t = tail_args(h, lt);
         if (lt == 0 && mode == RHS_SCALED_R) {
@@ -654,18 +720,16 @@ hipError_t enq_vcycle(mg_ctx *h, hipStream_t st, RhsMode mode, bool warm = false
         if (lt == 0 && skip0) --t.nu2_first;
         RUN(h, st, "coarse_tail", lt, 0.0, launch_tail(t, st));
         for (int l = lt - 1; l >= 0; --l) {
-            if ((e = enq_prolong(h, st, l, rhs[l])) != hipSuccess) return e;
-            if ((e = enq_post(h, st, l, rhs[l], l == 0 && skip0)) != hipSuccess) return e;
+            if ((e = enq_up(h, st, l, rhs[l], l == 0 && skip0)) != hipSuccess) return e;
         }
         return hipSuccess;
     }
     for (int l = 0; l < nl - 1; ++l) {
-        if ((e = enq_vcycle_down(h, st, mode, l, rhs[l], warm)) != hipSuccess) return e;
+        if ((e = enq_down(h, st, mode, l, rhs[l], warm)) != hipSuccess) return e;
     }
     if ((e = enq_coarse(h, st, nl - 1)) != hipSuccess) return e;
     for (int l = nl - 2; l >= 0; --l) {
-        if ((e = enq_prolong(h, st, l, rhs[l])) != hipSuccess) return e;
-        if ((e = enq_post(h, st, l, rhs[l], l == 0 && skip0)) != hipSuccess) return e;
+        if ((e = enq_up(h, st, l, rhs[l], l == 0 && skip0)) != hipSuccess) return e;
     }
     return hipSuccess;
 }
@@ -686,7 +750,10 @@ bool fusion_possible(mg_ctx *h) {
 }
 
 // Whether a refinement step writes its residual to the other array.
-bool swaps_r(const mg_ctx *h) { return h->fused && h->su_r; }
+bool swaps_r(const mg_ctx *h) {
+    if (h->fused2) return h->lv[0].prec == P_F64 && !h->opt.residual_scaling;  // r is the sweeps' right-hand side
+    return h->fused && h->su_r;
+}
 
 // Whether the step postpones the solution update (the fused finite-difference
 // update, or the Q1 update).
@@ -768,8 +835,10 @@ RShape default_srshape(const LevelPlan &L) {
 
 void set_fused(mg_ctx *h, bool on) {
     h->fused = on && fusion_possible(h);
+    h->fused2 = !h->batched && !h->nrhs && tile2(h, 0) && tail_level(h, 0) > 0 && (!finest_alias(h) || h->off_R2);
     const LevelPlan &L = h->lv[0];
-    h->outer_parts = h->q1      ? q1_outer_blocks(h->dim, L.n, L.prec, L.q1s[2])
+    h->outer_parts = h->fused2   ? tile2d_update_blocks(L.P, L.prec, h->opt.nu2)
+                     : h->q1      ? q1_outer_blocks(h->dim, L.n, L.prec, L.q1s[2])
                      : h->fused ? sweep_update_blocks(L.P, h->fsh)
                                 : stencil_blocks(h->dim, L.P, L.osh);
 }
@@ -786,7 +855,7 @@ hipError_t enq_cycle(mg_ctx *h, hipStream_t st) {
     const int m = std::max(1, h->opt.cycles_per_step);
     for (int j = 0; j < m; ++j) {
         const RhsMode mode = alias ? RHS_ALIAS_R : j == 0 ? RHS_SCALED_R : RHS_B;
-        const hipError_t e = enq_vcycle(h, st, mode, j > 0, j == m - 1 && h->fused);
+        const hipError_t e = enq_vcycle(h, st, mode, j > 0, j == m - 1 && (h->fused || h->fused2));
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -798,7 +867,32 @@ hipError_t enq_update(mg_ctx *h, hipStream_t st) {
     LevelPlan &L = h->lv[0];
     const double hh = 1.0 / (double)(L.n + 1);
     const double N = (double)points(h->dim, L.n);
-    if (h->fused) {
+    if (h->fused2) {
+        // prolongation, post-smoothing and update: c, b, e, r read, r written,
+        // u read and written or c written to the ring
+        const double s = sb(L.prec);
+        const bool d = defers(h), alias = finest_alias(h);
+        Tile2dArgs t = tile2_args(h, 0);
+        t.nu = h->opt.nu2;
+        t.b = alias ? (const void *)Rbuf(h) : bbuf(h, 0);
+        t.cin = cbuf(h, 0, h->cur[0]);
+        t.ec = cbuf(h, 1, h->cur[1]);
+        t.R = Rbuf(h);
+        t.Rout = alias ? Rnext(h) : Rbuf(h);
+        t.U = Ubuf(h);
+        t.f = update_factor(h);
+        t.scal = scal(h);
+        t.part = part(h);
+        if (d) {
+            t.cdefer = h->ws + h->off_cdef;
+            t.ctr = at_ws<int>(h, h->off_dctr);
+            t.cstride = h->cdef_stride;
+            t.adef = at_ws<double>(h, h->off_adef);
+        }
+        RUN(h, st, d ? "prolong_smooth_update_defer" : "prolong_smooth_update", 0,
+            N * (16 + (alias ? 1 : 2) * s + (d ? s : 16)) + (double)points(2, h->lv[1].n) * sb(h->lv[1].prec),
+            launch_tile2d_up(t, st));
+    } else if (h->fused) {
         // bytes: c, b, r read, r written, u read and written; b formed from
         // r is not read; a postponed update writes c' instead of reading and
         // writing u
@@ -1571,6 +1665,11 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
         h->off_R2 = off;
         off += fin;
     }
+    // the 2-D update reads r as the right-hand side on its tiles' halos too
+    if (dim == 2 && prec[0] == P_F64 && !o.residual_scaling && tile2(h, 0)) {
+        h->off_R2 = off;
+        off += fin;
+    }
     if ((fusable || q1) && o.defer_update > 0) {
         const LevelPlan &L = h->lv[0];
         h->defer = o.defer_update;
@@ -1599,6 +1698,7 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
         }
     }
     maxp = std::max(maxp, flat_blocks(points(dim, n)));
+    if (tile2(h, 0)) maxp = std::max(maxp, tile2d_update_blocks(h->lv[0].P, prec[0], o.nu2));
     h->max_parts = maxp;
     h->off_part = off;
     off += align_up((size_t)maxp * 2 * sizeof(double), 256);
@@ -2018,6 +2118,7 @@ mg_status_t mg_set_shape(mg_handle h, int level, int kind, const int *p, int np)
     if (kind == MG_SHAPE_TAIL) {
         if (np != 1 || (p[0] != 0 && p[0] != 1)) return fail(MG_ERR_ARG, "the tail shape is {0|1}");
         h->tail_on = p[0] != 0;
+        set_fused(h, h->fused);  // a finest level inside the fused end has no fused update of its own
         drop_graph(h);
         return MG_OK;
     }

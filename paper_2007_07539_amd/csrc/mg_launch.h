@@ -217,6 +217,33 @@ bool tail_ok(const TailArgs &t);  // the levels fit (pointers are not looked at)
 hipError_t tail_prepare();
 hipError_t launch_tail(const TailArgs &t, hipStream_t st);
 
+// Fused stages of a 2-D level by tiles (mg_tile2d.hip; pitch a multiple of 4,
+// at most three sweeps).  Down: nu pre-sweeps from zero on the right-hand side
+// b (or round(R scal[1]), then also written to bout if given), residual and
+// restriction into bc (format pc); c to cout.  Up: c = cin + 4 P ec (format
+// pc), nu post-sweeps into cout, or, with Rout, the update: Rout = R - alpha A
+// c, U += alpha f c (or c into ring slot *ctr of cdefer and alpha into adef),
+// one norm partial per block.  b must not be Rout's array.
+struct Tile2dArgs {
+    bool q1 = false;
+    int P = 0, prec = 0, pc = 0, nu = 0;
+    double omega = 0.8;
+    const void *b = nullptr;
+    const double *R = nullptr, *scal = nullptr;
+    void *bout = nullptr, *cout = nullptr, *bc = nullptr;  // down
+    const void *cin = nullptr, *ec = nullptr;              // up
+    double *Rout = nullptr, *U = nullptr;
+    double f = 0.0;
+    void *cdefer = nullptr;
+    const int *ctr = nullptr;
+    size_t cstride = 0;
+    double *adef = nullptr, *part = nullptr;
+};
+bool tile2d_ok(int P, int nu1, int nu2);
+int tile2d_update_blocks(int P, int prec, int nu2);  // norm partials of the update
+hipError_t launch_tile2d_down(const Tile2dArgs &t, hipStream_t st);
+hipError_t launch_tile2d_up(const Tile2dArgs &t, hipStream_t st);
+
 // ---- batched instances -------------------------------------------------------
 // Per-(instance, level) arguments of one batched launch.
 struct BDesc {

@@ -30,8 +30,7 @@
 // level kernel stores a value.  So a V-cycle with the fused end is bitwise the
 // one without it.  The right-hand sides and corrections of the inner levels
 // are also written to the workspace, where the level kernels leave them.
-#include "mg_device.h"
-#include "mg_launch.h"
+#include "mg_level_math.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -62,50 +61,6 @@ struct TailKArgs {
     int zero16;                // LDS in use, in 16-byte chunks
 };
 
-__device__ __forceinline__ float rnd(float v, int p) {
-    if (p == P_F16) return widen(Store<f16>::from_acc(v));
-    if (p == P_BF16) return widen(Store<bf16>::from_acc(v));
-    return v;
-}
-__device__ __forceinline__ double rnd(double v, int) { return v; }
-// Round an FP64 value once into format p, as a value of A.
-template <class A> __device__ __forceinline__ A rnd64(double v, int p) {
-    if constexpr (std::is_same<A, double>::value) {
-        return v;
-    } else {
-        if (p == P_F16) return widen(Store<f16>::from_f64(v));
-        if (p == P_BF16) return widen(Store<bf16>::from_f64(v));
-        return (float)v;
-    }
-}
-template <class A> __device__ __forceinline__ A rnd_w(float v, int p) { return rnd(v, p); }
-template <class A> __device__ __forceinline__ A rnd_w(double v, int p) { return rnd64<A>(v, p); }
-
-// V values of a level vector in memory, in format p.
-template <class A, int V> __device__ __forceinline__ void mem_load(const void *m, int o, int p, A (&v)[V]) {
-    if constexpr (std::is_same<A, double>::value) {
-        load_row<double, V>(static_cast<const double *>(m) + o, v);
-    } else {
-        if (p == P_F16) load_row<f16, V>(static_cast<const f16 *>(m) + o, v);
-        else if (p == P_BF16) load_row<bf16, V>(static_cast<const bf16 *>(m) + o, v);
-        else load_row<float, V>(static_cast<const float *>(m) + o, v);
-    }
-}
-template <class T, int V, class A> __device__ __forceinline__ void mem_store_t(void *m, int o, const A (&v)[V]) {
-    T t[V];
-#pragma unroll
-    for (int i = 0; i < V; ++i) t[i] = store_as<T>(v[i]);
-    store_row<T, V>(static_cast<T *>(m) + o, t);
-}
-template <class A, int V> __device__ __forceinline__ void mem_store(void *m, int o, int p, const A (&v)[V]) {
-    if constexpr (std::is_same<A, double>::value) {
-        mem_store_t<double, V>(m, o, v);
-    } else {
-        if (p == P_F16) mem_store_t<f16, V>(m, o, v);
-        else if (p == P_BF16) mem_store_t<bf16, V>(m, o, v);
-        else mem_store_t<float, V>(m, o, v);
-    }
-}
 __device__ __forceinline__ void mem_store1(void *m, int o, int p, double v) {
     if (p == P_F64) static_cast<double *>(m)[o] = v;
     else if (p == P_F32) static_cast<float *>(m)[o] = (float)v;
