@@ -861,7 +861,7 @@ hipError_t enq_cycle(mg_ctx *h, hipStream_t st) {
     return hipSuccess;
 }
 
-// The update part: u, r, norms, alpha, and the norm readback (with the fused
+// The update part: u, r, norms, alpha, the norms to the host (with the fused
 // form, also the last post-smoothing sweep of the finest level).
 hipError_t enq_update(mg_ctx *h, hipStream_t st) {
     LevelPlan &L = h->lv[0];
@@ -915,8 +915,8 @@ hipError_t enq_update(mg_ctx *h, hipStream_t st) {
     }
     RUN(h, st, "norm_finalize", 0, 16.0 * h->outer_parts,
         launch_finalize(part(h), h->outer_parts, scal(h), h->ascale, st,
-                        defers(h) ? at_ws<int>(h, h->off_dctr) : nullptr));
-    return hipMemcpyAsync(h->host_scal, scal(h), 4 * sizeof(double), hipMemcpyDeviceToHost, st);
+                        defers(h) ? at_ws<int>(h, h->off_dctr) : nullptr, h->host_scal));
+    return hipSuccess;
 }
 
 // Add the postponed corrections to u (their slots in order) and empty the
@@ -1738,7 +1738,7 @@ mg_status_t mg_bind_workspace(mg_handle h, void *dev_ptr, size_t bytes, void *st
     if (bytes < h->ws_need) return fail(MG_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", bytes, h->ws_need);
     if (reinterpret_cast<uintptr_t>(dev_ptr) % 256) return fail(MG_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (!h->host_scal) HIPCHK(hipHostMalloc((void **)&h->host_scal, 4 * sizeof(double), hipHostMallocDefault));
+    if (!h->host_scal) HIPCHK(hipHostMalloc((void **)&h->host_scal, 4 * sizeof(double), hipHostMallocCoherent));
     drop_graph(h);
     h->ws = static_cast<char *>(dev_ptr);
     h->ws_bytes = bytes;
@@ -1982,8 +1982,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
         else HIPCHK(launch_fill_zero(Ubuf(h), align_up(L.elems * sizeof(double), 16), st));
     }
     const int fparts = flat_blocks(points(D, L.n));
-    HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st));
-    HIPCHK(hipMemcpyAsync(h->host_scal, scal(h), 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+    HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st, nullptr, h->host_scal));
     HIPCHK(hipStreamSynchronize(st));
     const double nb = h->host_scal[2];
     if (!std::isfinite(nb) || nb == 0.0) HIPCHK(enq_flush(h, st));  // u = 0 in the handle too
@@ -2001,8 +2000,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
     if (h->opt.use_initial_guess) {
         HIPCHK(launch_pack(D, P_F64, P_F64, L.n, L.P, u, Ubuf(h), st));
         HIPCHK(finest_resid(h, b, Ubuf(h), Rbuf(h), nullptr, st));
-        HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st));
-        HIPCHK(hipMemcpyAsync(h->host_scal, scal(h), 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+        HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st, nullptr, h->host_scal));
         HIPCHK(hipStreamSynchronize(st));
     }
     const bool graph = h->opt.use_graph && !h->prof;
@@ -2039,8 +2037,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
             cycle_queued = false;
             HIPCHK(enq_flush(h, st));
             HIPCHK(finest_resid(h, b, Ubuf(h), Rbuf(h), u, st));
-            HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st));
-            HIPCHK(hipMemcpyAsync(h->host_scal, scal(h), 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+            HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st, nullptr, h->host_scal));
             HIPCHK(hipStreamSynchronize(st));
             recursive = false;
             prev_rn = -1.0;
@@ -2083,8 +2080,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
     // final: recompute the true residual and copy u out
     HIPCHK(enq_flush(h, st));
     HIPCHK(finest_resid(h, b, Ubuf(h), Rbuf(h), u, st));
-    HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st));
-    HIPCHK(hipMemcpyAsync(h->host_scal, scal(h), 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+    HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st, nullptr, h->host_scal));
     HIPCHK(hipStreamSynchronize(st));
     rel = h->host_scal[2] / nb;
     finish_stats(k, rel);

@@ -75,9 +75,10 @@ hipError_t launch_resid_flat(int D, int n, int P, const double *b, const double 
                              double *uout, double inv_h2, double *part, hipStream_t st);
 // Reduce partials: scal = {alpha, 1/alpha, ||r||_2, ||r||_inf}.  scaling 0:
 // alpha = 1; scaling 1 + j: alpha = 2^j ||r||_inf (also for launch_m_finalize).
-// A non-null ctr is incremented (the slot counter of postponed updates).
+// A non-null ctr is incremented (the slot counter of postponed updates); a
+// non-null host (pinned host memory) receives the four scalars too.
 hipError_t launch_finalize(const double *part, int nparts, double *scal, int scaling, hipStream_t st,
-                           int *ctr = nullptr);
+                           int *ctr = nullptr, double *host = nullptr);
 // Dense <-> padded copies with format conversion (round to nearest even).
 hipError_t launch_pack(int D, int src_prec, int dst_prec, int n, int P, const void *src, void *dst,
                        hipStream_t st);
