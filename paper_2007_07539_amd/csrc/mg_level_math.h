@@ -28,6 +28,18 @@ template <class A> __device__ __forceinline__ A rnd64(double v, int p) {
 template <class A> __device__ __forceinline__ A rnd_w(float v, int p) { return rnd(v, p); }
 template <class A> __device__ __forceinline__ A rnd_w(double v, int p) { return rnd64<A>(v, p); }
 
+// The same for a run of values (one test of the format).
+template <int V> __device__ __forceinline__ void rnd_run(float (&v)[V], int p) {
+    if (p == P_F16) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] = widen(Store<f16>::from_acc(v[i]));
+    } else if (p == P_BF16) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] = widen(Store<bf16>::from_acc(v[i]));
+    }
+}
+template <int V> __device__ __forceinline__ void rnd_run(double (&)[V], int) {}
+
 // V values of a level vector in memory, in format p (o: element offset).
 template <class A, int V> __device__ __forceinline__ void mem_load(const void *m, size_t o, int p, A (&v)[V]) {
     if constexpr (std::is_same<A, double>::value) {

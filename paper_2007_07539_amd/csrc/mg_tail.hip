@@ -5,21 +5,25 @@
 // on MI355X), not bandwidth; here it costs one pass over LDS and a barrier.
 // A cycle whose finest level is that small runs as this one kernel alone.
 //
-// Work split.  A thread owns a segment of V consecutive x values of a level
-// (K segments on the largest Q1 level) and keeps the segment's right-hand side
-// and correction in registers from the first sweep to the residual, so a sweep
-// costs the vector reads of its neighbour rows and one write.  Values sit in
-// LDS in the accumulator format (they are values of the level's storage
-// format: exact), which takes the conversions off every neighbour read.  The
-// residual goes to the level's free correction buffer; the threads of the next
-// level gather their full-weighting sums from it straight into registers, so a
-// level costs nu1 + 1 barriers on the way down and nu2 + 1 on the way up.
+// Work split.  A wave issues one instruction in four cycles or more, and these
+// stages wait for nothing else, so what counts is instructions per wave: a
+// level of up to 1024 points gives a thread one point, a larger one (up to 16^3
+// or 64^2) a segment of four consecutive x values (two with Q1 elements, two
+// segments).  A thread keeps right-hand side and correction in registers from
+// the first sweep to the residual, so a sweep costs the reads of its neighbours
+// and one write.  Values sit in LDS in the accumulator format (they are values
+// of the level's storage format: exact), which takes the conversions off every
+// neighbour read.  The residual goes to the level's free correction buffer; the
+// threads of the next level gather their full-weighting sums from it straight
+// into registers, so a level costs nu1 + 1 barriers on the way down and nu2 + 1
+// on the way up, and none where one wave holds the level.  Nothing is stored to
+// memory before the end, since every barrier would wait for it.
 //
-// What bounds it: one CU's LDS and VALU issue on the largest level, barrier and
-// LDS latency below.  Measured per launch: 3-D from 15^3 in FP16 14.8 us (33.7
-// for the form that stored the level formats in LDS and walked single points),
-// 2-D from 63^2 in FP64 17.5 us (21 level launches, 75 us), 3-D Q1 from 11^3
-// with its 2^3 CG base 17.6 us (13 launches, 68 us).
+// What bounds it: instruction issue and LDS latency, about 550 cycles a stage
+// on the small levels and 1000 on the largest.  Measured per launch, before
+// (level formats in LDS, single points walked by every thread) and now: 3-D
+// from 15^3 in FP16 33.7 and 11.0; 2-D from 63^2 in FP64 21 launches, 75 us,
+// and 14.3; 3-D Q1 from 11^3 with its 2^3 CG base 13 launches, 68 us, and 14.8.
 //
 // The arithmetic is the level kernels' own, operation for operation: the
 // neighbour sum order (x-, x+, y-, y+, z-, z+; the Q1 sums of q1_weighted, or
@@ -50,8 +54,7 @@ struct TailKArgs {
     const void *b0;          // right-hand side of the first level in its format (padded), or
     const double *R, *scal;  // ... the FP64 residual: b = round(R scal[1]), also written to wb[0]
     void *wb[kTailLevels + 1], *wc[kTailLevels + 1];  // workspace vectors of the levels and the base
-    int off[kTailLevels + 1];  // LDS offset (elements of A) of a level's b, c0, c1
-    int base_off;              // ... and, in doubles, of the base arrays
+    int base_off;              // LDS offset, in doubles, of the base arrays
     unsigned precs;            // storage format of level l at bits 2l
     int pb, nb;                // base level: format, points per dimension
     int P0, nlev, nu1, nu2, nu2_first;
@@ -59,6 +62,9 @@ struct TailKArgs {
     double tol;                // CG base
     int maxit;
     int zero16;                // LDS in use, in 16-byte chunks
+    int single;                // first level whose threads hold single points
+    int small;                 // first of these that one wave holds
+    float inv_p0;              // 1 / P0
 };
 
 __device__ __forceinline__ void mem_store1(void *m, int o, int p, double v) {
@@ -70,9 +76,9 @@ __device__ __forceinline__ void mem_store1(void *m, int o, int p, double v) {
 
 // Elements of a level array in LDS: P + 1 planes (rows in 2-D), the row above
 // plane P's first that the corner neighbours of the last point reach, and the
-// element a segment's right neighbour reaches.
+// element a segment's right neighbour reaches; a multiple of 4.
 __host__ __device__ __forceinline__ int lds_elems(int D, int P) {
-    return (D == 3 ? (P + 1) * P * P + P : (P + 1) * P) + 4;
+    return ((D == 3 ? (P + 1) * P * P + P : (P + 1) * P) + 7) & ~3;
 }
 
 // LDS rows
@@ -84,22 +90,37 @@ struct Item {
     int o, x0, y, z;
     bool on;  // an interior row
 };
-template <int D, int V> __device__ __forceinline__ Item item(int s, int P) {
-    // s < 2^12 and P <= 64: the reciprocal product is exact after truncation
+// inv_txr, inv_p: float reciprocals of P / V and P (s < 2^12, P <= 64: the
+// truncated products are exact).  Finite-difference pitches are powers of two.
+template <int D, int OP, int V> __device__ __forceinline__ Item item(int s, int P, float inv_txr, float inv_p) {
     Item t;
     const int TXR = P / V;
-    const int row = (int)(((float)s + 0.5f) / (float)TXR);
     t.o = s * V;
-    t.x0 = (s - row * TXR) * V;
+    int row;
+    if constexpr (OP == 0) {
+        const int lg = 31 - __clz(P), lt = lg - (V == 4 ? 2 : V == 2 ? 1 : 0);
+        row = s >> lt;
+        t.x0 = (s & (TXR - 1)) * V;
+        if (D == 3) {
+            t.z = row >> lg;
+            t.y = row & (P - 1);
+        }
+    } else {
+        row = (int)(((float)s + 0.5f) * inv_txr);
+        t.x0 = (s - row * TXR) * V;
+        if (D == 3) {
+            t.z = (int)(((float)row + 0.5f) * inv_p);
+            t.y = row - t.z * P;
+        }
+    }
     if (D == 3) {
-        t.z = (int)(((float)row + 0.5f) / (float)P);
-        t.y = row - t.z * P;
         t.on = t.z >= 1 && t.z < P && t.y >= 1;
     } else {
         t.z = row;
         t.y = 0;
         t.on = t.z >= 1 && t.z < P;
     }
+    if (V == 1) t.on = t.on && t.x0 >= 1;  // single points: the ghost keeps its zero
     return t;
 }
 
@@ -270,12 +291,15 @@ __device__ __forceinline__ void gather(const A *r, int X0, int Y, int Z, int P, 
 // rounded into format p.
 template <int D, int OP, class A, class W, int V>
 __device__ __forceinline__ void prolong(const A (&c)[V], const W *e, const Item &t, int Pc, int p, A (&out)[V]) {
-    constexpr int H = V / 2;
+    constexpr int H = V == 1 ? 1 : V / 2;  // (a single point takes one coarse value, or two)
     const int X0 = t.x0 >> 1;
     auto crow = [&](int Y, int Z, W (&v)[H + 1]) {
         const W *q = e + (D == 3 ? (Z * Pc + Y) * Pc : Z * Pc) + X0;
+        W m[H];
+        seg<W, H>(q, m);  // X0 is a multiple of H
 #pragma unroll
-        for (int j = 0; j <= H; ++j) v[j] = q[j];
+        for (int j = 0; j < H; ++j) v[j] = m[j];
+        v[H] = q[H];
     };
     const int z0 = t.z >> 1, z1 = (t.z + 1) >> 1, y0 = t.y >> 1, y1 = (t.y + 1) >> 1;
     W S[H + 1];
@@ -299,8 +323,9 @@ __device__ __forceinline__ void prolong(const A (&c)[V], const W *e, const Item 
         const W k1 = W(0.5) * k0;
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-            const W q = (i & 1) ? S[i >> 1] + S[(i >> 1) + 1] : S[i >> 1];
-            out[i] = rnd_w<A>((W)c[i] + ((i & 1) ? k1 : k0) * q, p);
+            const bool odd = V == 1 ? (t.x0 & 1) : (i & 1);
+            const W q = odd ? S[i >> 1] + S[(i >> 1) + 1] : S[i >> 1];
+            out[i] = rnd_w<A>((W)c[i] + (odd ? k1 : k0) * q, p);
         }
     } else {
         W a[H + 1], b[H + 1], d[H + 1];
@@ -318,7 +343,7 @@ __device__ __forceinline__ void prolong(const A (&c)[V], const W *e, const Item 
         }
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-            W s = S[i >> 1] + S[(i + 1) >> 1];
+            W s = S[i >> 1] + (V == 1 ? ((t.x0 & 1) ? S[1] : S[0]) : S[(i + 1) >> 1]);
             s *= W(D == 3 ? 0.5 : 1.0);
             out[i] = rnd_w<A>((W)c[i] + s, p);
         }
@@ -340,23 +365,47 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
     return s;
 }
 
+// Orders the LDS accesses of one wave (which the hardware runs in order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // CG on a base level of N <= blockDim.x points (k_cg_base, one point per
-// thread: x, r, q in registers, p in LDS with zero ghosts); returns x.
-template <int D, int OP, class AB>
-__device__ __forceinline__ AB cg_point(AB bi, bool on, AB *p, int o, int P, double tol, int maxit, double *red) {
+// thread: x, r, q in registers, p in LDS with zero ghosts); returns x.  WAVE:
+// N <= 64, called by the first wave alone: no barriers, and the sums start at
+// the butterfly step that first meets a point (the earlier steps and the other
+// waves of k_cg_base add zeros).
+template <int D, int OP, class AB, bool WAVE>
+__device__ __forceinline__ AB cg_point(AB bi, bool on, AB *p, int o, int P, int N, double tol, int maxit, double *red) {
     const int Z = D == 3 ? P * P : P;
     AB x = AB(0), r = on ? bi : AB(0), pi = r;
     int slot = 0;
+    const int top = N > 32 ? 32 : N > 16 ? 16 : N > 8 ? 8 : N > 4 ? 4 : 2;
     auto sum = [&](double v) {
-        const double s = wg_sum(v, red + 16 * slot);
-        slot ^= 1;
-        return s;
+        if constexpr (WAVE) {
+            for (int off = top; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+            const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+            const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+            const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
+            return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+        } else {
+            const double s = wg_sum(v, red + 16 * slot);
+            slot ^= 1;
+            return s;
+        }
+    };
+    auto sync = [&]() {
+        if constexpr (WAVE) wave_sync();
+        else __syncthreads();
     };
     if (on) p[o] = pi;
     double rr = sum((double)r * (double)r);
     const double stop = tol * sqrt(rr);
+    if (WAVE) wave_sync();
     for (int k = 0; k < maxit && sqrt(rr) > stop; ++k) {
-        // (the barrier of the last sum follows every write of p)
+        // (a barrier follows every write of p: that of the first sum, or the
+        // one at the end of the loop)
         AB q = AB(0);
         if (on) {
             if (OP == 1) {
@@ -380,45 +429,178 @@ __device__ __forceinline__ AB cg_point(AB bi, bool on, AB *p, int o, int P, doub
         const double rr_new = sum((double)r * (double)r);
         const AB beta = (AB)(rr_new / rr);
         pi = fmaT<AB>(beta, pi, r);
-        if (on) p[o] = pi;  // every thread read its neighbours before the last two barriers
-        __syncthreads();
+        if (WAVE) wave_sync();
+        if (on) p[o] = pi;  // every thread read its neighbours before the last two sums
+        sync();
         rr = rr_new;
     }
     return x;
 }
 
 // Base level: right-hand side gathered from the fine residual r (pitch P),
-// solved, the correction left in ec (W, zero ghosts) and in the workspace.
-template <int D, int OP, class A, class AB, class W>
-__device__ __forceinline__ void base_solve(const TailKArgs &a, const A *r, int P, AB *p, W *ec, double *red) {
+// solved, the correction left in ec (W, zero ghosts); both are returned for the
+// workspace copy.  WAVE: called by the first wave alone (at most 64 points).
+template <int D, int OP, class A, class AB, class W, bool WAVE>
+__device__ __forceinline__ void base_solve(const TailKArgs &a, const A *r, int P, AB *p, W *ec, double *red, bool on,
+                                           int X, int Y, int Z, int o, double &bout, double &cout) {
     const int n = a.nb, Pb = P / 2, N = D == 3 ? n * n * n : n * n;
-    const int i = (int)threadIdx.x;
-    const bool on = i < N;
-    int X = 1, Y = D == 3 ? 1 : 0, Z = 1;
-    if (n > 1) {
-        X = i % n + 1;
-        Y = D == 3 ? (i / n) % n + 1 : 0;
-        Z = D == 3 ? i / (n * n) + 1 : i / n + 1;
-    }
-    const int o = D == 3 ? (Z * Pb + Y) * Pb + X : Z * Pb + X;
     AB bv = AB(0);
     if (on) {
         A g[1];
         gather<D, OP, A, 1>(r, X, Y, Z, P, g);
         if constexpr (std::is_same<AB, double>::value) bv = a.pb == P_F64 ? (double)g[0] : (double)rnd64<float>(g[0], a.pb);
         else bv = rnd64<float>((double)g[0], a.pb);
-        mem_store1(a.wb[a.nlev], o, a.pb, (double)bv);
     }
     AB x;
     if (n == 1) {
         x = OP ? bv * AB(0.375) : bv / AB(2 * D);
     } else {
-        x = cg_point<D, OP, AB>(bv, on, p, o, Pb, a.tol, a.maxit, red);
+        x = cg_point<D, OP, AB, WAVE>(bv, on, p, o, Pb, N, a.tol, a.maxit, red);
     }
-    if (on) {
-        if constexpr (std::is_same<AB, float>::value) x = rnd(x, a.pb);
-        ec[o] = (W)x;
-        mem_store1(a.wc[a.nlev], o, a.pb, (double)x);
+    if constexpr (std::is_same<AB, float>::value) x = rnd(x, a.pb);
+    if (on) ec[o] = (W)x;
+    bout = (double)bv;
+    cout = (double)x;
+}
+
+// What the level passes share.
+template <class A> struct Ctx {
+    const TailKArgs &a;
+    A k;
+    __device__ __forceinline__ int prec(int l) const { return (int)(a.precs >> (2 * l)) & 3; }
+    // levels from a.small on have at most 64 points: one wave holds them, and
+    // its LDS accesses need no barrier (the other waves wait at the next one)
+    __device__ __forceinline__ void sync(int l) const {
+        if (l >= a.small) wave_sync();
+        else __syncthreads();
+    }
+    template <int D, int OP, int V, int K> __device__ __forceinline__ void items(int l, Item (&it)[K]) const {
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+            it[q] = item<D, OP, V>((int)(threadIdx.x + q * blockDim.x), a.P0 >> l, a.inv_p0 * (float)(V << l),
+                                   a.inv_p0 * (float)(1 << l));
+    }
+};
+
+// The first level's right-hand side, from memory.
+template <int D, int OP, class A, int V, int K>
+__device__ __forceinline__ void fetch_rhs(const Ctx<A> &x, A (&b)[K][V]) {
+    Item it[K];
+    x.template items<D, OP, V, K>(0, it);
+    const int p = x.prec(0);
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        if (!it[q].on) continue;
+        if (x.a.R) {
+            double r[V];
+            load_row<double, V>(x.a.R + it[q].o, r);
+            const double inv = x.a.scal[1];
+#pragma unroll
+            for (int i = 0; i < V; ++i) b[q][i] = rnd64<A>(r[i] * inv, p);
+            if (it[q].x0 == 0) b[q][0] = A(0);
+        } else {
+            mem_load<A, V>(x.a.b0, it[q].o, p, b[q]);
+        }
+    }
+}
+
+// Level l on the way down (its arrays b, c0, c1 at B): the right-hand side
+// gathered from the residual rf of the level above (l > 0; else b holds it),
+// nu1 sweeps, the residual into the free correction buffer.
+template <int D, int OP, class A, int V, int K>
+__device__ __forceinline__ void level_down(const Ctx<A> &x, int l, A *B, const A *rf, A (&b)[K][V]) {
+    const int P = x.a.P0 >> l, E = lds_elems(D, P), p = x.prec(l), nu1 = x.a.nu1;
+    A *const C0 = B + E, *const C1 = C0 + E;
+    const A k = x.k;
+    Item it[K];
+    A c[K][V];
+    x.template items<D, OP, V, K>(l, it);
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        if (!it[q].on) continue;
+        if (l > 0) {
+            gather<D, OP, A, V>(rf, it[q].x0, it[q].y, it[q].z, 2 * P, b[q]);
+            rnd_run<V>(b[q], p);
+            if (it[q].x0 == 0) b[q][0] = A(0);
+        }
+        put<A, V>(B + it[q].o, b[q]);
+#pragma unroll
+        for (int i = 0; i < V; ++i) c[q][i] = k * b[q][i];
+        rnd_run<V>(c[q], p);
+        put<A, V>(C0 + it[q].o, c[q]);
+    }
+    x.sync(l);
+    for (int s = 1; s <= nu1; ++s) {
+        const A *src = (s & 1) ? C0 : C1;
+        A *dst = (s & 1) ? C1 : C0;
+        const bool res = s == nu1;
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            if (!it[q].on) continue;
+            A lc[V], v[V];
+            apply<D, OP, A, V>(src, it[q], P, c[q], lc);
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                const A r = b[q][i] - lc[i];
+                v[i] = res ? r : fmaT<A>(k, r, c[q][i]);
+            }
+            if (!res) rnd_run<V>(v, p);
+            if (it[q].x0 == 0) v[0] = A(0);
+            put<A, V>(dst + it[q].o, v);
+#pragma unroll
+            for (int i = 0; i < V; ++i) c[q][i] = v[i];
+        }
+        x.sync(l);
+    }
+}
+
+// Level l on the way up: the coarse correction ec (W) prolongated onto its
+// correction, nu2 sweeps.  The first level's result goes to the workspace.
+template <int D, int OP, class A, int V, int K, class W>
+__device__ __forceinline__ void level_up(const Ctx<A> &x, int l, A *B, const W *ec) {
+    const int P = x.a.P0 >> l, E = lds_elems(D, P), p = x.prec(l), nu2 = l == 0 ? x.a.nu2_first : x.a.nu2;
+    const A k = x.k;
+    auto C = [&](int j) { return B + (1 + j) * E; };
+    int y = (x.a.nu1 & 1) ? 0 : 1;  // buffer of the current correction
+    Item it[K];
+    A b[K][V], c[K][V];
+    x.template items<D, OP, V, K>(l, it);
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        if (!it[q].on) continue;
+        A cv[V];
+        seg<A, V>(C(y) + it[q].o, cv);
+        seg<A, V>(B + it[q].o, b[q]);
+        prolong<D, OP, A, W, V>(cv, ec, it[q], P / 2, p, c[q]);
+        put<A, V>(C(y ^ 1) + it[q].o, c[q]);
+    }
+    y ^= 1;
+    x.sync(l);
+    for (int s = 0; s < nu2; ++s) {
+        const bool last = l == 0 && s + 1 == nu2;
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            if (!it[q].on) continue;
+            A lc[V], v[V];
+            apply<D, OP, A, V>(C(y), it[q], P, c[q], lc);
+#pragma unroll
+            for (int i = 0; i < V; ++i) v[i] = fmaT<A>(k, b[q][i] - lc[i], c[q][i]);
+            rnd_run<V>(v, p);
+            if (it[q].x0 == 0) v[0] = A(0);
+            if (!last) put<A, V>(C(y ^ 1) + it[q].o, v);
+#pragma unroll
+            for (int i = 0; i < V; ++i) c[q][i] = v[i];
+        }
+        y ^= 1;
+        if (!last) x.sync(l);
+    }
+    if (l == 0) {
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            if (!it[q].on) continue;
+            mem_store<A, V>(x.a.wc[0], it[q].o, p, c[q]);
+            if (x.a.R) mem_store<A, V>(x.a.wb[0], it[q].o, p, b[q]);
+        }
     }
 }
 
@@ -426,142 +608,95 @@ template <int D, int OP, class A>
 __global__ __launch_bounds__(kThreads) void k_tail(const TailKArgs a) {
     constexpr int V = TailSplit<OP>::V, K = TailSplit<OP>::K;
     extern __shared__ __align__(16) unsigned char smem[];
-    A *lds = reinterpret_cast<A *>(smem);
-    const A k = (A)a.k;
-    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
-    Item it[K];
-    A b[K][V], c[K][V];
+    A *const lds = reinterpret_cast<A *>(smem);
+    const Ctx<A> x{a, (A)a.k};
+    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x, nlev = a.nlev;
+    auto elems = [&](int l) { return lds_elems(D, a.P0 >> l); };
     // the first level's right-hand side is on its way while LDS is cleared
-    {
-        const int p = (int)(a.precs & 3u);
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            it[q] = item<D, V>(tid + q * nthr, a.P0);
-            if (!it[q].on) continue;
-            if (a.R) {
-                double r[V];
-                load_row<double, V>(a.R + it[q].o, r);
-                const double inv = a.scal[1];
-#pragma unroll
-                for (int i = 0; i < V; ++i) b[q][i] = rnd64<A>(r[i] * inv, p);
-                if (it[q].x0 == 0) b[q][0] = A(0);
-            } else {
-                mem_load<A, V>(a.b0, it[q].o, p, b[q]);
-            }
-        }
-    }
+    A b[K][V], b1[1][1];
+    if (a.single > 0) fetch_rhs<D, OP, A, V, K>(x, b);
+    else fetch_rhs<D, OP, A, 1, 1>(x, b1);
     for (int i = tid; i < a.zero16; i += nthr) reinterpret_cast<uint4 *>(smem)[i] = uint4{0u, 0u, 0u, 0u};
     __syncthreads();
-    auto elems = [&](int P) { return lds_elems(D, P); };
     // down: pre-smoothing, residual, restriction
-    for (int l = 0; l < a.nlev; ++l) {
-        const int P = a.P0 >> l, E = elems(P), p = (int)(a.precs >> (2 * l)) & 3;
-        A *const B = lds + a.off[l], *const C0 = B + E, *const C1 = C0 + E;
-        if (l > 0) {
-            const A *r = lds + a.off[l - 1] + elems(2 * P) * (1 + (a.nu1 & 1));
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                it[q] = item<D, V>(tid + q * nthr, P);
-                if (!it[q].on) continue;
-                gather<D, OP, A, V>(r, it[q].x0, it[q].y, it[q].z, 2 * P, b[q]);
-#pragma unroll
-                for (int i = 0; i < V; ++i) b[q][i] = rnd(b[q][i], p);
-                if (it[q].x0 == 0) b[q][0] = A(0);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            if (!it[q].on) continue;
-            put<A, V>(B + it[q].o, b[q]);
-            if (l > 0 || a.R) mem_store<A, V>(a.wb[l], it[q].o, p, b[q]);
-#pragma unroll
-            for (int i = 0; i < V; ++i) c[q][i] = rnd(k * b[q][i], p);
-            put<A, V>(C0 + it[q].o, c[q]);
-        }
-        __syncthreads();
-        // sweeps 1 .. nu1 - 1 and, last, the residual into the free buffer
-        for (int s = 1; s <= a.nu1; ++s) {
-            const A *src = (s & 1) ? C0 : C1;
-            A *dst = (s & 1) ? C1 : C0;
-            const bool res = s == a.nu1;
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                if (!it[q].on) continue;
-                A lc[V], v[V];
-                apply<D, OP, A, V>(src, it[q], P, c[q], lc);
-#pragma unroll
-                for (int i = 0; i < V; ++i) {
-                    const A r = b[q][i] - lc[i];
-                    v[i] = res ? r : rnd(fmaT<A>(k, r, c[q][i]), p);
-                }
-                if (it[q].x0 == 0) v[0] = A(0);
-                put<A, V>(dst + it[q].o, v);
-#pragma unroll
-                for (int i = 0; i < V; ++i) c[q][i] = v[i];
-            }
-            __syncthreads();
-        }
+    const int rbuf = 1 + (a.nu1 & 1);  // the residual's buffer among a level's arrays
+    A *B = lds;
+    const A *rf = nullptr;
+    for (int l = 0; l < nlev; ++l) {
+        if (l < a.single) level_down<D, OP, A, V, K>(x, l, B, rf, b);
+        else level_down<D, OP, A, 1, 1>(x, l, B, rf, b1);
+        rf = B + rbuf * elems(l);
+        B += 3 * elems(l);
     }
     // base level
     double *const base = reinterpret_cast<double *>(smem) + a.base_off;  // [32 sums][c][p]
-    const int Pl = a.P0 >> (a.nlev - 1);
-    const int Eb = elems(Pl / 2);
-    const A *rl = lds + a.off[a.nlev - 1] + elems(Pl) * (1 + (a.nu1 & 1));
+    const int Pl = a.P0 >> (nlev - 1), Pb = Pl / 2;
+    const int Eb = lds_elems(D, Pb);
     double *const ecd = base + 32;
     A *const eca = reinterpret_cast<A *>(ecd);
     const bool wide = std::is_same<A, double>::value || a.pb == P_F64;  // interpolation from the base in FP64
-    if (a.pb == P_F64) {
-        base_solve<D, OP, A, double, double>(a, rl, Pl, ecd + Eb, ecd, base);
-    } else {
-        base_solve<D, OP, A, float, A>(a, rl, Pl, reinterpret_cast<float *>(ecd + Eb), eca, base);
+    const int N = D == 3 ? a.nb * a.nb * a.nb : a.nb * a.nb;
+    const bool bon = tid < N;
+    int bX = 1, bY = D == 3 ? 1 : 0, bZ = 1;
+    if (a.nb > 1) {
+        bX = tid % a.nb + 1;
+        bY = D == 3 ? (tid / a.nb) % a.nb + 1 : 0;
+        bZ = D == 3 ? tid / (a.nb * a.nb) + 1 : tid / a.nb + 1;
     }
-    __syncthreads();
-    // up: prolongation, correction and post-smoothing.  The correction sits in
-    // C0 after an odd number of pre-sweeps, else in C1.
-    int cur = (a.nu1 & 1) ? 0 : 1;
-    for (int l = a.nlev - 1; l >= 0; --l) {
-        const int P = a.P0 >> l, E = elems(P), p = (int)(a.precs >> (2 * l)) & 3;
-        A *const B = lds + a.off[l];
-        auto C = [&](int j) { return B + (1 + j) * E; };
-        const int nu2 = l == 0 ? a.nu2_first : a.nu2;
-        int x = (a.nu1 & 1) ? 0 : 1;  // buffer of the current correction
-        // the coarse correction: the base's, or the buffer its last sweep wrote
-        const A *ec = l + 1 < a.nlev ? lds + a.off[l + 1] + elems(P / 2) * (1 + cur) : eca;
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            it[q] = item<D, V>(tid + q * nthr, P);
-            if (!it[q].on) continue;
-            A cv[V];
-            seg<A, V>(C(x) + it[q].o, cv);
-            seg<A, V>(B + it[q].o, b[q]);
-            if (!std::is_same<A, double>::value && l + 1 == a.nlev && wide)
-                prolong<D, OP, A, double, V>(cv, ecd, it[q], P / 2, p, c[q]);
-            else
-                prolong<D, OP, A, A, V>(cv, ec, it[q], P / 2, p, c[q]);
-            put<A, V>(C(x ^ 1) + it[q].o, c[q]);
+    const int bo = D == 3 ? (bZ * Pb + bY) * Pb + bX : bZ * Pb + bX;
+    double bb = 0.0, bc = 0.0;
+#define MG_BASE(AB, W, WV, EC) \
+    base_solve<D, OP, A, AB, W, WV>(a, rf, Pl, reinterpret_cast<AB *>(ecd + Eb), EC, base, bon, bX, bY, bZ, bo, bb, bc)
+    if (N <= 64) {
+        if (tid < 64) {
+            if (a.pb == P_F64) MG_BASE(double, double, true, ecd);
+            else MG_BASE(float, A, true, eca);
         }
-        x ^= 1;
+        x.sync(nlev - 1);
+    } else {
+        if (nlev - 1 >= a.small) __syncthreads();  // the residual came from one wave
+        if (a.pb == P_F64) MG_BASE(double, double, false, ecd);
+        else MG_BASE(float, A, false, eca);
         __syncthreads();
-        for (int s = 0; s < nu2; ++s) {
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                if (!it[q].on) continue;
-                A lc[V], v[V];
-                apply<D, OP, A, V>(C(x), it[q], P, c[q], lc);
-#pragma unroll
-                for (int i = 0; i < V; ++i) v[i] = rnd(fmaT<A>(k, b[q][i] - lc[i], c[q][i]), p);
-                if (it[q].x0 == 0) v[0] = A(0);
-                put<A, V>(C(x ^ 1) + it[q].o, v);
-#pragma unroll
-                for (int i = 0; i < V; ++i) c[q][i] = v[i];
-            }
-            x ^= 1;
-            __syncthreads();
+    }
+#undef MG_BASE
+    // up: prolongation, correction and post-smoothing.  A level's correction
+    // sits in c0 after an odd number of pre-sweeps, else in c1, and ends in
+    // array xf.
+    const int xf = 1 + ((a.nu1 & 1) ^ (a.nu2 & 1));
+    const A *ec = eca;
+    for (int l = nlev - 1; l >= 0; --l) {
+        B -= 3 * elems(l);
+        if (l + 1 == a.small) __syncthreads();  // the coarse correction came from one wave
+        const bool from_wide = !std::is_same<A, double>::value && l + 1 == nlev && wide;
+        if (l < a.single) {
+            if (from_wide) level_up<D, OP, A, V, K, double>(x, l, B, ecd);
+            else level_up<D, OP, A, V, K, A>(x, l, B, ec);
+        } else {
+            if (from_wide) level_up<D, OP, A, 1, 1, double>(x, l, B, ecd);
+            else level_up<D, OP, A, 1, 1, A>(x, l, B, ec);
         }
-        cur = x;
-#pragma unroll
-        for (int q = 0; q < K; ++q)
-            if (it[q].on) mem_store<A, V>(a.wc[l], it[q].o, p, c[q]);
+        ec = B + xf * elems(l);
+    }
+    // the inner levels' vectors, which the level kernels leave in the workspace.
+    // Copied here and not on the way, where the barriers would wait for the
+    // stores; whole arrays, ghosts (zeros) and all.
+    B = lds;
+    for (int l = 1; l < nlev; ++l) {
+        B += 3 * elems(l - 1);
+        const int P = a.P0 >> l, p = x.prec(l), n = (D == 3 ? P * P : P) * P, E = elems(l);
+        constexpr int VC = OP ? 2 : 4;
+        for (int i = VC * tid; i < n; i += VC * nthr) {
+            A v[VC];
+            seg<A, VC>(B + i, v);
+            mem_store<A, VC>(a.wb[l], i, p, v);
+            seg<A, VC>(B + xf * E + i, v);
+            mem_store<A, VC>(a.wc[l], i, p, v);
+        }
+    }
+    if (bon) {
+        mem_store1(a.wb[nlev], bo, a.pb, bb);
+        mem_store1(a.wc[nlev], bo, a.pb, bc);
     }
 }
 
@@ -581,29 +716,30 @@ bool plan_tail(const TailArgs &t, Plan &q) {
     TailKArgs &k = q.k;
     k = TailKArgs{};
     size_t off = 0;
-    int segs0 = 0;
+    int threads = 64;
     for (int l = 0; l < t.nlev; ++l) {
         const int P = t.P0 >> l;
         if ((P << l) != t.P0 || P % V || P < 4 || P > 64) return false;
         if ((t.prec[l] == P_F64) != f64) return false;  // one accumulator format
-        const int segs = (P / V) * P * (t.D == 3 ? P : 1);
-        if (l == 0) segs0 = segs;
-        k.off[l] = (int)(off / sa);
+        const int pts = P * P * (t.D == 3 ? P : 1), segs = pts / V;
+        if (pts > kThreads) k.single = l + 1;
+        if (pts > 64) k.small = l + 1;
+        threads = std::max(threads, pts > kThreads ? (segs + K - 1) / K : pts);
         off += 3 * (size_t)lds_elems(t.D, P) * sa;
-        off = (off + 15) & ~(size_t)15;
         k.precs |= (unsigned)t.prec[l] << (2 * l);
     }
+    if (threads > kThreads) return false;
+    off = (off + 15) & ~(size_t)15;
     const int Pl = t.P0 >> (t.nlev - 1), Pb = Pl / 2;
     if (Pl % 2 || t.nb != Pb - 1) return false;
     const int N = t.D == 3 ? t.nb * t.nb * t.nb : t.nb * t.nb;
-    if (t.nb < 1 || N > kThreads || segs0 > K * kThreads) return false;
+    if (t.nb < 1 || N > kThreads) return false;
     k.base_off = (int)(off / 8);
     off += 8 * (32 + (size_t)lds_elems(t.D, Pb) * (t.nb > 1 ? 2 : 1));
     off = (off + 15) & ~(size_t)15;
     if (off > kLdsMax) return false;
     q.lds = off;
-    q.threads = std::min(kThreads, std::max((segs0 + K - 1) / K, N));
-    q.threads = (q.threads + 63) / 64 * 64;
+    q.threads = (std::max(threads, N) + 63) / 64 * 64;
     k.b0 = t.b0;
     k.R = t.R;
     k.scal = t.scal;
@@ -622,6 +758,7 @@ bool plan_tail(const TailArgs &t, Plan &q) {
     k.tol = t.base_tol;
     k.maxit = t.base_maxit;
     k.zero16 = (int)(off / 16);
+    k.inv_p0 = 1.0f / (float)t.P0;
     return true;
 }
 
