@@ -126,12 +126,21 @@ struct mg_ctx {
         int part_off = 0, parts = 0;
         Shape osh;
         int ascale = 0;
+        int lt = 0;          // first level of the fused coarse end (nl - 1: none)
+        bool su = false;     // last sweep + update fused (shape fsh)
+        Shape fsh{4, 16, 256, 1, 4};
+        // postponed updates: ring of `defer` corrections (0: u updated every step)
+        int defer = 0, pending = 0;
+        bool u_zero = false;
+        size_t off_cd = 0, cstride = 0, off_adef = 0;
     };
     std::vector<Inst> inst;
     int Lmax = 0;
     std::vector<int> bprec;  // batched level map (finest first, last = base)
     struct BLaunch {
-        int what;  // 0 stencil, 1 restriction, 2 base solve, 3 finalize
+        // 0 stencil, 1 restriction, 2 base solve, 3 finalize, 4 LDS-plane stencil, 5 pipelined
+        // restriction, 6 smoothing + restriction, 7 sweep + update, 8 fused coarse end
+        int what;
         int kind, V, pf, pc;
         size_t off_desc, off_items;
         int ndesc, nitems, grid, threads;
@@ -141,6 +150,8 @@ struct mg_ctx {
         double bytes;
     };
     std::vector<BLaunch> bl;
+    size_t bl_update = 0;  // bl[bl_update ..] updates r and u, the launches before it are the V-cycle
+    size_t off_bctr = 0;  // slot counters of the instances' rings
     size_t off_bmeta = 0, bmeta_bytes = 0, off_active = 0, off_scal_all = 0, off_fin = 0;
     size_t bmeta_cap = 0;  // workspace bytes reserved for the descriptor image
     int *host_active = nullptr;
@@ -1006,6 +1017,7 @@ mg_status_t ensure_graph(mg_ctx *h) {
 void build_batched_plan(mg_ctx *h, char *base);
 hipError_t enq_batched_step(mg_ctx *h, hipStream_t st);
 hipError_t enq_multi_step(mg_ctx *h, hipStream_t st);
+hipError_t batched_flush(mg_ctx *h, int i, hipStream_t st);
 mg_status_t autotune_batched(mg_ctx *h, hipStream_t st);
 mg_status_t autotune_multi(mg_ctx *h, hipStream_t st);
 mg_status_t batched_upload(mg_ctx *h);
@@ -2292,6 +2304,12 @@ mg_status_t mg_profile_step(mg_handle h, void *stream, int cap, int *count, cons
         e = after_update(h, st);
         if (e == hipSuccess) e = enq_flush(h, st);
     }
+    if (e == hipSuccess && h->batched)
+        for (int i = 0; i < (int)h->inst.size() && e == hipSuccess; ++i)
+            if (h->inst[i].defer) {
+                ++h->inst[i].pending;
+                e = batched_flush(h, i, st);
+            }
     h->prof = false;
     hipError_t e2 = hipStreamSynchronize(st);
     int i = 0;
@@ -2378,6 +2396,43 @@ RShape batched_rshape(int P, int pf, int copies) {
     return r;
 }
 
+// Fused kernels of a batch: tiles as deep as leaves about `want` work items
+// over the copies of a grid (deeper ones read fewer halo planes).
+Shape batched_su_shape(int P, int prec, int copies) {
+    for (int ty = 4; ty >= 1; --ty)
+        for (int zc : {64, 32, 16, 8, 4, 2, 1}) {
+            const Shape s{4, std::min(zc, P - 1), 256, 1, ty};
+            if (!sweep_update_ok(P, prec, s)) continue;
+            if (zc == 1 || (long)copies * sweep_update_blocks(P, s) >= 1024) return s;
+        }
+    return Shape{4, 1, 256, 1, 1};
+}
+
+RShape batched_srshape(int P, int prec, int copies) {
+    const int Nc = P / 2 - 1;
+    for (int tyc = std::min(8, Nc); tyc >= 1; --tyc)
+        for (int zcc : {32, 16, 8, 4, 2, 1}) {
+            const RShape r{8, tyc, std::min(zcc, Nc), 3};
+            if (!smooth_restrict_ok(P, prec, r)) continue;
+            const long items = (long)copies * ((Nc + tyc - 1) / tyc) * ((Nc + r.zcc - 1) / r.zcc);
+            if (zcc == 1 || items >= 600) return r;
+        }
+    return RShape{8, 1, 1, 3};
+}
+
+// The fused coarse end of instance i from its level l, without pointers.
+TailArgs batched_tail_args(const mg_ctx *h, int i, int l) {
+    const auto &I = h->inst[i];
+    TailArgs t;
+    t.P0 = I.lv[l].P;
+    t.nlev = I.nl - 1 - l;
+    for (int j = 0; j <= t.nlev && j <= kTailLevels; ++j) t.prec[j] = I.lv[l + j].prec;
+    t.nu1 = h->opt.nu1;
+    t.nu2 = t.nu2_first = h->opt.nu2;
+    t.omega = h->opt.omega;
+    return t;
+}
+
 // Work items of one instance's stencil launch with shape s.
 int batched_stencil_blocks(int P, const Shape &s) {
     if (s.ty > 0) return ((P - 1 + s.ty - 1) / s.ty) * ((P - 1 + s.zc - 1) / s.zc);
@@ -2396,6 +2451,7 @@ void build_batched_plan(mg_ctx *h, char *base) {
     std::vector<BDesc> descs;
     std::vector<BItem> items;
     std::vector<BFin> fins;
+    std::vector<unsigned char> recs;  // fused coarse ends
     h->bl.clear();
     std::vector<std::vector<int>> cur(ni, std::vector<int>(h->Lmax, 0));
     // addresses are formed as integers so that sizing with base == nullptr is defined
@@ -2427,7 +2483,8 @@ void build_batched_plan(mg_ctx *h, char *base) {
         };
         auto key_of = [](const Pend &p) {
             if (p.what == 4) return Key{p.what, p.V, p.pc, p.d.P, p.d.ty, false};
-            if (p.what == 5) return Key{p.what, p.V, p.pc, p.d.P, p.d.tyc, p.xsh};
+            if (p.what == 5 || p.what == 6) return Key{p.what, p.V, p.pc, p.d.P, p.d.tyc, p.xsh};
+            if (p.what == 7) return Key{p.what, p.V, p.pc, p.d.P, p.d.ty, p.xsh};
             return Key{p.what, p.V, p.pc, 0, 0, false};
         };
         std::vector<Key> keys;
@@ -2435,7 +2492,7 @@ void build_batched_plan(mg_ctx *h, char *base) {
             if (std::find(keys.begin(), keys.end(), key_of(p)) == keys.end()) keys.push_back(key_of(p));
         for (auto &k : keys) {
             mg_ctx::BLaunch L{};
-            L.what = k.what, L.kind = k.what == 5 ? (k.xsh ? 1 : 0) : kind, L.V = k.V, L.pf = pf, L.pc = k.pc;
+            L.what = k.what, L.kind = k.what >= 5 ? (k.xsh ? 1 : 0) : kind, L.V = k.V, L.pf = pf, L.pc = k.pc;
             L.off_desc = descs.size(), L.off_items = items.size();
             L.name = name, L.level = level;
             int maxthreads = 0;
@@ -2498,13 +2555,35 @@ void build_batched_plan(mg_ctx *h, char *base) {
         p.d = x;
         return p;
     };
+    // fused first smoothing + restriction of a level (xsh: from the scaled residual)
+    auto sr_ok = [&](int i, int d) {
+        return h->opt.nu1 == 2 && smooth_restrict_ok(h->inst[i].lv[d].P, h->bprec[d], h->inst[i].lv[d].fsrsh);
+    };
     std::vector<Pend> pend;
     for (int d = 0; d + 1 < h->Lmax; ++d) {
         const int pf = h->bprec[d];
         const double s = (double)prec_bytes(pf);
+        const bool scaled = d == 0 && !alias;
+        for (int i = 0; i < ni; ++i) {
+            if (d >= h->inst[i].lt || !sr_ok(i, d)) continue;
+            const LevelPlan &L = h->inst[i].lv[d];
+            const RShape &r = L.fsrsh;
+            BDesc x{};
+            x.b = (d == 0) ? (const void *)Rp(i) : B(i, d);
+            x.bout = B(i, d), x.c2 = C(i, d, 0), x.cout = B(i, d + 1), x.scal = Sp(i), x.inst = i;
+            x.P = L.P, x.tyc = r.tyc, x.zcc = r.zcc, x.ytiles = (L.P / 2 - 1 + r.tyc - 1) / r.tyc;
+            Pend p{};
+            p.d = x, p.what = 6, p.xsh = scaled, p.pc = bprec_of(h, i, d + 1);
+            p.nblk = x.ytiles * ((L.P / 2 - 1 + r.zcc - 1) / r.zcc);
+            p.threads = (2 * r.tyc + 5) * (L.P / (pf == P_F64 ? 4 : 8));
+            p.lds = smooth_restrict_lds_bytes(L.P, r.tyc, pf, false);
+            pend.push_back(p);
+            cur[i][d] = 0;
+        }
+        flush(0, pf, "smooth_restrict", d, pend, scaled ? 8 + 2 * s : 2 * s);
         // first pre-smoothing (two sweeps fused)
         for (int i = 0; i < ni; ++i) {
-            if (d > h->inst[i].nl - 2) continue;
+            if (d >= h->inst[i].lt || sr_ok(i, d)) continue;
             const LevelPlan &L = h->inst[i].lv[d];
             BDesc x{};
             x.b = (d == 0) ? (const void *)Rp(i) : B(i, d);
@@ -2515,12 +2594,11 @@ void build_batched_plan(mg_ctx *h, char *base) {
             pend.push_back(stencil_pend(x, L.shs[SH_SMOOTH], L.P, pf, P_F64));
             cur[i][d] = 0;
         }
-        const bool scaled = d == 0 && !alias;
         flush(scaled ? BK_SMOOTH2_SCALED : BK_SMOOTH2, pf, scaled ? "smooth2_scaled" : "smooth2", d, pend,
               scaled ? 8 + 2 * s : 2 * s);
         for (int k = 2; k < h->opt.nu1; ++k) {
             for (int i = 0; i < ni; ++i) {
-                if (d > h->inst[i].nl - 2) continue;
+                if (d >= h->inst[i].lt || sr_ok(i, d)) continue;
                 const LevelPlan &L = h->inst[i].lv[d];
                 BDesc x{};
                 x.b = rhs(i, d), x.cin = C(i, d, cur[i][d]), x.cout = C(i, d, cur[i][d] ^ 1), x.inst = i;
@@ -2530,7 +2608,7 @@ void build_batched_plan(mg_ctx *h, char *base) {
             flush(BK_SWEEP, pf, "sweep", d, pend, 3 * s);
         }
         for (int i = 0; i < ni; ++i) {
-            if (d > h->inst[i].nl - 2) continue;
+            if (d >= h->inst[i].lt || sr_ok(i, d)) continue;
             const LevelPlan &L = h->inst[i].lv[d];
             BDesc x{};
             x.b = rhs(i, d), x.cin = C(i, d, cur[i][d]), x.cout = B(i, d + 1), x.inst = i;
@@ -2538,24 +2616,49 @@ void build_batched_plan(mg_ctx *h, char *base) {
         }
         flush(0, pf, "resid_restrict", d, pend, 2 * s);
     }
-    for (int i = 0; i < ni; ++i) {
-        const int lb = h->inst[i].nl - 1;
-        BDesc x{};
-        x.b = B(i, lb), x.cout = C(i, lb, 0), x.inst = i;
-        cur[i][lb] = 0;
-        descs.push_back(x);
-    }
+    // base levels, or the fused coarse ends (grouped by accumulator format)
     {
         mg_ctx::BLaunch L{};
-        L.what = 2, L.pf = h->bprec[h->Lmax - 1], L.off_desc = descs.size() - ni, L.ndesc = ni, L.name = "coarse_solve";
+        L.what = 2, L.pf = h->bprec[h->Lmax - 1], L.off_desc = descs.size(), L.name = "coarse_solve";
         L.level = h->Lmax - 1;
-        h->bl.push_back(L);
+        for (int i = 0; i < ni; ++i) {
+            const int lb = h->inst[i].nl - 1;
+            if (h->inst[i].lt < lb) continue;
+            BDesc x{};
+            x.b = B(i, lb), x.cout = C(i, lb, 0), x.inst = i;
+            cur[i][lb] = 0;
+            descs.push_back(x);
+            ++L.ndesc;
+        }
+        if (L.ndesc) h->bl.push_back(L);
+    }
+    for (int f64 = 0; f64 < 2; ++f64) {
+        mg_ctx::BLaunch L{};
+        L.what = 8, L.kind = f64, L.off_desc = recs.size(), L.name = "coarse_tail", L.level = h->Lmax - 1;
+        for (int i = 0; i < ni; ++i) {
+            const int lt = h->inst[i].lt;
+            if (lt >= h->inst[i].nl - 1 || (h->inst[i].lv[lt].prec == P_F64) != (f64 == 1)) continue;
+            TailArgs t = batched_tail_args(h, i, lt);
+            t.b0 = B(i, lt);
+            for (int l = lt; l < h->inst[i].nl; ++l) {
+                t.wb[l - lt] = B(i, l), t.wc[l - lt] = C(i, l, 0);
+                cur[i][l] = 0;
+            }
+            int threads = 0;
+            size_t lds = 0;
+            recs.resize(recs.size() + tail_record_bytes());
+            (void)tail_record(t, i, recs.data() + recs.size() - tail_record_bytes(), &threads, &lds);
+            L.threads = std::max(L.threads, threads);
+            L.lds = std::max(L.lds, lds);
+            ++L.ndesc;
+        }
+        if (L.ndesc) h->bl.push_back(L);
     }
     for (int d = h->Lmax - 2; d >= 0; --d) {
         const int pf = h->bprec[d];
         const double s = (double)prec_bytes(pf);
         for (int i = 0; i < ni; ++i) {
-            if (d > h->inst[i].nl - 2) continue;
+            if (d >= h->inst[i].lt) continue;
             const LevelPlan &L = h->inst[i].lv[d];
             BDesc x{};
             x.b = rhs(i, d), x.cin = C(i, d, cur[i][d]), x.ec = C(i, d + 1, cur[i][d + 1]);
@@ -2566,7 +2669,8 @@ void build_batched_plan(mg_ctx *h, char *base) {
         flush(BK_PROLONG, pf, "prolong_sweep", d, pend, 3 * s);
         for (int k = 1; k < h->opt.nu2; ++k) {
             for (int i = 0; i < ni; ++i) {
-                if (d > h->inst[i].nl - 2) continue;
+                if (d >= h->inst[i].lt) continue;
+                if (d == 0 && h->inst[i].su && k == h->opt.nu2 - 1) continue;  // fused with the update
                 const LevelPlan &L = h->inst[i].lv[d];
                 BDesc x{};
                 x.b = rhs(i, d), x.cin = C(i, d, cur[i][d]), x.cout = C(i, d, cur[i][d] ^ 1), x.inst = i;
@@ -2576,6 +2680,7 @@ void build_batched_plan(mg_ctx *h, char *base) {
             flush(BK_SWEEP, pf, "sweep", d, pend, 3 * s);
         }
     }
+    h->bl_update = h->bl.size();
     double *part_base = reinterpret_cast<double *>(at(h->off_part));
     for (int i = 0; i < ni; ++i) {
         const LevelPlan &L = h->inst[i].lv[0];
@@ -2583,10 +2688,38 @@ void build_batched_plan(mg_ctx *h, char *base) {
         BDesc x{};
         x.cin = C(i, 0, cur[i][0]), x.R = Rp(i), x.U = Up(i), x.scal = Sp(i), x.h2 = hh * hh;
         x.part_off = h->inst[i].part_off, x.inst = i;
-        pend.push_back(stencil_pend(x, h->inst[i].osh, L.P, h->bprec[0], P_F64));
-        fins.push_back(
-            BFin{part_base + 2 * (size_t)h->inst[i].part_off, batched_stencil_blocks(L.P, h->inst[i].osh), Sp(i),
-                 h->inst[i].ascale});
+        const auto &I = h->inst[i];
+        BFin f{part_base + 2 * (size_t)I.part_off, batched_stencil_blocks(L.P, I.osh), Sp(i), I.ascale, nullptr, 1};
+        if (I.su) {
+            x.b = B(i, 0);
+            x.P = L.P, x.ty = I.fsh.ty, x.zc = I.fsh.zc, x.ytiles = (L.P - 1 + I.fsh.ty - 1) / I.fsh.ty;
+            if (I.defer) {
+                x.cd = at(I.off_cd), x.cstride = I.cstride;
+                x.adef = reinterpret_cast<double *>(at(I.off_adef));
+                f.ctr = reinterpret_cast<int *>(at(h->off_bctr)) + i;
+                f.slots = I.defer;
+                x.ctr = f.ctr;
+            }
+            Pend p{};
+            p.d = x, p.what = 7, p.xsh = I.defer > 0, p.pc = P_F64, p.V = 4;
+            p.nblk = f.count = sweep_update_blocks(L.P, I.fsh);
+            p.threads = (I.fsh.ty + 4) * (L.P / 4);
+            p.lds = sweep_update_lds_bytes(L.P, I.fsh.ty, prec_bytes(h->bprec[0]));
+            pend.push_back(p);
+        } else {
+            pend.push_back(stencil_pend(x, I.osh, L.P, h->bprec[0], P_F64));
+        }
+        fins.push_back(f);
+    }
+    {
+        // the fused updates in their own launches (after the separate ones)
+        std::vector<Pend> fused;
+        for (auto it = pend.begin(); it != pend.end();)
+            if (it->what == 7) fused.push_back(*it), it = pend.erase(it);
+            else ++it;
+        const double s = (double)prec_bytes(h->bprec[0]);
+        const bool d = !fused.empty() && fused[0].xsh;
+        flush(BK_OUTER, h->bprec[0], d ? "sweep_update_defer" : "sweep_update", 0, fused, d ? 16 + 3 * s : 32 + 2 * s);
     }
     flush(BK_OUTER, h->bprec[0], "ir_update", 0, pend, 32 + (double)prec_bytes(h->bprec[0]));
     {
@@ -2594,18 +2727,24 @@ void build_batched_plan(mg_ctx *h, char *base) {
         L.what = 3, L.name = "norm_finalize", L.level = 0;
         h->bl.push_back(L);
     }
-    // image: descriptors, then items, then finalize records
+    // image: descriptors, then items, finalize records, records of the coarse ends
     const size_t nd = descs.size() * sizeof(BDesc), nit = items.size() * sizeof(BItem), nf = fins.size() * sizeof(BFin);
     const size_t off_items = align_up(nd, 256), off_fin = off_items + align_up(nit, 256);
-    h->bmeta_bytes = off_fin + align_up(nf, 256);
+    const size_t off_rec = off_fin + align_up(nf, 256);
+    h->bmeta_bytes = off_rec + align_up(recs.size(), 256);
     if (base) {
         std::vector<unsigned char> img(h->bmeta_bytes, 0);
         std::memcpy(img.data(), descs.data(), nd);
         std::memcpy(img.data() + off_items, items.data(), nit);
         std::memcpy(img.data() + off_fin, fins.data(), nf);
+        if (!recs.empty()) std::memcpy(img.data() + off_rec, recs.data(), recs.size());
         const BDesc *dd = reinterpret_cast<const BDesc *>(at(h->off_bmeta));
         const BItem *ii = reinterpret_cast<const BItem *>(at(h->off_bmeta + off_items));
         for (auto &L : h->bl) {
+            if (L.what == 8) {
+                L.off_desc = reinterpret_cast<size_t>(at(h->off_bmeta + off_rec + L.off_desc));
+                continue;
+            }
             L.off_desc = reinterpret_cast<size_t>(dd + L.off_desc);
             L.off_items = reinterpret_cast<size_t>(ii + L.off_items);
         }
@@ -2615,10 +2754,30 @@ void build_batched_plan(mg_ctx *h, char *base) {
     }
 }
 
-hipError_t enq_batched_step(mg_ctx *h, hipStream_t st) {
+// Add instance i's postponed corrections to its u (nothing pending: a u that
+// is zero and not yet stored is stored).
+hipError_t batched_flush(mg_ctx *h, int i, hipStream_t st) {
+    auto &I = h->inst[i];
+    const LevelPlan &L = I.lv[0];
+    const bool zero = I.u_zero;
+    const int count = I.pending;
+    I.u_zero = false;
+    I.pending = 0;
+    double *U = reinterpret_cast<double *>(h->ws + I.off_U);
+    if (count == 0) return zero ? launch_fill_zero(U, align_up(L.elems * sizeof(double), 16), st) : hipSuccess;
+    const double hh = 1.0 / (double)(L.n + 1);
+    RUN(h, st, "defer_flush", 0, (double)points(3, L.n) * ((zero ? 8 : 16) + count * sb(L.prec)),
+        launch_defer_flush(L.prec, h->ws + I.off_cd, I.cstride, reinterpret_cast<double *>(h->ws + I.off_adef), count,
+                           hh * hh, U, L.elems, reinterpret_cast<int *>(h->ws + h->off_bctr) + i, st, zero));
+    return hipSuccess;
+}
+
+// The launches [first, last) of a batched step.
+hipError_t enq_batched(mg_ctx *h, hipStream_t st, size_t first, size_t last) {
     const int *act = reinterpret_cast<const int *>(h->ws + h->off_active);
     double *part_base = reinterpret_cast<double *>(h->ws + h->off_part);
-    for (auto &L : h->bl) {
+    for (size_t j = first; j < last; ++j) {
+        const auto &L = h->bl[j];
         const BDesc *d = reinterpret_cast<const BDesc *>(L.off_desc);
         const BItem *it = reinterpret_cast<const BItem *>(L.off_items);
         if (L.what == 0) {
@@ -2638,15 +2797,28 @@ hipError_t enq_batched_step(mg_ctx *h, hipStream_t st) {
                 launch_batched_restrict(L.V, L.pf, L.pc, d, it, L.nitems, act, L.grid, L.threads, L.lds, st));
         } else if (L.what == 2) {
             RUN(h, st, L.name, L.level, 0.0, launch_batched_coarse(L.pf, d, L.ndesc, act, st));
+        } else if (L.what == 6) {
+            RUN(h, st, L.name, L.level, L.bytes,
+                launch_batched_smooth_restrict(L.pf, L.pc, L.kind == 1, d, it, L.nitems, act, h->opt.omega, L.grid,
+                                               L.threads, L.lds, st));
+        } else if (L.what == 7) {
+            RUN(h, st, L.name, L.level, L.bytes,
+                launch_batched_sweep_update(L.pf, L.kind == 1, d, it, L.nitems, act, h->opt.omega, part_base, L.grid,
+                                            L.threads, L.lds, st));
+        } else if (L.what == 8) {
+            RUN(h, st, L.name, L.level, 0.0,
+                launch_batched_tail(L.kind == 1, reinterpret_cast<const void *>(L.off_desc), L.ndesc, act, L.threads,
+                                    L.lds, st));
         } else {
             RUN(h, st, L.name, 0, 0.0,
                 launch_batched_finalize(reinterpret_cast<const BFin *>(h->ws + h->off_fin), (int)h->inst.size(), act,
-                                        st));
+                                        h->host_scal_all, st));
         }
     }
-    return hipMemcpyAsync(h->host_scal_all, h->ws + h->off_scal_all, 4 * sizeof(double) * h->inst.size(),
-                          hipMemcpyDeviceToHost, st);
+    return hipSuccess;
 }
+
+hipError_t enq_batched_step(mg_ctx *h, hipStream_t st) { return enq_batched(h, st, 0, h->bl.size()); }
 
 // ---- batched autotuner ---------------------------------------------------------
 // Launch shapes are chosen per class of levels (pitch and format): every level
@@ -2832,6 +3004,9 @@ mg_status_t mg_setup_batched(mg_handle *out, int dim, int ninst, const int *n, c
     h->Lmax = Lmax;
     h->bprec = prec;
     h->inst.resize(ninst);
+    // (larger tiles need more LDS than a launch gets unasked)
+    const bool tails = tail_prepare() == hipSuccess, sus = sweep_update_prepare() == hipSuccess;
+    (void)smooth_restrict_prepare();
     size_t off = 0;
     int parts = 0;
     for (int i = 0; i < ninst; ++i) {
@@ -2855,6 +3030,7 @@ mg_status_t mg_setup_batched(mg_handle *out, int dim, int ninst, const int *n, c
             if (nn > 1) {
                 L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = batched_shape(L.P, L.prec, copies);
                 L.rsh = batched_rshape(L.P, L.prec, copies);
+                L.fsrsh = batched_srshape(L.P, L.prec, copies);
             }
             nn = (nn - 1) / 2;
         }
@@ -2869,8 +3045,34 @@ mg_status_t mg_setup_batched(mg_handle *out, int dim, int ninst, const int *n, c
         I.osh = batched_shape(I.lv[0].P, P_F64, copies);  // V = 4: FP64 rows
         I.part_off = parts;
         I.parts = std::max(stencil_blocks(3, I.lv[0].P, I.osh), flat_blocks(points(3, n[i])));
+        // the fused coarse end, from the second level on
+        I.lt = m - 1;
+        for (int l = 1; l < m - 1 && I.lt == m - 1 && tails; ++l)
+            if (tail_ok(batched_tail_args(h, i, l))) I.lt = l;
+        // the last sweep fused with the update, where it reads a stored right-hand side
+        I.fsh = batched_su_shape(I.lv[0].P, prec[0], copies);
+        I.su = sus && m >= 2 && !(I.lv[0].prec == P_F64 && !o.residual_scaling) && o.nu2 >= 2 &&
+               sweep_update_ok(I.lv[0].P, I.lv[0].prec, I.fsh);
+        if (I.su) I.parts = std::max(I.parts, sweep_update_blocks(I.lv[0].P, I.fsh));
         parts += I.parts;
     }
+    // Postponed updates of u for 2-byte formats: each step stores its correction
+    // (2 bytes per point) in a ring of eight and a pass per eight steps adds
+    // them, 6 instead of 16 bytes per point and step; u is bit for bit the same.
+    // The ring adds 16 bytes per point to the workspace's 16 and the levels', so
+    // very large batches go without.
+    constexpr int kRing = 8;
+    if (off <= (size_t)64 << 30) {
+        for (auto &I : h->inst) {
+            const LevelPlan &L = I.lv[0];
+            if (!I.su || prec_bytes(L.prec) != 2) continue;
+            I.defer = kRing;
+            I.cstride = align_up(L.elems * 2, 256) / 2;
+            I.off_cd = off, off += kRing * I.cstride * 2;
+            I.off_adef = off, off += 256;
+        }
+    }
+    h->off_bctr = off, off += align_up((size_t)ninst * sizeof(int), 256);
     h->max_parts = parts;
     h->off_part = off, off += align_up((size_t)parts * 2 * sizeof(double), 256);
     h->off_scal_all = off, off += align_up((size_t)ninst * 4 * sizeof(double), 256);
@@ -2922,6 +3124,10 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
     // r = b - A u of instance i into R (and u copied out to uout) with its norms;
     // with use_u == false, r = b
     auto resid = [&](int i, bool use_u, double *uout) -> hipError_t {
+        if (use_u) {
+            const hipError_t e = batched_flush(h, i, st);
+            if (e != hipSuccess) return e;
+        }
         const auto &I = h->inst[i];
         const LevelPlan &L = I.lv[0];
         const double hh = 1.0 / (double)(L.n + 1);
@@ -2932,8 +3138,11 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
         return e;
     };
     // ||b||_2 of every instance, and the initial residual
+    HIPCHK(launch_fill_zero(h->ws + h->off_bctr, align_up((size_t)ni * sizeof(int), 16), st));
     for (int i = 0; i < ni; ++i) {
-        const auto &I = h->inst[i];
+        auto &I = h->inst[i];
+        I.pending = 0;
+        I.u_zero = false;
         if (h->opt.use_initial_guess) {
             HIPCHK(launch_resid_flat(3, I.n, I.lv[0].P, b[i], nullptr, nullptr, nullptr, 1.0,
                                      part_base + 2 * (size_t)I.part_off, st));
@@ -2941,7 +3150,9 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
                                    I.ascale, st));
         } else {
             HIPCHK(resid(i, false, nullptr));
-            HIPCHK(launch_fill_zero(h->ws + I.off_U, align_up(I.lv[0].elems * sizeof(double), 16), st));
+            // (with postponed updates the first pass over u starts from zero)
+            if (I.defer) I.u_zero = true;
+            else HIPCHK(launch_fill_zero(h->ws + I.off_U, align_up(I.lv[0].elems * sizeof(double), 16), st));
         }
     }
     if ((s = readback()) != MG_OK) return s;
@@ -2963,20 +3174,36 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
     }
     if (any_guess && (s = readback()) != MG_OK) return s;
     const bool graph = h->opt.use_graph && !h->prof;
-    if (graph && !h->gexec) {
+    if (graph && !(h->gexec && h->gexec2)) {
+        // the V-cycles and the update as two graphs (see ir_solve)
+        drop_graph(h);
         if (!h->cap_stream) HIPCHK(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-        HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-        hipError_t e = enq_batched_step(h, h->cap_stream);
-        hipGraph_t g = nullptr;
-        hipError_t e2 = hipStreamEndCapture(h->cap_stream, &g);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (g) (void)hipGraphDestroy(g);
-            return fail(MG_ERR_HIP, "capture of the batched step failed: %s",
-                        hipGetErrorString(e != hipSuccess ? e : e2));
+        for (int part = 0; part < 2; ++part) {
+            HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
+            hipError_t e = part == 0 ? enq_batched(h, h->cap_stream, 0, h->bl_update)
+                                     : enq_batched(h, h->cap_stream, h->bl_update, h->bl.size());
+            hipGraph_t g = nullptr;
+            hipError_t e2 = hipStreamEndCapture(h->cap_stream, &g);
+            if (e != hipSuccess || e2 != hipSuccess) {
+                if (g) (void)hipGraphDestroy(g);
+                return fail(MG_ERR_HIP, "capture of the batched step failed: %s",
+                            hipGetErrorString(e != hipSuccess ? e : e2));
+            }
+            (part == 0 ? h->graph : h->graph2) = g;
+            HIPCHK(hipGraphInstantiate(part == 0 ? &h->gexec : &h->gexec2, g, nullptr, nullptr, 0));
         }
-        h->graph = g;
-        HIPCHK(hipGraphInstantiate(&h->gexec, h->graph, nullptr, nullptr, 0));
     }
+    if (!h->ev_norm) HIPCHK(hipEventCreateWithFlags(&h->ev_norm, hipEventDisableTiming));
+    auto launch = [&](bool cycle) -> hipError_t {
+        if (graph) return hipGraphLaunch(cycle ? h->gexec : h->gexec2, st);
+        return cycle ? enq_batched(h, st, 0, h->bl_update) : enq_batched(h, st, h->bl_update, h->bl.size());
+    };
+    // V-cycles of the next step already on the stream: they read the residuals
+    // as they are and write only level vectors, so they are good for every
+    // instance that goes on, and do nothing to one that stops
+    bool cycle_queued = false;
+    std::vector<double> prev(ni, -1.0);
+    bool first_step = true;
     for (;;) {
         // classify the stepping instances on their latest residual norms
         int nact = 0, ncheck = 0;
@@ -3013,20 +3240,44 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
                     st_i[i] = std::isfinite(rn) ? MG_ERR_NOT_CONVERGED : MG_ERR_NONFINITE;
                 } else {
                     state[i] = ACTIVE;  // continue from the true residual
+                    prev[i] = -1.0;
+                    cycle_queued = false;  // ... which a queued V-cycle did not see
                     ++nact;
                 }
             }
         }
         if (nact == 0) break;
-        for (int i = 0; i < ni; ++i) h->host_active[i] = state[i] == ACTIVE;
-        HIPCHK(hipMemcpyAsync(act_dev, h->host_active, sizeof(int) * ni, hipMemcpyHostToDevice, st));
-        if (graph) {
-            HIPCHK(hipGraphLaunch(h->gexec, st));
-        } else {
-            hipError_t e = enq_batched_step(h, st);
-            if (e != hipSuccess) return fail(MG_ERR_HIP, "batched step failed: %s", hipGetErrorString(e));
+        bool changed = first_step;
+        for (int i = 0; i < ni; ++i) {
+            const int on = state[i] == ACTIVE;
+            changed = changed || h->host_active[i] != on;
+            h->host_active[i] = on;
         }
-        HIPCHK(hipStreamSynchronize(st));
+        first_step = false;
+        if (changed) HIPCHK(hipMemcpyAsync(act_dev, h->host_active, sizeof(int) * ni, hipMemcpyHostToDevice, st));
+        // whether to queue the next V-cycles before this step's norms are read:
+        // not if the last contraction factors predict that every instance
+        // stops (looked up before the update, whose kernel overwrites the norms)
+        bool more = false;
+        for (int i = 0; i < ni; ++i) {
+            if (state[i] != ACTIVE) continue;
+            const double rn = hs[4 * i + 2], rho = prev[i] > 0.0 ? std::min(1.0, rn / prev[i]) : 0.5;
+            more = more || (k[i] + 1 < h->opt.max_iter && rn * rho > 8.0 * h->opt.rtol * nb[i]);
+            prev[i] = rn;
+        }
+        hipError_t e = cycle_queued ? hipSuccess : launch(true);
+        if (e == hipSuccess) e = launch(false);
+        if (e == hipSuccess) e = hipEventRecord(h->ev_norm, st);
+        for (int i = 0; i < ni && e == hipSuccess; ++i)
+            if (state[i] == ACTIVE && h->inst[i].defer && ++h->inst[i].pending >= h->inst[i].defer)
+                e = batched_flush(h, i, st);
+        cycle_queued = false;
+        if (e == hipSuccess && more) {
+            e = launch(true);
+            cycle_queued = e == hipSuccess;
+        }
+        if (e != hipSuccess) return fail(MG_ERR_HIP, "batched step failed: %s", hipGetErrorString(e));
+        HIPCHK(hipEventSynchronize(h->ev_norm));
         for (int i = 0; i < ni; ++i)
             if (state[i] == ACTIVE) ++k[i];
     }

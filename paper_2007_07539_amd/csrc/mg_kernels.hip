@@ -2093,24 +2093,28 @@ __global__ void k_batched_coarse(const BDesc *__restrict__ descs, int n, const i
 }
 
 // One block per instance: reduce its partials into its scalars.
-__global__ __launch_bounds__(256) void k_batched_finalize(const BFin *__restrict__ fin,
-                                                          const int *__restrict__ active) {
-    __shared__ double red[8];
+__global__ __launch_bounds__(1024) void k_batched_finalize(const BFin *__restrict__ fin,
+                                                           const int *__restrict__ active, double *host) {
+    __shared__ double red[32];
     if (!active[blockIdx.x]) return;
     const BFin f = fin[blockIdx.x];
     double s = 0.0, m = 0.0;
     for (int i = threadIdx.x; i < f.count; i += blockDim.x) {
-        s += f.part[2 * i];
-        m = nanmax(m, f.part[2 * i + 1]);
+        const double2 v = reinterpret_cast<const double2 *>(f.part)[i];
+        s += v.x;
+        m = nanmax(m, v.y);
     }
     block_reduce(s, m, red);
     if (threadIdx.x == 0) {
         double a = f.ascale ? ldexp(m, f.ascale - 1) : 1.0;
         if (!(a > 0.0) || a > 1.7e308) a = 1.0;
-        f.scal[0] = a;
-        f.scal[1] = 1.0 / a;
-        f.scal[2] = sqrt(s);
-        f.scal[3] = m;
+        const double v[4] = {a, 1.0 / a, sqrt(s), m};
+        for (int j = 0; j < 4; ++j) {
+            f.scal[j] = v[j];
+            if (host) host[4 * blockIdx.x + j] = v[j];
+        }
+        if (host) __threadfence_system();
+        if (f.ctr) *f.ctr = (*f.ctr + 1) % f.slots;
     }
 }
 
@@ -2369,8 +2373,8 @@ hipError_t launch_batched_restrict2(int V, int pf, int pc, bool xsh, const BDesc
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_batched_finalize(const BFin *fin, int ninst, const int *active, hipStream_t st) {
-    hipLaunchKernelGGL(k_batched_finalize, dim3(ninst), dim3(256), 0, st, fin, active);
+hipError_t launch_batched_finalize(const BFin *fin, int ninst, const int *active, double *host, hipStream_t st) {
+    hipLaunchKernelGGL(k_batched_finalize, dim3(ninst), dim3(1024), 0, st, fin, active, host);
     return hipGetLastError();
 }
 

@@ -217,6 +217,13 @@ bool tail_ok(const TailArgs &t);  // the levels fit (pointers are not looked at)
 // launch, outside a stream capture.
 hipError_t tail_prepare();
 hipError_t launch_tail(const TailArgs &t, hipStream_t st);
+// Batched instances: one record (tail_record_bytes) per instance in device
+// memory, all of one accumulator format (FP64 or not); tail_record fills one
+// (dst may be null: only sizes) and returns the block size and LDS it needs.
+size_t tail_record_bytes();
+bool tail_record(const TailArgs &t, int inst, void *dst, int *threads, size_t *lds);
+hipError_t launch_batched_tail(bool f64, const void *records, int n, const int *active, int threads, size_t lds,
+                               hipStream_t st);
 
 // Fused stages of a 2-D level by tiles (mg_tile2d.hip; pitch a multiple of 4,
 // at most three sweeps).  Down: nu pre-sweeps from zero on the right-hand side
@@ -261,6 +268,12 @@ struct BDesc {
     int part_off;        // first reduction partial of the instance (update)
     int inst;
     int ty;              // LDS-plane kernels: rows per block (ytiles = its y tiles)
+    void *c2;            // fused smoothing + restriction: output correction (cout is the coarse right-hand side)
+    // postponed updates: ring of corrections, its slot counter and alphas
+    void *cd;
+    const int *ctr;
+    double *adef;
+    size_t cstride;
 };
 struct BItem {
     int d, blk;  // descriptor, tile
@@ -270,6 +283,8 @@ struct BFin {
     int count;
     double *scal;
     int ascale;  // 0: alpha = 1; 1 + j: alpha = 2^j ||r||_inf
+    int *ctr;    // slot counter of postponed updates (null: none), modulo slots
+    int slots;
 };
 enum { BK_SMOOTH2 = 0, BK_SMOOTH2_SCALED = 1, BK_SWEEP = 2, BK_PROLONG = 3, BK_OUTER = 4 };
 
@@ -285,7 +300,15 @@ hipError_t launch_batched_march(int kind, int V, int pf, int pc, const BDesc *d,
                                 hipStream_t st);
 hipError_t launch_batched_restrict2(int V, int pf, int pc, bool xsh, const BDesc *d, const BItem *items, int nitems,
                                     const int *active, int grid, int threads, size_t lds, hipStream_t st);
-hipError_t launch_batched_finalize(const BFin *fin, int ninst, const int *active, hipStream_t st);
+// (host: pinned memory that also receives every active instance's scalars)
+hipError_t launch_batched_finalize(const BFin *fin, int ninst, const int *active, double *host, hipStream_t st);
+// Fused forms (3-D; one pitch and coarse format per launch).
+hipError_t launch_batched_smooth_restrict(int pf, int pc, bool scaled, const BDesc *d, const BItem *items, int nitems,
+                                          const int *active, double omega, int grid, int threads, size_t lds,
+                                          hipStream_t st);
+hipError_t launch_batched_sweep_update(int pf, bool defer, const BDesc *d, const BItem *items, int nitems,
+                                       const int *active, double omega, double *part, int grid, int threads,
+                                       size_t lds, hipStream_t st);
 
 // ---- many right-hand sides, interleaved [z][y][x][k] -------------------------
 // Arguments of one interleaved stage launch (unused members may stay null).

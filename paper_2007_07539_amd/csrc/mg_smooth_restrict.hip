@@ -49,11 +49,11 @@ template <class T> constexpr int sr_bound() { return sizeof(T) == 8 ? 1024 : 768
 // NARROW: c1 and c2 sit in LDS in the storage format T instead of the
 // accumulator format (exact: both are values of T), which halves that part of
 // the LDS so that two workgroups fit a CU; they are widened when read.
+// One tile (blk = y tile + ytiles * z chunk); inv = 1 / alpha (SCALED).
 template <class T, class TC, bool SCALED, bool NARROW>
-__global__ __launch_bounds__(sr_bound<T>()) void k_smooth_restrict(const void *__restrict__ src,
-                                                          const double *__restrict__ scal, T *__restrict__ bout,
-                                                          T *__restrict__ cout, TC *__restrict__ bc, int P, int tyc,
-                                                          int zcc, int ytiles, double omega, int xcd) {
+__device__ __forceinline__ void sr_body(const void *__restrict__ src, double inv, T *__restrict__ bout,
+                                        T *__restrict__ cout, TC *__restrict__ bc, int P, int tyc, int zcc, int ytiles,
+                                        double omega, int blk, unsigned char *smem_raw) {
     constexpr int V = sr_vec<T>(), VC = V / 2;
     constexpr bool XW = V == 4;  // x weights in the coarse threads, from raw residual rows
     typedef acc_t<T> A;
@@ -61,7 +61,6 @@ __global__ __launch_bounds__(sr_bound<T>()) void k_smooth_restrict(const void *_
     typedef LdsRun<LC, V> LR;   // fine rows in LDS, chunk-major
     typedef LdsRun<A, XW ? V : VC> LRC;  // residual rows: raw (XW) or x-weighted
     typedef typename std::conditional<SCALED, double, T>::type S;  // source format
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     const int G = 2 * tyc + 5, RR = 2 * tyc + 1, RW = XW ? P : P / 2;
     const size_t cslot = (size_t)G * P, rslot = (size_t)RR * RW;
     // c1 and c2 sit in LDS widened to the accumulator type, so that neither
@@ -71,11 +70,6 @@ __global__ __launch_bounds__(sr_bound<T>()) void k_smooth_restrict(const void *_
     A *rs = reinterpret_cast<A *>(c2s + 2 * cslot);  // [2][RR][RW]
     const int Pc = P >> 1, TXR = P / V;
     const Grid<3> gc{Pc};
-    int blk = blockIdx.x;
-    if (xcd) {
-        const int nb = gridDim.x;
-        blk = xcd_block(blk, nb);
-    }
     const int ytile = blk % ytiles, zch = blk / ytiles;
     const int Y0 = 1 + ytile * tyc;
     const int Z0 = 1 + zch * zcc, Z1 = min(Z0 + zcc, Pc);
@@ -94,7 +88,6 @@ __global__ __launch_bounds__(sr_bound<T>()) void k_smooth_restrict(const void *_
     auto own_plane = [&](int z) { return z >= zf0 && (z <= zf1 - 1 || (last_z && z == P - 1)); };
     const bool coarse = gi < tyc && Y0 + gi < Pc;
     const int Yc = Y0 + gi;
-    const double inv = SCALED ? scal[1] : 1.0;
     const A k = (A)(omega / 6.0);
     // offsets of the own row (plane 0) and of plane z, the latter uniform
     const size_t roff = (size_t)(long)y * P + x0;
@@ -312,6 +305,37 @@ __global__ __launch_bounds__(sr_bound<T>()) void k_smooth_restrict(const void *_
     if (coarse) coarse_step(zf1, zf1 & 1);
 }
 
+template <class T, class TC, bool SCALED, bool NARROW>
+__global__ __launch_bounds__(sr_bound<T>()) void k_smooth_restrict(const void *__restrict__ src,
+                                                                   const double *__restrict__ scal,
+                                                                   T *__restrict__ bout, T *__restrict__ cout,
+                                                                   TC *__restrict__ bc, int P, int tyc, int zcc,
+                                                                   int ytiles, double omega, int xcd) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int blk = xcd ? xcd_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+    sr_body<T, TC, SCALED, NARROW>(src, SCALED ? scal[1] : 1.0, bout, cout, bc, P, tyc, zcc, ytiles, omega, blk,
+                                   smem_raw);
+}
+
+// Batched instances: the work list's tiles (descriptors of one pitch), each the
+// single grid's tile.
+template <class T, class TC, bool SCALED>
+__global__ __launch_bounds__(sr_bound<T>()) void k_batched_smooth_restrict(const BDesc *__restrict__ descs,
+                                                                           const BItem *__restrict__ items, int nitems,
+                                                                           const int *__restrict__ active,
+                                                                           double omega) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    for (int it = xcd_block((int)blockIdx.x, (int)gridDim.x); it < nitems; it += gridDim.x) {
+        const BItem item = items[it];
+        const BDesc &d = descs[item.d];
+        if (!active[d.inst]) continue;
+        sr_body<T, TC, SCALED, false>(d.b, SCALED ? d.scal[1] : 1.0, static_cast<T *>(d.bout),
+                                      static_cast<T *>(d.c2), static_cast<TC *>(d.cout), d.P, d.tyc, d.zcc, d.ytiles,
+                                      omega, item.blk, smem_raw);
+        __syncthreads();  // the next item reuses the LDS rows
+    }
+}
+
 template <class T, bool SCALED, bool NARROW>
 hipError_t smooth_restrict_t(int pc, int P, const void *src, const double *scal, void *bout, void *cout, void *bc,
                              double omega, const RShape &s, hipStream_t st) {
@@ -353,7 +377,13 @@ hipError_t smooth_restrict_prepare() {
             MG_SR_FN(double, true, false), MG_SR_FN(float, true, false), MG_SR_FN(f16, true, false),
             MG_SR_FN(bf16, true, false), MG_SR_FN(double, false, false), MG_SR_FN(float, false, false),
             MG_SR_FN(f16, false, false), MG_SR_FN(bf16, false, false), MG_SR_FN(f16, true, true),
-            MG_SR_FN(bf16, true, true), MG_SR_FN(f16, false, true), MG_SR_FN(bf16, false, true)
+            MG_SR_FN(bf16, true, true), MG_SR_FN(f16, false, true), MG_SR_FN(bf16, false, true),
+#undef MG_SR_FN
+#define MG_SR_FN(T, S)                                                                                          \
+    (const void *)k_batched_smooth_restrict<T, double, S>, (const void *)k_batched_smooth_restrict<T, float, S>, \
+        (const void *)k_batched_smooth_restrict<T, f16, S>, (const void *)k_batched_smooth_restrict<T, bf16, S>
+            MG_SR_FN(double, true), MG_SR_FN(float, true), MG_SR_FN(f16, true), MG_SR_FN(bf16, true),
+            MG_SR_FN(double, false), MG_SR_FN(float, false), MG_SR_FN(f16, false), MG_SR_FN(bf16, false)
 #undef MG_SR_FN
         };
         for (const void *f : fns) {
@@ -411,6 +441,43 @@ hipError_t launch_smooth_restrict_b(int prec, int pc, int P, const void *b, void
         return nw ? smooth_restrict_t<bf16, false, true>(pc, P, b, nullptr, nullptr, cout, bc, omega, s, st)
                   : smooth_restrict_t<bf16, false, false>(pc, P, b, nullptr, nullptr, cout, bc, omega, s, st);
     }
+    return hipErrorInvalidValue;
+}
+
+namespace {
+template <class T, bool SCALED>
+hipError_t bsr_t(int pc, const BDesc *d, const BItem *items, int nitems, const int *active, double omega, int grid,
+                 int threads, size_t lds, hipStream_t st) {
+#define MG_BSR(TCT)                                                                                               \
+    hipLaunchKernelGGL((k_batched_smooth_restrict<T, TCT, SCALED>), dim3(grid), dim3(threads), lds, st, d, items, \
+                       nitems, active, omega)
+    switch (pc) {
+    case P_F64: MG_BSR(double); break;
+    case P_F32: MG_BSR(float); break;
+    case P_F16: MG_BSR(f16); break;
+    case P_BF16: MG_BSR(bf16); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef MG_BSR
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_batched_smooth_restrict(int pf, int pc, bool scaled, const BDesc *d, const BItem *items, int nitems,
+                                          const int *active, double omega, int grid, int threads, size_t lds,
+                                          hipStream_t st) {
+    if (threads > (pf == P_F64 ? 1024 : 768) || lds > kLdsMax) return hipErrorInvalidValue;
+    if (lds > 65536 && smooth_restrict_prepare() != hipSuccess) return hipErrorInvalidValue;
+#define MG_BSR(T)                                                                                            \
+    return scaled ? bsr_t<T, true>(pc, d, items, nitems, active, omega, grid, threads, lds, st)              \
+                  : bsr_t<T, false>(pc, d, items, nitems, active, omega, grid, threads, lds, st)
+    switch (pf) {
+    case P_F64: MG_BSR(double);
+    case P_F32: MG_BSR(float);
+    case P_F16: MG_BSR(f16);
+    case P_BF16: MG_BSR(bf16);
+    }
+#undef MG_BSR
     return hipErrorInvalidValue;
 }
 

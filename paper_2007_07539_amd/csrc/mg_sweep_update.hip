@@ -42,27 +42,21 @@ namespace {
 // FP64 rows need more registers than a 1024-thread block leaves a thread
 template <class T> constexpr int su_bound() { return sizeof(T) == 8 ? 768 : 1024; }
 
+// One tile (blk = y tile + ytiles * z chunk); cd: this step's ring slot (DEFER);
+// pidx: the tile's norm partial.  Called by every thread of the block.
 template <int V, class T, bool ALIAS, bool DEFER>
-__global__ __launch_bounds__(su_bound<T>()) void k_sweep_update(
-    const T *__restrict__ c, const T *__restrict__ b, const double *R, double *Rout, double *__restrict__ U,
-    T *__restrict__ Cd, const int *__restrict__ ctr, size_t cstride, double *__restrict__ adef,
-    const double *__restrict__ scal, double h2, double omega, double *__restrict__ part, int P, int TY, int zc,
-    int ytiles, int xcd) {
+__device__ __forceinline__ void su_body(const T *__restrict__ c, const T *__restrict__ b, const double *R, double *Rout,
+                                        double *__restrict__ U, T *__restrict__ cd, double a, double inv, double h2,
+                                        double omega, double *__restrict__ part, int P, int TY, int zc, int ytiles,
+                                        int blk, size_t pidx, unsigned char *smem_raw, double *red) {
     typedef acc_t<T> A;
     typedef typename std::conditional<ALIAS, double, T>::type TB;  // what the b queue holds
     typedef LdsRun<T, V> LR;  // LDS rows, chunk-major
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ double red[32];
     const int G = TY + 4;
     const size_t slot = (size_t)G * P;
     T *cs = reinterpret_cast<T *>(smem_raw);  // [2][G][P]: c of the plane being swept
     T *fs = cs + 2 * slot;                    // [2][G][P]: c' of the plane being updated
     const Grid<3> g{P};
-    int blk = blockIdx.x;
-    if (xcd) {
-        const int nb = gridDim.x;
-        blk = xcd_block(blk, nb);
-    }
     const int yt = blk % ytiles, zch = blk / ytiles;
     const int y0 = 1 + yt * TY;
     const int z0 = 1 + zch * zc;
@@ -75,17 +69,9 @@ __global__ __launch_bounds__(su_bound<T>()) void k_sweep_update(
     const bool sweep_row = gi >= 1 && gi <= TY + 2;
     const bool out_row = gi >= 2 && gi <= TY + 1 && y <= P - 1;
     const A k = (A)(omega / 6.0);
-    const double a = scal[0];
-    const double inv = scal[1];  // ALIAS: b = round_T(r * (1 / alpha)), as the first smoothing formed it
+    // (ALIAS: b = round_T(r * inv), inv = 1 / alpha, as the first smoothing formed it)
     const TB *bsrc = ALIAS ? reinterpret_cast<const TB *>(R) : reinterpret_cast<const TB *>(b);
     const double ah2 = a * h2;
-    T *cd = nullptr;  // DEFER: this step's slot
-    if constexpr (DEFER) {
-        const int k = *ctr;
-        cd = Cd + (size_t)k * cstride;
-        if (blockIdx.x == 0 && threadIdx.x == 0) adef[k] = a;
-    }
-
     auto fetch_c = [&](int z, RawRow<T, V> &r) {
         if (!row_in || z <= 0 || z >= P) {
             zero_row(r);
@@ -246,8 +232,55 @@ __global__ __launch_bounds__(su_bound<T>()) void k_sweep_update(
     }
     block_reduce(ss, mx, red);
     if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = ss;
-        part[2 * blockIdx.x + 1] = mx;
+        part[2 * pidx] = ss;
+        part[2 * pidx + 1] = mx;
+    }
+}
+
+template <int V, class T, bool ALIAS, bool DEFER>
+__global__ __launch_bounds__(su_bound<T>()) void k_sweep_update(
+    const T *__restrict__ c, const T *__restrict__ b, const double *R, double *Rout, double *__restrict__ U,
+    T *__restrict__ Cd, const int *__restrict__ ctr, size_t cstride, double *__restrict__ adef,
+    const double *__restrict__ scal, double h2, double omega, double *__restrict__ part, int P, int TY, int zc,
+    int ytiles, int xcd) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double red[32];
+    const int blk = xcd ? xcd_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+    const double a = scal[0];
+    T *cd = nullptr;  // DEFER: this step's slot
+    if constexpr (DEFER) {
+        const int k = *ctr;
+        cd = Cd + (size_t)k * cstride;
+        if (blockIdx.x == 0 && threadIdx.x == 0) adef[k] = a;
+    }
+    su_body<V, T, ALIAS, DEFER>(c, b, R, Rout, U, cd, a, scal[1], h2, omega, part, P, TY, zc, ytiles, blk,
+                                (size_t)blockIdx.x, smem_raw, red);
+}
+
+// Batched instances: the work list's tiles (descriptors of one pitch), each the
+// single grid's tile.  Consecutive items share an XCD, as a grid's tiles do.
+template <class T, bool DEFER>
+__global__ __launch_bounds__(su_bound<T>()) void k_batched_sweep_update(const BDesc *__restrict__ descs,
+                                                                        const BItem *__restrict__ items, int nitems,
+                                                                        const int *__restrict__ active, double omega,
+                                                                        double *__restrict__ part) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double red[32];
+    for (int it = xcd_block((int)blockIdx.x, (int)gridDim.x); it < nitems; it += gridDim.x) {
+        const BItem item = items[it];
+        const BDesc &d = descs[item.d];
+        if (!active[d.inst]) continue;
+        const double a = d.scal[0];
+        T *cd = nullptr;
+        if constexpr (DEFER) {
+            const int k = *d.ctr;
+            cd = static_cast<T *>(d.cd) + (size_t)k * d.cstride;
+            if (item.blk == 0 && threadIdx.x == 0) d.adef[k] = a;
+        }
+        su_body<4, T, false, DEFER>(static_cast<const T *>(d.cin), static_cast<const T *>(d.b), d.R, d.R, d.U, cd, a,
+                                    d.scal[1], d.h2, omega, part, d.P, d.ty, d.zc, d.ytiles, item.blk,
+                                    (size_t)d.part_off + item.blk, smem_raw, red);
+        __syncthreads();  // the next item reuses the LDS slots
     }
 }
 
@@ -286,6 +319,9 @@ hipError_t sweep_update_prepare() {
 #define MG_SU_FN(T)                                                                                       \
     (const void *)k_sweep_update<4, T, false, false>, (const void *)k_sweep_update<4, T, false, true>,       \
         (const void *)k_sweep_update<4, T, true, false>, (const void *)k_sweep_update<4, T, true, true>
+            MG_SU_FN(double), MG_SU_FN(float), MG_SU_FN(f16), MG_SU_FN(bf16),
+#undef MG_SU_FN
+#define MG_SU_FN(T) (const void *)k_batched_sweep_update<T, false>, (const void *)k_batched_sweep_update<T, true>
             MG_SU_FN(double), MG_SU_FN(float), MG_SU_FN(f16), MG_SU_FN(bf16)
 #undef MG_SU_FN
         };
@@ -326,6 +362,29 @@ hipError_t launch_sweep_update(int prec, int P, const SweepUpdateArgs &q, const 
     case P_F16: return sweep_update_mode<f16>(P, q, s, st);
     case P_BF16: return sweep_update_mode<bf16>(P, q, s, st);
     }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_batched_sweep_update(int pf, bool defer, const BDesc *d, const BItem *items, int nitems,
+                                       const int *active, double omega, double *part, int grid, int threads,
+                                       size_t lds, hipStream_t st) {
+    if (threads > (pf == P_F64 ? 768 : 1024) || lds > kSuDynLdsMax) return hipErrorInvalidValue;
+    if (lds > 65536 - 1024 && sweep_update_prepare() != hipSuccess) return hipErrorInvalidValue;
+#define MG_BSU(T)                                                                                                  \
+    if (defer)                                                                                                     \
+        hipLaunchKernelGGL((k_batched_sweep_update<T, true>), dim3(grid), dim3(threads), lds, st, d, items,        \
+                           nitems, active, omega, part);                                                           \
+    else                                                                                                           \
+        hipLaunchKernelGGL((k_batched_sweep_update<T, false>), dim3(grid), dim3(threads), lds, st, d, items,       \
+                           nitems, active, omega, part);                                                           \
+    return hipGetLastError()
+    switch (pf) {
+    case P_F64: MG_BSU(double);
+    case P_F32: MG_BSU(float);
+    case P_F16: MG_BSU(f16);
+    case P_BF16: MG_BSU(bf16);
+    }
+#undef MG_BSU
     return hipErrorInvalidValue;
 }
 

@@ -65,6 +65,7 @@ struct TailKArgs {
     int single;                // first level whose threads hold single points
     int small;                 // first of these that one wave holds
     float inv_p0;              // 1 / P0
+    int inst;                  // batched: the instance
 };
 
 __device__ __forceinline__ void mem_store1(void *m, int o, int p, double v) {
@@ -604,8 +605,7 @@ __device__ __forceinline__ void level_up(const Ctx<A> &x, int l, A *B, const W *
     }
 }
 
-template <int D, int OP, class A>
-__global__ __launch_bounds__(kThreads) void k_tail(const TailKArgs a) {
+template <int D, int OP, class A> __device__ __forceinline__ void tail_body(const TailKArgs &a) {
     constexpr int V = TailSplit<OP>::V, K = TailSplit<OP>::K;
     extern __shared__ __align__(16) unsigned char smem[];
     A *const lds = reinterpret_cast<A *>(smem);
@@ -700,6 +700,18 @@ __global__ __launch_bounds__(kThreads) void k_tail(const TailKArgs a) {
     }
 }
 
+template <int D, int OP, class A> __global__ __launch_bounds__(kThreads) void k_tail(const TailKArgs a) {
+    tail_body<D, OP, A>(a);
+}
+
+// Batched instances: one workgroup each (block sizes and LDS of the largest).
+template <class A>
+__global__ __launch_bounds__(kThreads) void k_batched_tail(const TailKArgs *__restrict__ args,
+                                                           const int *__restrict__ active) {
+    const TailKArgs &a = args[blockIdx.x];  // (scalar loads where used: a copy would sit in scratch memory)
+    if (active[a.inst]) tail_body<3, 0, A>(a);
+}
+
 // Launch plan: LDS offsets and sizes, and whether the levels fit.
 struct Plan {
     TailKArgs k;
@@ -790,9 +802,38 @@ hipError_t tail_prepare() {
                 return e;
             }
         }
+        for (const void *f : {(const void *)k_batched_tail<float>, (const void *)k_batched_tail<double>}) {
+            const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                return e;
+            }
+        }
         return hipSuccess;
     }();
     return done;
+}
+
+size_t tail_record_bytes() { return sizeof(TailKArgs); }
+
+bool tail_record(const TailArgs &t, int inst, void *dst, int *threads, size_t *lds) {
+    Plan q;
+    if (t.D != 3 || t.q1 || !plan_tail(t, q)) return false;
+    q.k.inst = inst;
+    if (dst) *static_cast<TailKArgs *>(dst) = q.k;
+    *threads = q.threads;
+    *lds = q.lds;
+    return true;
+}
+
+hipError_t launch_batched_tail(bool f64, const void *records, int n, const int *active, int threads, size_t lds,
+                               hipStream_t st) {
+    if (n < 1 || threads < 64 || threads > kThreads || lds > kLdsMax) return hipErrorInvalidValue;
+    if (lds > 65536 && tail_prepare() != hipSuccess) return hipErrorInvalidValue;
+    const TailKArgs *r = static_cast<const TailKArgs *>(records);
+    if (f64) hipLaunchKernelGGL((k_batched_tail<double>), dim3(n), dim3(threads), lds, st, r, active);
+    else hipLaunchKernelGGL((k_batched_tail<float>), dim3(n), dim3(threads), lds, st, r, active);
+    return hipGetLastError();
 }
 
 hipError_t launch_tail(const TailArgs &t, hipStream_t st) {

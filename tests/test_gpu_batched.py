@@ -196,3 +196,22 @@ def test_batched_autotuned_bitwise_and_cached(dev, tmp_path, monkeypatch, name):
         u1, r1 = _single(n, tuned.instance_prec(i), bs[i], residual_scaling=scaling)
         assert r1.iterations == rt[i].iterations and torch.equal(ut[i], u1), (i, n)
         assert rt[i].rel_residual <= 1e-10
+
+
+@pytest.mark.parametrize("name", ["f16", "bf16", "h_mg", "f32"])
+@pytest.mark.parametrize("steps", [1, 7, 8, 9, 100])
+def test_batched_postponed_updates_around_the_ring(dev, name, steps):
+    """2-byte formats add their corrections to u eight steps at a time: stopped
+    before, at and after a full ring, u is what single solves return (FP32
+    updates u every step)."""
+    sizes = [31, 7, 63, 31]
+    lmax = W.levels_for(max(sizes))
+    print(f"batched ring {name} steps={steps}", flush=True)
+    s = mgir.BatchedSolver(sizes, W.precision_map(name, lmax), max_iter=steps)
+    bs = [torch.from_numpy(W.uniform_rhs(3, n, seed=20 + i)).to(dev) for i, n in enumerate(sizes)]
+    us, res, _ = s.solve(bs, check=False)
+    for i, n in enumerate(sizes):
+        one = mgir.Solver(3, n, s.instance_prec(i), max_iter=steps)
+        u, r = one.solve(bs[i], check=False)
+        assert res[i].iterations == r.iterations
+        assert torch.equal(us[i], u), i
