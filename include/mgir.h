@@ -238,7 +238,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
  *              same map a single-grid solver gets from level_prec[0..m_i-2]
  *              followed by level_prec[Lmax-1].  NULL means all MG_F64.
  *   opt        NULL for defaults; needs nu1 >= 2.  use_graph captures one
- *              refinement step of the whole batch; autotune times launch
+ *              refinement step of the whole batch as two graphs; autotune times launch
  *              shapes per class of levels (pitch and format) at
  *              mg_bind_workspace, whole batched steps at a time (cached as
  *              for mg_setup under MGIR_TUNE_CACHE).
@@ -270,8 +270,9 @@ mg_status_t mg_instances(mg_handle h, int *ninst);
 /* ---- Many right-hand sides -------------------------------------------------
  * nrhs Poisson problems on one 3-D grid (same operator, different b), stored
  * interleaved: value k of grid point (x, y, z) (0-based) at
- * ((z*n + y)*n + x)*nrhs + k.  One kernel launch per V-cycle stage serves all
- * right-hand sides; each one runs Algorithm 2 on its own (its own alpha_k,
+ * ((z*n + y)*n + x)*nrhs + k.  The workspace holds a grid per right-hand side,
+ * split from the interleaved vectors on the way in and joined on the way out;
+ * one kernel launch per V-cycle stage serves all of them; each one runs Algorithm 2 on its own (its own alpha_k,
  * norms, stop test and confirmation), and column k computes what a
  * single-grid solve of that right-hand side computes.  (The paper solves one
  * right-hand side at a time; the interleaved batch is an extension.)
@@ -280,11 +281,10 @@ mg_status_t mg_instances(mg_handle h, int *ninst);
  *   dim        3.
  *   n          2^m - 1 with 2 <= m <= 9.
  *   nrhs       4, 8, 16, 32 or 64, and at least 8 when any level is stored
- *              in FP32, FP16 or BF16 (a thread handles 8 such columns).
+ *              in FP32, FP16 or BF16.
  *   level_prec m formats, finest first, as for mg_setup.
- *   opt        NULL for defaults; needs nu1 >= 2; autotune times the planes
- *              per thread of each level's stages at mg_bind_workspace, whole
- *              steps at a time (cached under MGIR_TUNE_CACHE).
+ *   opt        NULL for defaults; needs nu1 >= 2; autotune times launch
+ *              shapes per class of levels as for mg_setup_batched.
  * Errors: MG_ERR_ARG, MG_ERR_SHAPE, MG_ERR_PREC.  Workspace as for mg_setup;
  * single-grid calls other than mg_levels / mg_level_n refuse the handle with
  * MG_ERR_STATE. */

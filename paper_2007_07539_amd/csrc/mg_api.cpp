@@ -157,12 +157,10 @@ struct mg_ctx {
     int *host_active = nullptr;
     double *host_scal_all = nullptr;
     std::vector<unsigned char> bmeta_img_tmp;
-    // many right-hand sides (interleaved); nrhs == 0 for other handles
+    size_t off_rfin = 0;  // finalize records of the true residuals
+    // many right-hand sides (nrhs == 0 for other handles): nrhs equal instances
     int nrhs = 0;
-    size_t off_act = 0, off_mask = 0, off_zmask = 0, off_mres = 0;
-    int m_upd_blocks = 0;
-    int *host_mask = nullptr;
-    double *host_scal_m = nullptr;
+    size_t col_stride = 0;  // bytes between the same arrays of two columns
 };
 
 namespace {
@@ -1017,7 +1015,7 @@ mg_status_t ensure_graph(mg_ctx *h) {
 void build_batched_plan(mg_ctx *h, char *base);
 hipError_t enq_batched_step(mg_ctx *h, hipStream_t st);
 hipError_t enq_multi_step(mg_ctx *h, hipStream_t st);
-hipError_t batched_flush(mg_ctx *h, int i, hipStream_t st);
+hipError_t batched_flush(mg_ctx *h, const std::vector<char> &sel, hipStream_t st);
 mg_status_t autotune_batched(mg_ctx *h, hipStream_t st);
 mg_status_t autotune_multi(mg_ctx *h, hipStream_t st);
 mg_status_t batched_upload(mg_ctx *h);
@@ -1757,14 +1755,7 @@ mg_status_t mg_bind_workspace(mg_handle h, void *dev_ptr, size_t bytes, void *st
     HIPCHK(hipMemsetAsync(h->ws, 0, h->ws_need, st));
     HIPCHK(hipStreamSynchronize(st));
     for (int l = 0; l < h->nl; ++l) h->cur[l] = 0;
-    if (h->nrhs) {
-        const int K = h->nrhs;
-        if (!h->host_mask) HIPCHK(hipHostMalloc((void **)&h->host_mask, 2 * sizeof(int) * K, hipHostMallocDefault));
-        if (!h->host_scal_m) HIPCHK(hipHostMalloc((void **)&h->host_scal_m, 4 * sizeof(double) * K, hipHostMallocDefault));
-        if (h->opt.autotune) return autotune_multi(h, st);
-        return MG_OK;
-    }
-    if (h->batched) {
+    if (h->batched || h->nrhs) {
         const int ni = (int)h->inst.size();
         if (!h->host_active) HIPCHK(hipHostMalloc((void **)&h->host_active, sizeof(int) * ni, hipHostMallocDefault));
         if (!h->host_scal_all)
@@ -1787,8 +1778,6 @@ mg_status_t mg_destroy(mg_handle h) {
     if (h->host_scal) (void)hipHostFree(h->host_scal);
     if (h->host_active) (void)hipHostFree(h->host_active);
     if (h->host_scal_all) (void)hipHostFree(h->host_scal_all);
-    if (h->host_mask) (void)hipHostFree(h->host_mask);
-    if (h->host_scal_m) (void)hipHostFree(h->host_scal_m);
     delete h;
     return MG_OK;
 }
@@ -2284,7 +2273,8 @@ mg_status_t mg_profile_step(mg_handle h, void *stream, int cap, int *count, cons
     if (s != MG_OK) return s;
     if (!count || cap < 0) return fail(MG_ERR_ARG, "null argument");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (h->batched) {
+    const bool grouped = h->batched || h->nrhs;
+    if (grouped) {
         // profile a step of every instance from its current state
         const int ni = (int)h->inst.size();
         for (int i = 0; i < ni; ++i) h->host_active[i] = 1;
@@ -2292,24 +2282,17 @@ mg_status_t mg_profile_step(mg_handle h, void *stream, int cap, int *count, cons
     }
     h->prof = true;
     h->recs.clear();
-    if (h->nrhs) {
-        for (int k = 0; k < h->nrhs; ++k) h->host_mask[k] = 1;
-        HIPCHK(hipMemcpyAsync(h->ws + h->off_act, h->host_mask, sizeof(int) * h->nrhs, hipMemcpyHostToDevice, st));
-        HIPCHK(hipStreamSynchronize(st));
-    }
-    hipError_t e = h->batched ? enq_batched_step(h, st) : h->nrhs ? enq_multi_step(h, st) : enq_step(h, st);
-    if (e == hipSuccess && !h->batched && !h->nrhs) {
+    hipError_t e = grouped ? enq_batched_step(h, st) : enq_step(h, st);
+    if (e == hipSuccess && !grouped) {
         // a postponed update is added to u at once, so that the step leaves
         // the state a real one would after its flush (timed as defer_flush)
         e = after_update(h, st);
         if (e == hipSuccess) e = enq_flush(h, st);
     }
-    if (e == hipSuccess && h->batched)
-        for (int i = 0; i < (int)h->inst.size() && e == hipSuccess; ++i)
-            if (h->inst[i].defer) {
-                ++h->inst[i].pending;
-                e = batched_flush(h, i, st);
-            }
+    if (e == hipSuccess && grouped) {
+        for (auto &I : h->inst) I.pending += I.defer > 0;
+        e = batched_flush(h, std::vector<char>(h->inst.size(), 1), st);
+    }
     h->prof = false;
     hipError_t e2 = hipStreamSynchronize(st);
     int i = 0;
@@ -2344,8 +2327,11 @@ namespace {
 // default uses them (pitch >= 16), else the register-queue kernel with a
 // fixed block size of 256.
 // `copies`: instances of this size in the batch, which share each launch.
-// Longer z marches amortise a tile's pipeline prologue; the plane chunk is
-// chosen so that a launch still has about 4096 tiles.
+// Longer z marches amortise a tile's pipeline prologue, more tiles fill the
+// chip: about 2560 tiles of a large level (blocks of four waves and more), 1280
+// of a small one, but no prologue for a single plane.  (FP16, prolongation +
+// sweep, us: 31^3 x 16 12 with one plane, 9.2 with two; 63^3 x 16 17.5 with two,
+// 15.6 with four; 127^3 x 32 124 with 16, 137 with 32 or with four.)
 Shape batched_shape(int P, int prec, int copies) {
     Shape s{};
     s.xcd = 1;
@@ -2358,9 +2344,9 @@ Shape batched_shape(int P, int prec, int copies) {
             if (stencil_fits(P, (int)prec_bytes(prec), s)) break;
     }
     if (s.ty > 0) {
-        const long ytiles = (P - 1 + s.ty - 1) / s.ty;
-        const long nch = std::max(1L, (4096 + ytiles * copies - 1) / (ytiles * copies));
-        s.zc = std::max(1, std::min(32, (int)((P - 1 + nch - 1) / nch)));
+        const long ytiles = (P - 1 + s.ty - 1) / s.ty, want = P >= 128 ? 2560 : 1280;
+        const long nch = std::max(1L, (want + ytiles * copies - 1) / (ytiles * copies));
+        s.zc = std::max(2, std::min(32, (int)((P - 1 + nch - 1) / nch)));
         return s;
     }
     const long per_chunk = (long)(P / s.V) * P;
@@ -2369,21 +2355,25 @@ Shape batched_shape(int P, int prec, int copies) {
     return s;
 }
 
+// Residual + restriction: V = 8 only for the 2-byte formats (FP32 at V = 8
+// spills: 63^3 x 32 70 us against 19), five coarse rows on large levels (127^3 x
+// 32 in FP16 89 us, 114 with seven), seven on small ones; tiles as above.
 RShape batched_rshape(int P, int pf, int copies) {
+    const bool half = prec_bytes(pf) == 2;
     if (P >= 16) {
-        RShape r{(P >= 8 && pf != P_F64) ? 8 : 4, 1, 1, 1};
+        RShape r{half ? 8 : 4, 1, 1, 1};
         if (P / r.V <= 64) r.pipe = 2;
-        for (r.tyc = std::min(7, P / 2 - 1); r.tyc >= 1; --r.tyc)
+        for (r.tyc = std::min(P >= 128 ? 5 : 7, P / 2 - 1); r.tyc >= 1; --r.tyc)
             if ((2 * r.tyc + 3) * (P / r.V) <= 1024 && restrict_lds_bytes(3, P, pf, r) <= 65536) break;
         if (r.tyc >= 1) {
-            const long ytiles = (P / 2 - 1 + r.tyc - 1) / r.tyc;
-            const long nzc = std::max(1L, (4096 + ytiles * copies - 1) / (ytiles * copies));
+            const long ytiles = (P / 2 - 1 + r.tyc - 1) / r.tyc, want = P >= 128 ? 2560 : 1280;
+            const long nzc = std::max(1L, (want + ytiles * copies - 1) / (ytiles * copies));
             r.zcc = std::max(1, std::min(16, (int)((P / 2 - 1 + nzc - 1) / nzc)));
             return r;
         }
     }
     RShape r;
-    r.V = (P >= 8 && pf != P_F64) ? 8 : 4;
+    r.V = (P >= 8 && half) ? 8 : 4;
     r.pipe = 0;
     const int TXR = P / r.V, Pc = P / 2;
     const size_t acc = pf == P_F64 ? 8 : 4;
@@ -2396,26 +2386,36 @@ RShape batched_rshape(int P, int pf, int copies) {
     return r;
 }
 
-// Fused kernels of a batch: tiles as deep as leaves about `want` work items
-// over the copies of a grid (deeper ones read fewer halo planes).
+// Fused kernels of a batch: tiles as deep as leaves enough work items over the
+// copies of a grid (deeper ones read fewer halo planes).  Sweep + update: 4096
+// waves and 1024 tiles, at least four planes (FP16, us: 127^3 x 8 73.5 with 32
+// planes = 1024 tiles, 79.8 with 16, 104 with 64; 63^3 x 16 27.6 with 8, 35 with
+// 16; 31^3 x 16 12.1 with 4, 16 with 8).
 Shape batched_su_shape(int P, int prec, int copies) {
     for (int ty = 4; ty >= 1; --ty)
         for (int zc : {64, 32, 16, 8, 4, 2, 1}) {
             const Shape s{4, std::min(zc, P - 1), 256, 1, ty};
             if (!sweep_update_ok(P, prec, s)) continue;
-            if (zc == 1 || (long)copies * sweep_update_blocks(P, s) >= 1024) return s;
+            const long items = (long)copies * sweep_update_blocks(P, s), waves = ((ty + 4) * (P / 4) + 63) / 64;
+            if (zc <= 4 || (items >= 1024 && items * waves >= 4096)) return s;
         }
     return Shape{4, 1, 256, 1, 1};
 }
 
+// Smoothing + restriction: eight coarse rows, at pitch 128 five (240 threads:
+// three blocks fit a CU instead of two; 127^3 x 32 in FP16 231 us against 293,
+// 255^3 x 21 1412 against 1074); FP64 blocks hold twice the LDS, so that fewer
+// run at once and deeper ones win (127^3 x 8 73 us with 256 items, 87 with 1024).
 RShape batched_srshape(int P, int prec, int copies) {
     const int Nc = P / 2 - 1;
-    for (int tyc = std::min(8, Nc); tyc >= 1; --tyc)
+    const bool f64 = prec == P_F64, five = P == 128 && !f64;
+    const long want = f64 ? 256 : five ? 1500 : 600;
+    for (int tyc = std::min(five ? 5 : 8, Nc); tyc >= 1; --tyc)
         for (int zcc : {32, 16, 8, 4, 2, 1}) {
             const RShape r{8, tyc, std::min(zcc, Nc), 3};
             if (!smooth_restrict_ok(P, prec, r)) continue;
             const long items = (long)copies * ((Nc + tyc - 1) / tyc) * ((Nc + r.zcc - 1) / r.zcc);
-            if (zcc == 1 || items >= 600) return r;
+            if (zcc == 1 || items >= want) return r;
         }
     return RShape{8, 1, 1, 3};
 }
@@ -2450,7 +2450,7 @@ void build_batched_plan(mg_ctx *h, char *base) {
     const bool alias = h->bprec[0] == P_F64 && !h->opt.residual_scaling;
     std::vector<BDesc> descs;
     std::vector<BItem> items;
-    std::vector<BFin> fins;
+    std::vector<BFin> fins, rfins;    // of the update, of the true residual
     std::vector<unsigned char> recs;  // fused coarse ends
     h->bl.clear();
     std::vector<std::vector<int>> cur(ni, std::vector<int>(h->Lmax, 0));
@@ -2502,14 +2502,18 @@ void build_batched_plan(mg_ctx *h, char *base) {
                 if (!(key_of(p) == k)) continue;
                 const int di = (int)(descs.size() - L.off_desc);
                 descs.push_back(p.d);
-                for (int b = 0; b < p.nblk; ++b) items.push_back(BItem{di, b});
+                // (tile of the b-th workgroup: contiguous ranges of tiles on each XCD)
+                for (int b = 0; b < p.nblk; ++b) {
+                    const int q = p.nblk >> 3, r = p.nblk & 7, j = b & 7;
+                    items.push_back(BItem{di, k.what < 6 ? j * q + std::min(j, r) + (b >> 3) : b});
+                }
                 pts += (double)(p.d.P - 1) * (p.d.P - 1) * (p.d.P - 1);
                 maxthreads = std::max(maxthreads, p.threads);
                 maxlds = std::max(maxlds, p.lds);
             }
             L.ndesc = (int)(descs.size() - L.off_desc);
             L.nitems = (int)(items.size() - L.off_items);
-            L.grid = std::max(1, std::min(L.nitems, k.what == 0 ? 4096 : 2048));
+            L.grid = std::max(1, std::min(L.nitems, 1 << 20));
             // the register restriction tolerates extra threads; the LDS forms
             // take exactly their row groups
             L.threads = k.what == 0 ? 256 : k.what == 1 ? ((maxthreads + 63) / 64) * 64 : maxthreads;
@@ -2690,6 +2694,8 @@ void build_batched_plan(mg_ctx *h, char *base) {
         x.part_off = h->inst[i].part_off, x.inst = i;
         const auto &I = h->inst[i];
         BFin f{part_base + 2 * (size_t)I.part_off, batched_stencil_blocks(L.P, I.osh), Sp(i), I.ascale, nullptr, 1};
+        rfins.push_back(f);
+        rfins.back().count = h->nrhs ? columns_blocks(L.n, h->nrhs) : flat_blocks(points(3, L.n));
         if (I.su) {
             x.b = B(i, 0);
             x.P = L.P, x.ty = I.fsh.ty, x.zc = I.fsh.zc, x.ytiles = (L.P - 1 + I.fsh.ty - 1) / I.fsh.ty;
@@ -2730,13 +2736,14 @@ void build_batched_plan(mg_ctx *h, char *base) {
     // image: descriptors, then items, finalize records, records of the coarse ends
     const size_t nd = descs.size() * sizeof(BDesc), nit = items.size() * sizeof(BItem), nf = fins.size() * sizeof(BFin);
     const size_t off_items = align_up(nd, 256), off_fin = off_items + align_up(nit, 256);
-    const size_t off_rec = off_fin + align_up(nf, 256);
+    const size_t off_rfin = off_fin + align_up(nf, 256), off_rec = off_rfin + align_up(nf, 256);
     h->bmeta_bytes = off_rec + align_up(recs.size(), 256);
     if (base) {
         std::vector<unsigned char> img(h->bmeta_bytes, 0);
         std::memcpy(img.data(), descs.data(), nd);
         std::memcpy(img.data() + off_items, items.data(), nit);
         std::memcpy(img.data() + off_fin, fins.data(), nf);
+        std::memcpy(img.data() + off_rfin, rfins.data(), nf);
         if (!recs.empty()) std::memcpy(img.data() + off_rec, recs.data(), recs.size());
         const BDesc *dd = reinterpret_cast<const BDesc *>(at(h->off_bmeta));
         const BItem *ii = reinterpret_cast<const BItem *>(at(h->off_bmeta + off_items));
@@ -2749,26 +2756,40 @@ void build_batched_plan(mg_ctx *h, char *base) {
             L.off_items = reinterpret_cast<size_t>(ii + L.off_items);
         }
         h->off_fin = h->off_bmeta + off_fin;
+        h->off_rfin = h->off_bmeta + off_rfin;
         // the caller copies img into the workspace
         h->bmeta_img_tmp = std::move(img);
     }
 }
 
-// Add instance i's postponed corrections to its u (nothing pending: a u that
-// is zero and not yet stored is stored).
-hipError_t batched_flush(mg_ctx *h, int i, hipStream_t st) {
-    auto &I = h->inst[i];
-    const LevelPlan &L = I.lv[0];
-    const bool zero = I.u_zero;
-    const int count = I.pending;
-    I.u_zero = false;
-    I.pending = 0;
-    double *U = reinterpret_cast<double *>(h->ws + I.off_U);
-    if (count == 0) return zero ? launch_fill_zero(U, align_up(L.elems * sizeof(double), 16), st) : hipSuccess;
-    const double hh = 1.0 / (double)(L.n + 1);
-    RUN(h, st, "defer_flush", 0, (double)points(3, L.n) * ((zero ? 8 : 16) + count * sb(L.prec)),
-        launch_defer_flush(L.prec, h->ws + I.off_cd, I.cstride, reinterpret_cast<double *>(h->ws + I.off_adef), count,
-                           hh * hh, U, L.elems, reinterpret_cast<int *>(h->ws + h->off_bctr) + i, st, zero));
+// Add the postponed corrections of the instances with sel[i] to their u
+// (nothing pending: a u that is zero and not yet stored is stored).
+hipError_t batched_flush(mg_ctx *h, const std::vector<char> &sel, hipStream_t st) {
+    GroupFlush g{};
+    int m = 0;
+    double bytes = 0.0;
+    const int prec = h->bprec[0], ni = (int)h->inst.size();
+    for (int i = 0; i < ni; ++i) {
+        auto &I = h->inst[i];
+        if (sel[i] && (I.pending || I.u_zero)) {
+            const LevelPlan &L = I.lv[0];
+            const double hh = 1.0 / (double)(L.n + 1);
+            g.cd[m] = h->ws + I.off_cd, g.cstride[m] = I.cstride;
+            g.adef[m] = reinterpret_cast<double *>(h->ws + I.off_adef);
+            g.U[m] = reinterpret_cast<double *>(h->ws + I.off_U);
+            g.ctr[m] = I.defer ? reinterpret_cast<int *>(h->ws + h->off_bctr) + i : nullptr;
+            g.n8[m] = L.elems / 8, g.h2[m] = hh * hh;
+            g.count[m] = I.pending, g.zero[m] = I.u_zero;
+            bytes += (double)points(3, L.n) * ((I.u_zero ? 8 : 16) + I.pending * sb(prec));
+            I.pending = 0;
+            I.u_zero = false;
+            ++m;
+        }
+        if (m == kGroup || (m && i == ni - 1)) {
+            RUN(h, st, "defer_flush", 0, bytes, launch_group_flush(prec, g, m, st));
+            m = 0, bytes = 0.0;
+        }
+    }
     return hipSuccess;
 }
 
@@ -2854,7 +2875,7 @@ template <class F> void for_class(mg_ctx *h, const BClass &c, F &&f) {
 std::string batched_tune_key(const mg_ctx *h) {
     const std::string dk = device_key();
     if (dk.empty()) return dk;
-    std::string k = dk + "|batched|nu" + std::to_string(h->opt.nu1) + "," + std::to_string(h->opt.nu2) + "|sc" +
+    std::string k = dk + (h->nrhs ? "|multi|grids|nu" : "|batched|nu") + std::to_string(h->opt.nu1) + "," + std::to_string(h->opt.nu2) + "|sc" +
                     std::to_string(h->opt.residual_scaling) + "|p";
     for (int p : h->bprec) k += std::to_string(p);
     std::vector<int> ns;
@@ -2962,6 +2983,161 @@ mg_status_t autotune_batched(mg_ctx *h, hipStream_t st) {
     return s;
 }
 
+// Instances of n[i]^3 points: levels, launch shapes, workspace layout.
+void plan_instances(mg_ctx *h, const std::vector<int> &n) {
+    const int ninst = (int)n.size(), Lmax = h->Lmax;
+    const std::vector<int> &prec = h->bprec;
+    const mg_options_t &o = h->opt;
+    h->inst.resize(ninst);
+    // (larger tiles need more LDS than a launch gets unasked)
+    const bool tails = tail_prepare() == hipSuccess, sus = sweep_update_prepare() == hipSuccess;
+    (void)smooth_restrict_prepare();
+    size_t off = 0;
+    int parts = 0;
+    for (int i = 0; i < ninst; ++i) {
+        auto &I = h->inst[i];
+        I.n = n[i];
+        const int copies = (int)std::count(n.begin(), n.end(), n[i]);
+        int m = 0;
+        while ((1 << m) < n[i] + 1) ++m;
+        I.nl = m;
+        I.lv.resize(m);
+        int nn = n[i];
+        for (int l = 0; l < m; ++l) {
+            LevelPlan &L = I.lv[l];
+            L.n = nn, L.P = nn + 1;
+            L.prec = l == m - 1 ? prec[Lmax - 1] : prec[l];
+            L.elems = level_elems(3, L.P);
+            const size_t bytes = align_up(L.elems * prec_bytes(L.prec), 256);
+            L.off_b = off, off += bytes;
+            L.off_c[0] = off, off += bytes;
+            L.off_c[1] = off, off += bytes;
+            if (nn > 1) {
+                L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = batched_shape(L.P, L.prec, copies);
+                L.rsh = batched_rshape(L.P, L.prec, copies);
+                L.fsrsh = batched_srshape(L.P, L.prec, copies);
+            }
+            nn = (nn - 1) / 2;
+        }
+        {
+            std::vector<int> ns(m), pr(m);
+            for (int l = 0; l < m; ++l) ns[l] = I.lv[l].n, pr[l] = I.lv[l].prec;
+            (void)alpha_code(3, ns, pr, std::vector<bool>(m, false), o.residual_scaling, &I.ascale);
+        }
+        const size_t fin = align_up(I.lv[0].elems * sizeof(double), 256);
+        I.off_R = off, off += fin;
+        I.off_U = off, off += fin;
+        I.osh = batched_shape(I.lv[0].P, P_F64, copies);  // V = 4: FP64 rows
+        I.part_off = parts;
+        I.parts = std::max(stencil_blocks(3, I.lv[0].P, I.osh), flat_blocks(points(3, n[i])));
+        if (h->nrhs) I.parts = std::max(I.parts, columns_blocks(n[i], h->nrhs));
+        // the fused coarse end, from the second level on
+        I.lt = m - 1;
+        for (int l = 1; l < m - 1 && I.lt == m - 1 && tails; ++l)
+            if (tail_ok(batched_tail_args(h, i, l))) I.lt = l;
+        // the last sweep fused with the update, where it reads a stored right-hand side
+        I.fsh = batched_su_shape(I.lv[0].P, prec[0], copies);
+        I.su = sus && m >= 2 && !(I.lv[0].prec == P_F64 && !o.residual_scaling) && o.nu2 >= 2 &&
+               sweep_update_ok(I.lv[0].P, I.lv[0].prec, I.fsh);
+        if (I.su) I.parts = std::max(I.parts, sweep_update_blocks(I.lv[0].P, I.fsh));
+        parts += I.parts;
+    }
+    // Postponed updates of u for 2-byte formats: each step stores its correction
+    // (2 bytes per point) in a ring of eight and a pass per eight steps adds
+    // them, 6 instead of 16 bytes per point and step; u is bit for bit the same.
+    // The ring adds 16 bytes per point to the workspace's 16 and the levels', so
+    // very large batches go without.
+    constexpr int kRing = 8;
+    if (off <= (size_t)64 << 30) {
+        for (auto &I : h->inst) {
+            const LevelPlan &L = I.lv[0];
+            if (!I.su || prec_bytes(L.prec) != 2) continue;
+            I.defer = kRing;
+            I.cstride = align_up(L.elems * 2, 256) / 2;
+            I.off_cd = off, off += kRing * I.cstride * 2;
+            I.off_adef = off, off += 256;
+        }
+    }
+    h->off_bctr = off, off += align_up((size_t)ninst * sizeof(int), 256);
+    h->max_parts = parts;
+    h->off_part = off, off += align_up((size_t)parts * 2 * sizeof(double), 256);
+    h->off_scal_all = off, off += align_up((size_t)ninst * 4 * sizeof(double), 256);
+    h->off_active = off, off += align_up((size_t)ninst * sizeof(int), 256);
+    h->off_bmeta = off;
+    build_batched_plan(h, nullptr);
+    // room for the plans of other launch shapes (the autotuner's candidates
+    // with shorter plane chunks have more work items)
+    h->bmeta_cap = align_up(4 * h->bmeta_bytes, 256);
+    off += h->bmeta_cap;
+    h->ws_need = off;
+}
+
+// The vectors of a batched solve: per instance, or interleaved columns.
+struct GroupIo {
+    const double *const *b = nullptr;
+    double *const *u = nullptr;
+    const double *bm = nullptr;
+    double *um = nullptr;
+};
+
+// True residual r = b - A u (use_u; postponed updates are added first) or
+// r = b of the instances with sel[i], with its norms; store_r: keep it as R.
+// write_u: also copy out u (of the selected instances; of every column).
+hipError_t group_resid(mg_ctx *h, const GroupIo &io, const std::vector<char> &sel, bool use_u, bool store_r,
+                       bool write_u, hipStream_t st) {
+    const int ni = (int)h->inst.size();
+    if (use_u) {
+        const hipError_t e = batched_flush(h, write_u && io.bm ? std::vector<char>(ni, 1) : sel, st);
+        if (e != hipSuccess) return e;
+    }
+    double *part_base = at_ws<double>(h, h->off_part);
+    const BFin *fin = at_ws<BFin>(h, h->off_rfin);
+    auto U = [&](int i) { return at_ws<double>(h, h->inst[i].off_U); };
+    auto R = [&](int i) { return store_r ? at_ws<double>(h, h->inst[i].off_R) : nullptr; };
+    if (io.bm) {
+        ColumnsArgs a;
+        a.n = h->inst[0].n, a.K = h->nrhs, a.src = io.bm, a.U = use_u ? U(0) : nullptr, a.R = R(0);
+        a.out = write_u ? io.um : nullptr, a.stride = h->col_stride / sizeof(double);
+        const double hh = 1.0 / (double)(a.n + 1);
+        a.inv_h2 = 1.0 / (hh * hh);
+        a.part = part_base, a.pstride = 2 * (size_t)h->inst[0].parts;
+        for (int i = 0; i < ni; ++i) a.mask |= (unsigned long long)(sel[i] != 0) << i;
+        hipError_t e = launch_columns(a, st);
+        if (e == hipSuccess && a.mask) e = launch_group_finalize(fin, 0, ni, a.mask, h->host_scal_all, st);
+        return e;
+    }
+    // a launch per size and 32 instances
+    std::vector<char> todo(sel);
+    for (int i0 = 0; i0 < ni; ++i0) {
+        if (!todo[i0]) continue;
+        const int n = h->inst[i0].n;
+        GroupResid g{};
+        int m = 0;
+        for (int i = i0; i < ni && m < kGroup; ++i) {
+            if (!todo[i] || h->inst[i].n != n) continue;
+            todo[i] = 0;
+            g.b[m] = io.b[i], g.U[m] = U(i), g.R[m] = R(i), g.uout[m] = write_u ? io.u[i] : nullptr;
+            g.part[m] = part_base + 2 * (size_t)h->inst[i].part_off;
+            ++m;
+        }
+        const double hh = 1.0 / (double)(n + 1);
+        const hipError_t e = launch_group_resid(g, m, n, n + 1, 1.0 / (hh * hh), use_u, st);
+        if (e != hipSuccess) return e;
+    }
+    for (int i0 = 0; i0 < ni; i0 += 64) {
+        unsigned long long mask = 0;
+        const int cnt = std::min(64, ni - i0);
+        for (int j = 0; j < cnt; ++j) mask |= (unsigned long long)(sel[i0 + j] != 0) << j;
+        if (!mask) continue;
+        const hipError_t e = launch_group_finalize(fin, i0, cnt, mask, h->host_scal_all, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+mg_status_t solve_group(mg_ctx *h, const GroupIo &io, mg_stats_t *stats, hipStream_t st,
+                        std::chrono::steady_clock::time_point t0);
+
 }  // namespace
 
 extern "C" {
@@ -3003,87 +3179,7 @@ mg_status_t mg_setup_batched(mg_handle *out, int dim, int ninst, const int *n, c
     h->opt = o;
     h->Lmax = Lmax;
     h->bprec = prec;
-    h->inst.resize(ninst);
-    // (larger tiles need more LDS than a launch gets unasked)
-    const bool tails = tail_prepare() == hipSuccess, sus = sweep_update_prepare() == hipSuccess;
-    (void)smooth_restrict_prepare();
-    size_t off = 0;
-    int parts = 0;
-    for (int i = 0; i < ninst; ++i) {
-        auto &I = h->inst[i];
-        I.n = n[i];
-        const int copies = (int)std::count(n, n + ninst, n[i]);
-        int m = 0;
-        while ((1 << m) < n[i] + 1) ++m;
-        I.nl = m;
-        I.lv.resize(m);
-        int nn = n[i];
-        for (int l = 0; l < m; ++l) {
-            LevelPlan &L = I.lv[l];
-            L.n = nn, L.P = nn + 1;
-            L.prec = l == m - 1 ? prec[Lmax - 1] : prec[l];
-            L.elems = level_elems(3, L.P);
-            const size_t bytes = align_up(L.elems * prec_bytes(L.prec), 256);
-            L.off_b = off, off += bytes;
-            L.off_c[0] = off, off += bytes;
-            L.off_c[1] = off, off += bytes;
-            if (nn > 1) {
-                L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = batched_shape(L.P, L.prec, copies);
-                L.rsh = batched_rshape(L.P, L.prec, copies);
-                L.fsrsh = batched_srshape(L.P, L.prec, copies);
-            }
-            nn = (nn - 1) / 2;
-        }
-        {
-            std::vector<int> ns(m), pr(m);
-            for (int l = 0; l < m; ++l) ns[l] = I.lv[l].n, pr[l] = I.lv[l].prec;
-            (void)alpha_code(3, ns, pr, std::vector<bool>(m, false), o.residual_scaling, &I.ascale);
-        }
-        const size_t fin = align_up(I.lv[0].elems * sizeof(double), 256);
-        I.off_R = off, off += fin;
-        I.off_U = off, off += fin;
-        I.osh = batched_shape(I.lv[0].P, P_F64, copies);  // V = 4: FP64 rows
-        I.part_off = parts;
-        I.parts = std::max(stencil_blocks(3, I.lv[0].P, I.osh), flat_blocks(points(3, n[i])));
-        // the fused coarse end, from the second level on
-        I.lt = m - 1;
-        for (int l = 1; l < m - 1 && I.lt == m - 1 && tails; ++l)
-            if (tail_ok(batched_tail_args(h, i, l))) I.lt = l;
-        // the last sweep fused with the update, where it reads a stored right-hand side
-        I.fsh = batched_su_shape(I.lv[0].P, prec[0], copies);
-        I.su = sus && m >= 2 && !(I.lv[0].prec == P_F64 && !o.residual_scaling) && o.nu2 >= 2 &&
-               sweep_update_ok(I.lv[0].P, I.lv[0].prec, I.fsh);
-        if (I.su) I.parts = std::max(I.parts, sweep_update_blocks(I.lv[0].P, I.fsh));
-        parts += I.parts;
-    }
-    // Postponed updates of u for 2-byte formats: each step stores its correction
-    // (2 bytes per point) in a ring of eight and a pass per eight steps adds
-    // them, 6 instead of 16 bytes per point and step; u is bit for bit the same.
-    // The ring adds 16 bytes per point to the workspace's 16 and the levels', so
-    // very large batches go without.
-    constexpr int kRing = 8;
-    if (off <= (size_t)64 << 30) {
-        for (auto &I : h->inst) {
-            const LevelPlan &L = I.lv[0];
-            if (!I.su || prec_bytes(L.prec) != 2) continue;
-            I.defer = kRing;
-            I.cstride = align_up(L.elems * 2, 256) / 2;
-            I.off_cd = off, off += kRing * I.cstride * 2;
-            I.off_adef = off, off += 256;
-        }
-    }
-    h->off_bctr = off, off += align_up((size_t)ninst * sizeof(int), 256);
-    h->max_parts = parts;
-    h->off_part = off, off += align_up((size_t)parts * 2 * sizeof(double), 256);
-    h->off_scal_all = off, off += align_up((size_t)ninst * 4 * sizeof(double), 256);
-    h->off_active = off, off += align_up((size_t)ninst * sizeof(int), 256);
-    h->off_bmeta = off;
-    build_batched_plan(h, nullptr);
-    // room for the plans of other launch shapes (the autotuner's candidates
-    // with shorter plane chunks have more work items)
-    h->bmeta_cap = align_up(4 * h->bmeta_bytes, 256);
-    off += h->bmeta_cap;
-    h->ws_need = off;
+    plan_instances(h, std::vector<int>(n, n + ninst));
     h->nl = Lmax;
     h->n = n[0];
     *out = h;
@@ -3098,12 +3194,31 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
     mg_status_t s = need_ws(h);
     if (s != MG_OK) return s;
     if (!b || !u) return fail(MG_ERR_ARG, "null argument");
-    const int ni = (int)h->inst.size();
-    for (int i = 0; i < ni; ++i)
+    for (int i = 0; i < (int)h->inst.size(); ++i)
         if (!b[i] || !u[i]) return fail(MG_ERR_ARG, "null pointer for instance %d", i);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    double *part_base = reinterpret_cast<double *>(h->ws + h->off_part);
-    double *scal_all = reinterpret_cast<double *>(h->ws + h->off_scal_all);
+    GroupIo io;
+    io.b = b, io.u = u;
+    return solve_group(h, io, stats, static_cast<hipStream_t>(stream), t0);
+}
+
+mg_status_t mg_instances(mg_handle h, int *ninst) {
+    if (!h || !ninst) return fail(MG_ERR_ARG, "null argument");
+    *ninst = h->batched ? (int)h->inst.size() : 1;
+    return MG_OK;
+}
+
+}  // extern "C"
+
+// ============================================================================
+// Many right-hand sides
+// ============================================================================
+namespace {
+
+// Algorithm 2 on every instance (or column): one work-list launch per stage
+// for all that still step.
+mg_status_t solve_group(mg_ctx *h, const GroupIo &io, mg_stats_t *stats, hipStream_t st,
+                        std::chrono::steady_clock::time_point t0) {
+    const int ni = (int)h->inst.size();
     int *act_dev = reinterpret_cast<int *>(h->ws + h->off_active);
     const double *hs = h->host_scal_all;
     // per instance: ACTIVE (stepping), CHECK (recursive residual below tolerance,
@@ -3116,63 +3231,59 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
     auto hist = [&](int i, int kk, double v) {
         if (stats && stats[i].history && kk < stats[i].history_cap) stats[i].history[kk] = v;
     };
-    auto readback = [&]() -> mg_status_t {
-        HIPCHK(hipMemcpyAsync(h->host_scal_all, scal_all, 4 * sizeof(double) * ni, hipMemcpyDeviceToHost, st));
+    const bool cols = io.bm != nullptr;
+    std::vector<char> sel(ni, 1);
+    // norms (and r) of the instances in sel, read back
+    auto resid = [&](bool use_u, bool store_r, bool write_u) -> mg_status_t {
+        HIPCHK(group_resid(h, io, sel, use_u, store_r, write_u, st));
         HIPCHK(hipStreamSynchronize(st));
         return MG_OK;
     };
-    // r = b - A u of instance i into R (and u copied out to uout) with its norms;
-    // with use_u == false, r = b
-    auto resid = [&](int i, bool use_u, double *uout) -> hipError_t {
-        if (use_u) {
-            const hipError_t e = batched_flush(h, i, st);
-            if (e != hipSuccess) return e;
-        }
-        const auto &I = h->inst[i];
-        const LevelPlan &L = I.lv[0];
-        const double hh = 1.0 / (double)(L.n + 1);
-        double *part = part_base + 2 * (size_t)I.part_off;
-        hipError_t e = launch_resid_flat(3, L.n, L.P, b[i], use_u ? (const double *)(h->ws + I.off_U) : nullptr,
-                                         reinterpret_cast<double *>(h->ws + I.off_R), uout, 1.0 / (hh * hh), part, st);
-        if (e == hipSuccess) e = launch_finalize(part, flat_blocks(points(3, L.n)), scal_all + 4 * i, I.ascale, st);
-        return e;
+    auto select = [&](int what) {
+        for (int i = 0; i < ni; ++i) sel[i] = state[i] == what;
     };
+    mg_status_t s;
     // ||b||_2 of every instance, and the initial residual
     HIPCHK(launch_fill_zero(h->ws + h->off_bctr, align_up((size_t)ni * sizeof(int), 16), st));
-    for (int i = 0; i < ni; ++i) {
-        auto &I = h->inst[i];
-        I.pending = 0;
-        I.u_zero = false;
-        if (h->opt.use_initial_guess) {
-            HIPCHK(launch_resid_flat(3, I.n, I.lv[0].P, b[i], nullptr, nullptr, nullptr, 1.0,
-                                     part_base + 2 * (size_t)I.part_off, st));
-            HIPCHK(launch_finalize(part_base + 2 * (size_t)I.part_off, flat_blocks(points(3, I.n)), scal_all + 4 * i,
-                                   I.ascale, st));
-        } else {
-            HIPCHK(resid(i, false, nullptr));
-            // (with postponed updates the first pass over u starts from zero)
-            if (I.defer) I.u_zero = true;
-            else HIPCHK(launch_fill_zero(h->ws + I.off_U, align_up(I.lv[0].elems * sizeof(double), 16), st));
-        }
-    }
-    if ((s = readback()) != MG_OK) return s;
-    bool any_guess = false;
+    for (auto &I : h->inst) I.pending = 0, I.u_zero = !h->opt.use_initial_guess;
+    // (with postponed updates the first pass over u starts from zero)
+    for (int i = 0; i < ni; ++i) sel[i] = !h->inst[i].defer;
+    HIPCHK(batched_flush(h, sel, st));
+    sel.assign(ni, 1);
+    if ((s = resid(false, !h->opt.use_initial_guess, false)) != MG_OK) return s;
     for (int i = 0; i < ni; ++i) {
         nb[i] = hs[4 * i + 2];
         if (!std::isfinite(nb[i])) {
             state[i] = DEAD, st_i[i] = MG_ERR_NONFINITE, rel[i] = NAN;
         } else if (nb[i] == 0.0) {
-            HIPCHK(hipMemsetAsync(u[i], 0, sizeof(double) * points(3, h->inst[i].n), st));
+            if (!cols) HIPCHK(hipMemsetAsync(io.u[i], 0, sizeof(double) * points(3, h->inst[i].n), st));
             state[i] = DONE;
             hist(i, 0, 0.0);
-        } else if (h->opt.use_initial_guess) {
-            const auto &I = h->inst[i];
-            HIPCHK(launch_pack(3, P_F64, P_F64, I.n, I.lv[0].P, u[i], h->ws + I.off_U, st));
-            HIPCHK(resid(i, true, nullptr));
-            any_guess = true;
         }
     }
-    if (any_guess && (s = readback()) != MG_OK) return s;
+    if (h->opt.use_initial_guess) {
+        if (cols) {
+            ColumnsArgs a;
+            a.n = h->inst[0].n, a.K = ni, a.src = io.um, a.R = at_ws<double>(h, h->inst[0].off_U);
+            a.stride = h->col_stride / sizeof(double);
+            for (int i = 0; i < ni; ++i) {
+                // (a zero right-hand side has the solution zero)
+                h->inst[i].u_zero = nb[i] == 0.0;
+                a.mask |= (unsigned long long)(nb[i] != 0.0) << i;
+            }
+            if (a.mask) HIPCHK(launch_columns(a, st));
+        }
+        bool any = false;
+        for (int i = 0; i < ni; ++i) {
+            sel[i] = state[i] == ACTIVE;
+            any = any || sel[i];
+            if (sel[i] && !cols) {
+                const auto &I = h->inst[i];
+                HIPCHK(launch_pack(3, P_F64, P_F64, I.n, I.lv[0].P, io.u[i], h->ws + I.off_U, st));
+            }
+        }
+        if (any && (s = resid(true, true, false)) != MG_OK) return s;
+    }
     const bool graph = h->opt.use_graph && !h->prof;
     if (graph && !(h->gexec && h->gexec2)) {
         // the V-cycles and the update as two graphs (see ir_solve)
@@ -3202,6 +3313,11 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
     // as they are and write only level vectors, so they are good for every
     // instance that goes on, and do nothing to one that stops
     bool cycle_queued = false;
+    // columns: u has been written out, for all of them (b may be u's array: then only at the end)
+    bool joined = false;
+    const size_t iobytes = cols ? sizeof(double) * points(3, h->inst[0].n) * ni : 0;
+    const uintptr_t ba = reinterpret_cast<uintptr_t>(io.bm), ua = reinterpret_cast<uintptr_t>(io.um);
+    const bool overlap = cols && ba < ua + iobytes && ua < ba + iobytes;
     std::vector<double> prev(ni, -1.0);
     bool first_step = true;
     for (;;) {
@@ -3225,9 +3341,11 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
             }
         }
         if (ncheck > 0) {
-            for (int i = 0; i < ni; ++i)
-                if (state[i] == CHECK) HIPCHK(resid(i, true, u[i]));
-            if ((s = readback()) != MG_OK) return s;
+            // (columns are written out together: here only if all are to be
+            // confirmed, else at the end)
+            select(CHECK);
+            joined = cols && ncheck == ni && !overlap;
+            if ((s = resid(true, true, !cols || joined)) != MG_OK) return s;
             for (int i = 0; i < ni; ++i) {
                 if (state[i] != CHECK) continue;
                 const double rn = hs[4 * i + 2];
@@ -3265,12 +3383,16 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
             more = more || (k[i] + 1 < h->opt.max_iter && rn * rho > 8.0 * h->opt.rtol * nb[i]);
             prev[i] = rn;
         }
+        joined = false;
         hipError_t e = cycle_queued ? hipSuccess : launch(true);
         if (e == hipSuccess) e = launch(false);
         if (e == hipSuccess) e = hipEventRecord(h->ev_norm, st);
-        for (int i = 0; i < ni && e == hipSuccess; ++i)
-            if (state[i] == ACTIVE && h->inst[i].defer && ++h->inst[i].pending >= h->inst[i].defer)
-                e = batched_flush(h, i, st);
+        bool full = false;
+        for (int i = 0; i < ni; ++i) {
+            sel[i] = state[i] == ACTIVE && h->inst[i].defer && ++h->inst[i].pending >= h->inst[i].defer;
+            full = full || sel[i];
+        }
+        if (e == hipSuccess && full) e = batched_flush(h, sel, st);
         cycle_queued = false;
         if (e == hipSuccess && more) {
             e = launch(true);
@@ -3282,16 +3404,16 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
             if (state[i] == ACTIVE) ++k[i];
     }
     // instances that stopped without a confirmation: true residual and u
-    bool pending = false;
-    for (int i = 0; i < ni; ++i)
-        if (state[i] == STOP) {
-            HIPCHK(resid(i, true, u[i]));
-            pending = true;
-        }
-    if (pending) {
-        if ((s = readback()) != MG_OK) return s;
+    select(STOP);
+    if (std::count(sel.begin(), sel.end(), 1)) {
+        if ((s = resid(true, true, !cols)) != MG_OK) return s;
         for (int i = 0; i < ni; ++i)
             if (state[i] == STOP) rel[i] = hs[4 * i + 2] / nb[i];
+    }
+    if (cols && !joined) {
+        // u out, every column (those that failed keep their last iterate)
+        sel.assign(ni, 0);
+        HIPCHK(group_resid(h, io, sel, true, false, true, st));
     }
     HIPCHK(hipStreamSynchronize(st));
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -3305,164 +3427,8 @@ mg_status_t ir_solve_batched(mg_handle h, const double *const *b, double *const 
         }
         if (st_i[i] != MG_OK && result == MG_OK) result = st_i[i], first_bad = i;
     }
-    if (result != MG_OK) return fail(result, "%s (first in instance %d)", mg_status_string(result), first_bad);
-    return MG_OK;
-}
-
-mg_status_t mg_instances(mg_handle h, int *ninst) {
-    if (!h || !ninst) return fail(MG_ERR_ARG, "null argument");
-    *ninst = h->batched ? (int)h->inst.size() : 1;
-    return MG_OK;
-}
-
-}  // extern "C"
-
-// ============================================================================
-// Many right-hand sides, interleaved
-// ============================================================================
-namespace {
-
-int m_zc(int prec, int P, int K) {
-    const long per_chunk = (long)(P - 1) * (K / m_vec(prec)) * (P - 1);
-    const long nch = std::max(1L, ((1L << 19) + per_chunk - 1) / per_chunk);
-    return std::max(1, std::min((int)((P - 1 + nch - 1) / nch), 64));
-}
-
-hipError_t enq_multi_step(mg_ctx *h, hipStream_t st) {
-    const int K = h->nrhs, nl = h->nl;
-    const bool alias = finest_alias(h);
-    double *sc = scal(h);
-    const int *act = at_ws<int>(h, h->off_act);
-    auto rhs = [&](int l) -> const void * { return (l == 0 && alias) ? (const void *)Rbuf(h) : bbuf(h, l); };
-    for (int l = 0; l + 1 < nl; ++l) {
-        LevelPlan &L = h->lv[l];
-        const double N = (double)points(3, L.n) * K;
-        const double s = sb(L.prec);
-        MArgs a;
-        a.prec = L.prec, a.P = L.P, a.K = K, a.zc = L.shs[SH_SMOOTH].zc, a.omega = h->opt.omega;
-        a.cout = cbuf(h, l, 0);
-        if (l == 0 && !alias) {
-            a.r = Rbuf(h), a.inv = sc + K, a.act = act, a.bout = bbuf(h, 0);
-            RUN(h, st, "smooth2_scaled", l, N * (8 + 2 * s), launch_m_stage(MS_SMOOTH2, a, st));
-        } else {
-            a.b = rhs(l);
-            RUN(h, st, "smooth2", l, N * 2 * s, launch_m_stage(MS_SMOOTH2, a, st));
-        }
-        int cur = 0;
-        for (int k = 2; k < h->opt.nu1; ++k) {
-            MArgs w;
-            w.prec = L.prec, w.P = L.P, w.K = K, w.zc = L.shs[SH_SWEEP].zc, w.omega = h->opt.omega;
-            w.b = rhs(l), w.cin = cbuf(h, l, cur), w.cout = cbuf(h, l, cur ^ 1);
-            RUN(h, st, "sweep", l, N * 3 * s, launch_m_stage(MS_SWEEP, w, st));
-            cur ^= 1;
-        }
-        h->cur[l] = cur;
-        MArgs r;
-        r.prec = L.prec, r.pc = h->lv[l + 1].prec, r.P = L.P, r.K = K, r.zc = L.shs[SH_SWEEP].zc;
-        r.b = rhs(l), r.cin = cbuf(h, l, cur), r.cout = bbuf(h, l + 1);
-        RUN(h, st, "resid_restrict", l, N * 2 * s + (double)points(3, h->lv[l + 1].n) * K * sb(r.pc),
-            launch_m_restrict2(r, h->ws + h->off_mres, L.rsh.zcc, st));
-    }
-    RUN(h, st, "coarse_solve", nl - 1, 2.0 * K * sb(h->lv[nl - 1].prec),
-        launch_m_coarse(h->lv[nl - 1].prec, K, bbuf(h, nl - 1), cbuf(h, nl - 1, 0), st));
-    h->cur[nl - 1] = 0;
-    for (int l = nl - 2; l >= 0; --l) {
-        LevelPlan &L = h->lv[l];
-        const double N = (double)points(3, L.n) * K;
-        const double s = sb(L.prec);
-        int cur = h->cur[l];
-        MArgs a;
-        a.prec = L.prec, a.pc = h->lv[l + 1].prec, a.P = L.P, a.K = K, a.zc = L.shs[SH_PROLONG].zc;
-        a.omega = h->opt.omega;
-        a.b = rhs(l), a.cin = cbuf(h, l, cur), a.ec = cbuf(h, l + 1, h->cur[l + 1]), a.cout = cbuf(h, l, cur ^ 1);
-        RUN(h, st, "prolong", l, N * 2 * s + (double)points(3, h->lv[l + 1].n) * K * sb(a.pc),
-            launch_m_prolong_field(a, st));
-        RUN(h, st, "prolong_sweep", l, N * 3 * s, launch_m_stage(MS_SWEEP, a, st));
-        cur ^= 1;
-        for (int k = 1; k < h->opt.nu2; ++k) {
-            MArgs w;
-            w.prec = L.prec, w.P = L.P, w.K = K, w.zc = L.shs[SH_SWEEP].zc, w.omega = h->opt.omega;
-            w.b = rhs(l), w.cin = cbuf(h, l, cur), w.cout = cbuf(h, l, cur ^ 1);
-            RUN(h, st, "sweep", l, N * 3 * s, launch_m_stage(MS_SWEEP, w, st));
-            cur ^= 1;
-        }
-        h->cur[l] = cur;
-    }
-    LevelPlan &L = h->lv[0];
-    const double hh = 1.0 / (double)(L.n + 1);
-    const double N = (double)points(3, L.n) * K;
-    MArgs u;
-    u.prec = L.prec, u.P = L.P, u.K = K, u.zc = L.osh.zc, u.cin = cbuf(h, 0, h->cur[0]), u.act = act;
-    RUN(h, st, "ir_update", 0, N * (32 + sb(L.prec)), launch_m_update(u, Rbuf(h), Ubuf(h), sc, hh * hh, part(h), st));
-    RUN(h, st, "norm_finalize", 0, 16.0 * h->m_upd_blocks * K,
-        launch_m_finalize(part(h), h->m_upd_blocks, K, sc, act, h->ascale, st));
-    return hipMemcpyAsync(h->host_scal_m, sc, 4 * sizeof(double) * K, hipMemcpyDeviceToHost, st);
-}
-
-// ---- many-right-hand-side autotuner --------------------------------------------
-// Per level, the planes per thread of the first smoothing, the sweeps (and the
-// residual pass of the restriction), the prolongation and the coarse planes
-// per block of the restriction, each timed as a whole refinement step with
-// every column active (the update keeps its shape: its block count sizes the
-// reduction partials).  Every choice forms the same roundings.
-std::string multi_tune_key(const mg_ctx *h) {
-    const std::string dk = device_key();
-    if (dk.empty()) return dk;
-    std::string k = dk + "|multi|n" + std::to_string(h->n) + "|K" + std::to_string(h->nrhs) + "|nu" +
-                    std::to_string(h->opt.nu1) + "," + std::to_string(h->opt.nu2) + "|sc" +
-                    std::to_string(h->opt.residual_scaling) + "|p";
-    for (int l = 0; l < h->nl; ++l) k += std::to_string(h->lv[l].prec);
-    return k;
-}
-
-constexpr int kMLevelInts = 4;  // zc of smoothing, sweeps, prolongation; zcc of the restriction
-
-bool apply_multi_state(mg_ctx *h, const std::vector<int> &v) {
-    if (v.size() != (size_t)(h->nl - 1) * kMLevelInts) return false;
-    for (int l = 0; l + 1 < h->nl; ++l) {
-        const int *q = v.data() + l * kMLevelInts, P = h->lv[l].P;
-        for (int j = 0; j < 3; ++j)
-            if (q[j] < 1 || q[j] > std::max(1, P - 1)) return false;
-        if (q[3] < 1 || q[3] > std::max(1, P / 2 - 1)) return false;
-    }
-    for (int l = 0; l + 1 < h->nl; ++l) {
-        const int *q = v.data() + l * kMLevelInts;
-        LevelPlan &L = h->lv[l];
-        L.shs[SH_SMOOTH].zc = q[0], L.shs[SH_SWEEP].zc = q[1], L.shs[SH_PROLONG].zc = q[2], L.rsh.zcc = q[3];
-    }
-    return true;
-}
-
-mg_status_t autotune_multi(mg_ctx *h, hipStream_t st) {
-    const std::string key = multi_tune_key(h);
-    std::vector<int> v;
-    if (cache_read(key, v) && apply_multi_state(h, v)) return MG_OK;
-    const int K = h->nrhs;
-    for (int k = 0; k < K; ++k) h->host_mask[k] = 1;
-    HIPCHK(hipMemcpy(h->ws + h->off_act, h->host_mask, sizeof(int) * K, hipMemcpyHostToDevice));
-    auto step_ms = [&]() { return time_ms(st, [&]() { return enq_multi_step(h, st); }, 2); };
-    v.clear();
-    for (int l = 0; l + 1 < h->nl; ++l) {
-        LevelPlan &L = h->lv[l];
-        int *knobs[4] = {&L.shs[SH_SMOOTH].zc, &L.shs[SH_SWEEP].zc, &L.shs[SH_PROLONG].zc, &L.rsh.zcc};
-        const int lim[4] = {L.P - 1, L.P - 1, L.P - 1, L.P / 2 - 1};
-        for (int j = 0; j < 4; ++j) {
-            if (lim[j] < 2) continue;
-            int bestv = *knobs[j];
-            float best = step_ms();
-            for (int zc : {1, 2, 4, 8, 16, 32, 64}) {
-                if (zc > lim[j] || zc == bestv) continue;
-                *knobs[j] = zc;
-                const float t = step_ms();
-                if (t < best) best = t, bestv = zc;
-            }
-            *knobs[j] = bestv;
-        }
-        v.insert(v.end(), {L.shs[SH_SMOOTH].zc, L.shs[SH_SWEEP].zc, L.shs[SH_PROLONG].zc, L.rsh.zcc});
-    }
-    HIPCHK(hipMemsetAsync(h->ws, 0, h->ws_need, st));
-    HIPCHK(hipStreamSynchronize(st));
-    cache_write(key, v);
+    if (result != MG_OK) return fail(result, "%s (first in %s %d)", mg_status_string(result),
+                                     cols ? "right-hand side" : "instance", first_bad);
     return MG_OK;
 }
 
@@ -3498,9 +3464,9 @@ mg_status_t mg_setup_multi(mg_handle *out, int dim, int n, int nrhs, const mg_pr
             prec[l] = (int)level_prec[l];
         }
     for (int l = 0; l < m; ++l)
-        if (!m_supported(prec[l], nrhs))
+        if (!columns_ok(prec[l], nrhs))
             return fail(MG_ERR_ARG, "nrhs = %d is below the %d columns a thread of level %d handles", nrhs,
-                        m_vec(prec[l]), l);
+                        prec[l] == P_F64 ? 4 : 8, l);
     int ascale = 0;
     {
         std::vector<int> ns(m);
@@ -3510,40 +3476,12 @@ mg_status_t mg_setup_multi(mg_handle *out, int dim, int n, int nrhs, const mg_pr
     mg_ctx *h = new mg_ctx();
     h->dim = 3, h->n = n, h->nl = m, h->opt = o, h->nrhs = nrhs;
     h->ascale = ascale;
-    h->lv.resize(m);
-    const int K = nrhs;
-    size_t off = 0;
-    int nn = n;
-    for (int l = 0; l < m; ++l) {
-        LevelPlan &L = h->lv[l];
-        L.n = nn, L.P = nn + 1, L.prec = prec[l];
-        L.elems = level_elems(3, L.P) * K;
-        const size_t bytes = align_up(L.elems * prec_bytes(L.prec), 256);
-        L.off_b = off, off += bytes;
-        L.off_c[0] = off, off += bytes;
-        L.off_c[1] = off, off += bytes;
-        if (nn > 1) {
-            Shape s{m_vec(L.prec), m_zc(L.prec, L.P, K), 256, 0, 0};
-            L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = s;
-            L.osh = Shape{4, m_zc(P_F64, L.P, K), 256, 0, 0};
-            L.rsh = RShape{m_vec(L.prec), 1, m_zc(L.prec, L.P / 2, K), 0};
-        }
-        nn = (nn - 1) / 2;
-    }
-    const size_t fin = align_up(h->lv[0].elems * sizeof(double), 256);
-    h->off_R = off, off += fin;
-    h->off_U = off, off += fin;
-    h->m_upd_blocks = m_update_blocks(h->lv[0].prec, h->lv[0].P, K, h->lv[0].osh.zc);
-    h->max_parts = std::max(h->m_upd_blocks, m_resid_blocks(n));
-    h->off_part = off, off += align_up((size_t)h->max_parts * K * 2 * sizeof(double), 256);
-    h->off_scal = off, off += align_up(4 * sizeof(double) * K, 256);
-    h->off_act = off, off += 256;
-    h->off_mask = off, off += 256;
-    h->off_zmask = off, off += 256;
-    size_t mres = 0;
-    for (int l = 0; l + 1 < m; ++l) mres = std::max(mres, m_resid_bytes(h->lv[l].prec, h->lv[l].elems));
-    h->off_mres = off, off += align_up(mres, 256);
-    h->ws_need = off;
+    h->Lmax = m;
+    h->bprec = prec;
+    plan_instances(h, std::vector<int>(nrhs, n));
+    h->col_stride = h->inst[1].off_R - h->inst[0].off_R;
+    h->lv = h->inst[0].lv;  // (the shapes that mg_get_shape reports)
+    h->lv[0].osh = h->inst[0].osh;
     *out = h;
     return MG_OK;
 }
@@ -3555,157 +3493,9 @@ mg_status_t ir_solve_multi(mg_handle h, const double *b, double *u, mg_stats_t *
     mg_status_t s = need_ws(h);
     if (s != MG_OK) return s;
     if (!b || !u) return fail(MG_ERR_ARG, "null argument");
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const int K = h->nrhs;
-    const LevelPlan &L = h->lv[0];
-    const int n = L.n, P = L.P;
-    const double hh = 1.0 / (double)(n + 1);
-    const double inv_h2 = 1.0 / (hh * hh);
-    const int scaling = h->ascale;
-    const int rparts = m_resid_blocks(n);
-    double *sc = scal(h);
-    const double *hs = h->host_scal_m;
-    int *act_dev = at_ws<int>(h, h->off_act);
-    int *mask_dev = at_ws<int>(h, h->off_mask);
-    const int *zmask = at_ws<int>(h, h->off_zmask);
-    int *hact = h->host_mask, *hmask = h->host_mask + K;
-    enum { ACTIVE, CHECK, DONE, STOP, DEAD };
-    std::vector<double> nb(K, 0.0), rel(K, 0.0);
-    std::vector<int> it(K, 0), state(K, ACTIVE);
-    std::vector<mg_status_t> st_k(K, MG_OK);
-    auto hist = [&](int k, int kk, double v) {
-        if (stats && stats[k].history && kk < stats[k].history_cap) stats[k].history[kk] = v;
-    };
-    auto readback = [&]() -> mg_status_t {
-        HIPCHK(hipMemcpyAsync(h->host_scal_m, sc, 4 * sizeof(double) * K, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        return MG_OK;
-    };
-    // true residual and norms of the columns in `which` (mask uploaded first)
-    auto resid_cols = [&](const std::vector<int> &which) -> mg_status_t {
-        HIPCHK(hipStreamSynchronize(st));  // an earlier copy may still read hmask
-        for (int k = 0; k < K; ++k) hmask[k] = which[k];
-        HIPCHK(hipMemcpyAsync(mask_dev, hmask, sizeof(int) * K, hipMemcpyHostToDevice, st));
-        HIPCHK(launch_m_resid(n, P, K, b, Ubuf(h), Rbuf(h), nullptr, mask_dev, inv_h2, part(h), st));
-        HIPCHK(launch_m_finalize(part(h), rparts, K, sc, mask_dev, scaling, st));
-        return readback();
-    };
-    // ||b||_2 per column (r = b when starting from zero)
-    if (h->opt.use_initial_guess) {
-        HIPCHK(launch_m_resid(n, P, K, b, nullptr, nullptr, nullptr, nullptr, inv_h2, part(h), st));
-    } else {
-        HIPCHK(launch_m_resid(n, P, K, b, nullptr, Rbuf(h), nullptr, nullptr, inv_h2, part(h), st));
-        HIPCHK(launch_fill_zero(Ubuf(h), align_up(L.elems * sizeof(double), 16), st));
-    }
-    HIPCHK(launch_m_finalize(part(h), rparts, K, sc, nullptr, scaling, st));
-    if ((s = readback()) != MG_OK) return s;
-    for (int k = 0; k < K; ++k) {
-        nb[k] = hs[2 * K + k];
-        if (!std::isfinite(nb[k])) {
-            state[k] = DEAD, st_k[k] = MG_ERR_NONFINITE, rel[k] = NAN;
-        } else if (nb[k] == 0.0) {
-            state[k] = DONE;  // u = 0: its column of U is (made) zero
-            hist(k, 0, 0.0);
-        }
-    }
-    if (h->opt.use_initial_guess) {
-        for (int k = 0; k < K; ++k) hmask[k] = nb[k] != 0.0;
-        HIPCHK(hipMemcpyAsync(mask_dev, hmask, sizeof(int) * K, hipMemcpyHostToDevice, st));
-        HIPCHK(launch_m_pack(n, P, K, u, Ubuf(h), mask_dev, st));
-        std::vector<int> all(K, 1);
-        if ((s = resid_cols(all)) != MG_OK) return s;
-    }
-    const bool graph = h->opt.use_graph && !h->prof;
-    if (graph && !h->gexec) {
-        if (!h->cap_stream) HIPCHK(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-        HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-        hipError_t e = enq_multi_step(h, h->cap_stream);
-        hipGraph_t g = nullptr;
-        hipError_t e2 = hipStreamEndCapture(h->cap_stream, &g);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (g) (void)hipGraphDestroy(g);
-            return fail(MG_ERR_HIP, "capture of the interleaved step failed: %s",
-                        hipGetErrorString(e != hipSuccess ? e : e2));
-        }
-        h->graph = g;
-        HIPCHK(hipGraphInstantiate(&h->gexec, h->graph, nullptr, nullptr, 0));
-    }
-    for (;;) {
-        int nact = 0, ncheck = 0;
-        std::vector<int> check(K, 0);
-        for (int k = 0; k < K; ++k) {
-            if (state[k] != ACTIVE) continue;
-            const double rn = hs[2 * K + k];
-            rel[k] = rn / nb[k];
-            hist(k, it[k], rel[k]);
-            if (!std::isfinite(rn)) {
-                state[k] = STOP, st_k[k] = MG_ERR_NONFINITE;
-            } else if (rn <= h->opt.rtol * nb[k]) {
-                state[k] = it[k] > 0 ? CHECK : STOP;
-                if (it[k] > 0) check[k] = 1, ++ncheck;
-            } else if (it[k] >= h->opt.max_iter) {
-                state[k] = STOP, st_k[k] = MG_ERR_NOT_CONVERGED;
-            } else {
-                ++nact;
-            }
-        }
-        if (ncheck > 0) {
-            // confirm from u; only these columns' R and norms are rewritten
-            if ((s = resid_cols(check)) != MG_OK) return s;
-            for (int k = 0; k < K; ++k) {
-                if (!check[k]) continue;
-                const double rn = hs[2 * K + k];
-                rel[k] = rn / nb[k];
-                hist(k, it[k], rel[k]);
-                if (rn <= h->opt.rtol * nb[k]) {
-                    state[k] = DONE;
-                } else if (!std::isfinite(rn) || it[k] >= h->opt.max_iter) {
-                    state[k] = DONE;
-                    st_k[k] = std::isfinite(rn) ? MG_ERR_NOT_CONVERGED : MG_ERR_NONFINITE;
-                } else {
-                    state[k] = ACTIVE;
-                    ++nact;
-                }
-            }
-        }
-        if (nact == 0) break;
-        for (int k = 0; k < K; ++k) hact[k] = state[k] == ACTIVE;
-        HIPCHK(hipMemcpyAsync(act_dev, hact, sizeof(int) * K, hipMemcpyHostToDevice, st));
-        if (graph) {
-            HIPCHK(hipGraphLaunch(h->gexec, st));
-        } else {
-            hipError_t e = enq_multi_step(h, st);
-            if (e != hipSuccess) return fail(MG_ERR_HIP, "interleaved step failed: %s", hipGetErrorString(e));
-        }
-        HIPCHK(hipStreamSynchronize(st));
-        for (int k = 0; k < K; ++k)
-            if (state[k] == ACTIVE) ++it[k];
-    }
-    std::vector<int> stop(K, 0);
-    bool any_stop = false;
-    for (int k = 0; k < K; ++k)
-        if (state[k] == STOP) stop[k] = 1, any_stop = true;
-    if (any_stop) {
-        if ((s = resid_cols(stop)) != MG_OK) return s;
-        for (int k = 0; k < K; ++k)
-            if (stop[k]) rel[k] = hs[2 * K + k] / nb[k];
-    }
-    // u out, every column (held columns keep their last iterate)
-    HIPCHK(launch_m_resid(n, P, K, b, Ubuf(h), nullptr, u, zmask, inv_h2, part(h), st));
-    HIPCHK(hipStreamSynchronize(st));
-    const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-    mg_status_t result = MG_OK;
-    int first_bad = -1;
-    for (int k = 0; k < K; ++k) {
-        if (stats) {
-            stats[k].iterations = it[k];
-            stats[k].rel_residual = nb[k] == 0.0 ? 0.0 : rel[k];
-            stats[k].seconds = secs;
-        }
-        if (st_k[k] != MG_OK && result == MG_OK) result = st_k[k], first_bad = k;
-    }
-    if (result != MG_OK) return fail(result, "%s (first in right-hand side %d)", mg_status_string(result), first_bad);
-    return MG_OK;
+    GroupIo io;
+    io.bm = b, io.um = u;
+    return solve_group(h, io, stats, static_cast<hipStream_t>(stream), t0);
 }
 
 mg_status_t mg_rhs_count(mg_handle h, int *nrhs) {

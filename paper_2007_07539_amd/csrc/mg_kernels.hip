@@ -1272,10 +1272,9 @@ template <int D, class T> __global__ void k_coarse(const T *__restrict__ b, T *_
 // (grid-stride over rows), consecutive lanes on consecutive x, so both the
 // dense arrays and the padded ones are read and written coalesced.
 template <int D>
-__global__ __launch_bounds__(256) void k_resid_rows(const double *__restrict__ b, const double *__restrict__ U,
-                                                    double *__restrict__ R, double *__restrict__ uout, int n, int P,
-                                                    double inv_h2, double *__restrict__ part) {
-    __shared__ double red[8];
+__device__ __forceinline__ void resid_rows_body(const double *__restrict__ b, const double *__restrict__ U,
+                                                double *__restrict__ R, double *__restrict__ uout, int n, int P,
+                                                double inv_h2, double *__restrict__ part, double *red) {
     const Grid<D> g{P};
     const size_t plane = D == 3 ? (size_t)P * P : (size_t)P;
     const long rows = D == 3 ? (long)n * n : (long)n;
@@ -1319,6 +1318,14 @@ __global__ __launch_bounds__(256) void k_resid_rows(const double *__restrict__ b
     }
 }
 
+template <int D>
+__global__ __launch_bounds__(256) void k_resid_rows(const double *__restrict__ b, const double *__restrict__ U,
+                                                    double *__restrict__ R, double *__restrict__ uout, int n, int P,
+                                                    double inv_h2, double *__restrict__ part) {
+    __shared__ double red[8];
+    resid_rows_body<D>(b, U, R, uout, n, P, inv_h2, part, red);
+}
+
 // The same residual in 3-D, marching z: a tile is four consecutive rows y (one
 // wave each, lane l on x = l + 64 k) and a chunk of zc planes.  Each lane keeps
 // U of its points on planes z-1, z, z+1 in registers, so a plane of U is read
@@ -1328,11 +1335,10 @@ __global__ __launch_bounds__(256) void k_resid_rows(const double *__restrict__ b
 // ranges (neighbouring y bands share an L2).  Blocks loop over tiles
 // (gridDim.x may be below the tile count); one partial per block.
 template <int KX>
-__global__ __launch_bounds__(256) void k_resid_march(const double *__restrict__ b, const double *__restrict__ U,
-                                                     double *__restrict__ R, double *__restrict__ uout, int n, int P,
-                                                     double inv_h2, double *__restrict__ part, int ytiles, int zc,
-                                                     int ntiles) {
-    __shared__ double red[8];
+__device__ __forceinline__ void resid_march_body(const double *__restrict__ b, const double *__restrict__ U,
+                                                 double *__restrict__ R, double *__restrict__ uout, int n, int P,
+                                                 double inv_h2, double *__restrict__ part, int ytiles, int zc,
+                                                 int ntiles, double *red) {
     const Grid<3> g{P};
     const size_t plane = (size_t)P * P;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1389,6 +1395,30 @@ __global__ __launch_bounds__(256) void k_resid_march(const double *__restrict__ 
     }
 }
 
+template <int KX>
+__global__ __launch_bounds__(256) void k_resid_march(const double *__restrict__ b, const double *__restrict__ U,
+                                                     double *__restrict__ R, double *__restrict__ uout, int n, int P,
+                                                     double inv_h2, double *__restrict__ part, int ytiles, int zc,
+                                                     int ntiles) {
+    __shared__ double red[8];
+    resid_march_body<KX>(b, U, R, uout, n, P, inv_h2, part, ytiles, zc, ntiles, red);
+}
+
+// The same for up to kGroup grids of one size in a launch, grid blockIdx.y on
+// its own pointers: a launch per grid left the chip waiting on launches (20
+// grids of 63^3: 60 launches of about 5 us at the start of a solve and as many
+// at its end).  KX = 0: r = b.
+template <int KX>
+__global__ __launch_bounds__(256) void k_group_resid(const GroupResid g, int n, int P, double inv_h2, int ytiles,
+                                                     int zc, int ntiles) {
+    __shared__ double red[8];
+    const int i = blockIdx.y;
+    if constexpr (KX == 0)
+        resid_rows_body<3>(g.b[i], nullptr, g.R[i], nullptr, n, P, inv_h2, g.part[i], red);
+    else
+        resid_march_body<KX>(g.b[i], g.U[i], g.R[i], g.uout[i], n, P, inv_h2, g.part[i], ytiles, zc, ntiles, red);
+}
+
 // host: pinned host memory that also receives the four scalars (vector stores;
 // the host reads them after the stream or an event behind this kernel has been
 // waited for).  A copy command behind the kernel took 2-4 us of every step.
@@ -1428,10 +1458,10 @@ __global__ __launch_bounds__(1024) void k_finalize(const double *__restrict__ pa
 // from_zero: u starts from 0 (the same sums as from a zero-filled U, which is
 // then neither filled nor read).
 template <class T>
-__global__ __launch_bounds__(256) void k_defer_flush(const T *__restrict__ cd, size_t cstride,
-                                                     const double *__restrict__ adef, int count, double h2,
-                                                     double *__restrict__ U, size_t n8, int *__restrict__ ctr,
-                                                     int from_zero) {
+__device__ __forceinline__ void defer_flush_body(const T *__restrict__ cd, size_t cstride,
+                                                 const double *__restrict__ adef, int count, double h2,
+                                                 double *__restrict__ U, size_t n8, int *__restrict__ ctr,
+                                                 int from_zero) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n8; i += (size_t)gridDim.x * blockDim.x) {
         double u[8];
         if (from_zero) {
@@ -1449,7 +1479,22 @@ __global__ __launch_bounds__(256) void k_defer_flush(const T *__restrict__ cd, s
         }
         store_row<double, 8>(U + 8 * i, u);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *ctr = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && ctr) *ctr = 0;
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_defer_flush(const T *__restrict__ cd, size_t cstride,
+                                                     const double *__restrict__ adef, int count, double h2,
+                                                     double *__restrict__ U, size_t n8, int *__restrict__ ctr,
+                                                     int from_zero) {
+    defer_flush_body<T>(cd, cstride, adef, count, h2, U, n8, ctr, from_zero);
+}
+
+// The same for up to kGroup grids in a launch (grid blockIdx.y).
+template <class T> __global__ __launch_bounds__(256) void k_group_flush(const GroupFlush g) {
+    const int i = blockIdx.y;
+    defer_flush_body<T>(static_cast<const T *>(g.cd[i]), g.cstride[i], g.adef[i], g.count[i], g.h2[i], g.U[i],
+                        g.n8[i], g.ctr[i], g.zero[i]);
 }
 
 template <int D, class TS, class TD>
@@ -1930,6 +1975,41 @@ hipError_t launch_defer_flush(int prec, const void *cdefer, size_t cstride, cons
     return hipGetLastError();
 }
 
+hipError_t launch_group_resid(const GroupResid &g, int count, int n, int P, double inv_h2, bool use_u, hipStream_t st) {
+    if (count < 1 || count > kGroup) return hipErrorInvalidValue;
+    const int blocks = flat_blocks((long)n * n * n);
+    const int ytiles = (n + 3) / 4;
+    const int nzparts = std::max(1, (blocks + ytiles - 1) / ytiles);
+    const int zc = std::max(1, (n + nzparts - 1) / nzparts);
+    const int ntiles = ytiles * ((n + zc - 1) / zc);
+    const int kx = use_u ? (n + 63) / 64 : 0;
+#define MG_GR(KX)                                                                                                   \
+    hipLaunchKernelGGL(k_group_resid<KX>, dim3(blocks, count), dim3(256), 0, st, g, n, P, inv_h2, ytiles, zc, ntiles)
+    if (kx == 0) MG_GR(0);
+    else if (kx <= 1) MG_GR(1);
+    else if (kx <= 2) MG_GR(2);
+    else if (kx <= 4) MG_GR(4);
+    else if (kx <= 8) MG_GR(8);
+    else MG_GR(16);
+#undef MG_GR
+    return hipGetLastError();
+}
+
+hipError_t launch_group_flush(int prec, const GroupFlush &g, int count, hipStream_t st) {
+    if (count < 1 || count > kGroup) return hipErrorInvalidValue;
+    size_t n8 = 1;
+    for (int i = 0; i < count; ++i) n8 = std::max(n8, g.n8[i]);
+    const unsigned blocks = (unsigned)std::min<size_t>((n8 + 255) / 256, 8192);
+    switch (prec) {
+    case P_F64: hipLaunchKernelGGL(k_group_flush<double>, dim3(blocks, count), dim3(256), 0, st, g); break;
+    case P_F32: hipLaunchKernelGGL(k_group_flush<float>, dim3(blocks, count), dim3(256), 0, st, g); break;
+    case P_F16: hipLaunchKernelGGL(k_group_flush<f16>, dim3(blocks, count), dim3(256), 0, st, g); break;
+    case P_BF16: hipLaunchKernelGGL(k_group_flush<bf16>, dim3(blocks, count), dim3(256), 0, st, g); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_finalize(const double *part, int nparts, double *scal, int scaling, hipStream_t st, int *ctr,
                            double *host) {
     const int threads = std::min(1024, (nparts + 63) / 64 * 64);
@@ -2093,11 +2173,7 @@ __global__ void k_batched_coarse(const BDesc *__restrict__ descs, int n, const i
 }
 
 // One block per instance: reduce its partials into its scalars.
-__global__ __launch_bounds__(1024) void k_batched_finalize(const BFin *__restrict__ fin,
-                                                           const int *__restrict__ active, double *host) {
-    __shared__ double red[32];
-    if (!active[blockIdx.x]) return;
-    const BFin f = fin[blockIdx.x];
+__device__ __forceinline__ void batched_finalize_body(const BFin &f, int inst, double *host, double *red) {
     double s = 0.0, m = 0.0;
     for (int i = threadIdx.x; i < f.count; i += blockDim.x) {
         const double2 v = reinterpret_cast<const double2 *>(f.part)[i];
@@ -2111,11 +2187,28 @@ __global__ __launch_bounds__(1024) void k_batched_finalize(const BFin *__restric
         const double v[4] = {a, 1.0 / a, sqrt(s), m};
         for (int j = 0; j < 4; ++j) {
             f.scal[j] = v[j];
-            if (host) host[4 * blockIdx.x + j] = v[j];
+            if (host) host[4 * inst + j] = v[j];
         }
         if (host) __threadfence_system();
         if (f.ctr) *f.ctr = (*f.ctr + 1) % f.slots;
     }
+}
+
+__global__ __launch_bounds__(1024) void k_batched_finalize(const BFin *__restrict__ fin,
+                                                           const int *__restrict__ active, double *host) {
+    __shared__ double red[32];
+    if (!active[blockIdx.x]) return;
+    const BFin f = fin[blockIdx.x];
+    batched_finalize_body(f, blockIdx.x, host, red);
+}
+
+// The instances first + j of the bits j set in `mask`.
+__global__ __launch_bounds__(1024) void k_group_finalize(const BFin *__restrict__ fin, int first,
+                                                         unsigned long long mask, double *host) {
+    __shared__ double red[32];
+    if (!((mask >> blockIdx.x) & 1)) return;
+    const BFin f = fin[first + blockIdx.x];
+    batched_finalize_body(f, first + blockIdx.x, host, red);
 }
 
 // LDS-plane forms: the same per-tile bodies as k_march and k_restrict2.
@@ -2375,6 +2468,13 @@ hipError_t launch_batched_restrict2(int V, int pf, int pc, bool xsh, const BDesc
 
 hipError_t launch_batched_finalize(const BFin *fin, int ninst, const int *active, double *host, hipStream_t st) {
     hipLaunchKernelGGL(k_batched_finalize, dim3(ninst), dim3(1024), 0, st, fin, active, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_group_finalize(const BFin *fin, int first, int count, unsigned long long mask, double *host,
+                                 hipStream_t st) {
+    if (count < 1 || count > 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_group_finalize, dim3(count), dim3(1024), 0, st, fin, first, mask, host);
     return hipGetLastError();
 }
 

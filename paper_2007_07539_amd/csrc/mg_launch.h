@@ -310,46 +310,53 @@ hipError_t launch_batched_sweep_update(int pf, bool defer, const BDesc *d, const
                                        const int *active, double omega, double *part, int grid, int threads,
                                        size_t lds, hipStream_t st);
 
-// ---- many right-hand sides, interleaved [z][y][x][k] -------------------------
-// Arguments of one interleaved stage launch (unused members may stay null).
-struct MArgs {
-    int prec = 0;        // level storage format
-    int pc = 0;          // coarse format (prolongation: of ec; restriction: of cout)
-    int P = 0, K = 0;    // pitch of the level, number of right-hand sides
-    int zc = 1;          // planes per thread (restriction: coarse planes)
-    const void *b = nullptr;       // right-hand side (level format, or FP64 residual when aliased)
-    const double *r = nullptr;     // scaled first smoothing: FP64 residual
-    const double *inv = nullptr;   // 1/alpha_k (K values)
-    const int *act = nullptr;      // per-column flags (K values)
-    void *bout = nullptr;          // scaled first smoothing: round(r/alpha) out
-    const void *cin = nullptr;     // input correction
-    const void *ec = nullptr;      // coarse correction (prolongation)
-    void *cout = nullptr;          // output correction, or coarse right-hand side (restriction)
-    double omega = 0.8;
+// ---- groups of grids in one launch (start and end of a batched solve) ---------
+// Per-grid pointers passed by value, so that the caller's arrays need no copy
+// to the device.
+constexpr int kGroup = 32;
+struct GroupResid {
+    const double *b[kGroup];
+    const double *U[kGroup];
+    double *R[kGroup];
+    double *uout[kGroup];  // null: u is not copied out
+    double *part[kGroup];
 };
-enum { MS_SMOOTH2 = 0, MS_SWEEP = 1 };
+// r = b - A U (use_u) or r = b on `count` grids of n^3 points; flat_blocks(n^3)
+// norm partials each.
+hipError_t launch_group_resid(const GroupResid &g, int count, int n, int P, double inv_h2, bool use_u, hipStream_t st);
+// u += the postponed corrections (zero: from u = 0; then a count of 0 stores zeros).
+struct GroupFlush {
+    const void *cd[kGroup];
+    const double *adef[kGroup];
+    double *U[kGroup];
+    int *ctr[kGroup];  // null: none
+    size_t cstride[kGroup], n8[kGroup];
+    double h2[kGroup];
+    int count[kGroup], zero[kGroup];
+};
+hipError_t launch_group_flush(int prec, const GroupFlush &g, int count, hipStream_t st);
+hipError_t launch_group_finalize(const BFin *fin, int first, int count, unsigned long long mask, double *host,
+                                 hipStream_t st);
 
-int m_vec(int prec);
-bool m_supported(int prec, int K);
-int m_stencil_blocks(int prec, int P, int K, int zc);
-int m_update_blocks(int prec, int P, int K, int zc);  // workgroups (and partials) of the update
-int m_resid_blocks(int n);
-hipError_t launch_m_stage(int kind, const MArgs &a, hipStream_t st);
-hipError_t launch_m_update(const MArgs &a, double *R, double *U, const double *alpha, double h2, double *part,
-                           hipStream_t st);
-hipError_t launch_m_coarse(int prec, int K, const void *b, void *c, hipStream_t st);
-hipError_t launch_m_resid(int n, int P, int K, const double *b, const double *U, double *R, double *uout,
-                          const int *mask, double inv_h2, double *part, hipStream_t st);
-hipError_t launch_m_pack(int n, int P, int K, const double *src, double *dst, const int *keep, hipStream_t st);
-hipError_t launch_m_finalize(const double *part, int nparts, int K, double *scal, const int *mask, int scaling,
-                             hipStream_t st);
-// Two-pass restriction: the fine residual (accumulator type, m_resid_bytes
-// for a level of `elems` values) into rbuf, then full weighting into a.cout.
-size_t m_resid_bytes(int prec, size_t elems);
-hipError_t launch_m_restrict2(const MArgs &a, void *rbuf, int zcc, hipStream_t st);
-// c = round(c + 4 P e) in place on a.cin (then a plain sweep completes the
-// prolongation stage).
-hipError_t launch_m_prolong_field(const MArgs &a, hipStream_t st);
+// ---- many right-hand sides, interleaved [z][y][x][k] (mg_multi.hip) -----------
+// The right-hand sides are split into K padded grids (grid k of U and R at
+// k * stride) on the way in and joined on the way out.
+struct ColumnsArgs {
+    int n = 0, K = 0;
+    const double *src = nullptr;  // interleaved: b, or the initial guess
+    const double *U = nullptr;    // grids; null: r = src
+    double *R = nullptr;          // grids; null: not stored
+    double *out = nullptr;        // interleaved u, every column; null: not stored
+    size_t stride = 0;            // doubles between the grids of two columns
+    unsigned long long mask = 0;  // columns whose r (and norm partials) is formed
+    double inv_h2 = 0.0;
+    double *part = nullptr;       // column k's partials at part + k * pstride
+    size_t pstride = 0;
+};
+int columns_blocks(int n, int K);  // workgroups, and norm partials per column
+hipError_t launch_columns(const ColumnsArgs &a, hipStream_t st);
+// Fewest columns of a level in format prec (at most 64, a power of two).
+bool columns_ok(int prec, int K);
 
 // ---- the V-cycle on a caller-given scratch array (host side, mg_api.cpp) -----
 // Bytes the V-cycle of a single-grid handle touches (its level vectors and

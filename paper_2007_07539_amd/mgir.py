@@ -466,8 +466,7 @@ class MultiSolver:
         return Solver.profile_step(self, stream, cap)
 
     def get_shape(self, level: int, kind: int, count: int | None = None):
-        """Level's shape (see Solver.get_shape; zc, and zcc of the restriction,
-        are the values that shape these kernels)."""
+        """Level's shape (see Solver.get_shape), the same for every right-hand side."""
         return Solver.get_shape(self, level, kind, count)
 
 

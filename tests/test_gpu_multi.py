@@ -184,3 +184,34 @@ def test_multi_autotuned_bitwise_and_cached(dev, tmp_path, monkeypatch, name):
         assert rt[j].history == rp[j].history == ra[j].history, j
     assert torch.equal(ut, up) and torch.equal(ut, ua)
     assert max(r.rel_residual for r in rt) <= 1e-10
+
+
+@pytest.mark.parametrize("n,k,name", [(3, 4, "f64"), (7, 4, "f64"), (3, 64, "f16"), (63, 8, "f32"), (127, 64, "f16")])
+def test_multi_split_and_join_edges(dev, n, k, name):
+    """Splitting and joining the columns at the edges of its row segments (4096 / k points): from a
+    guess, with a zero column, a smooth column that stops before the others and one that starts from
+    its solution; and with the solution written over the right-hand sides.  Every iterate is the
+    single-grid one bit for bit; residual norms are sums of the same values in another order, n^3
+    terms apart by at most n^3 eps, far below 1e-9."""
+    print(f"multi split/join {name} n={n} k={k}", flush=True)
+    prec = W.precision_map(name, W.levels_for(n))
+    kw = dict(residual_scaling=name != "f64", use_initial_guess=True, max_iter=4, rtol=1e-4)
+    b = torch.from_numpy(_rhs(n, k, 350 + n, emax=2.0)).to(dev)
+    x = torch.sin(torch.pi * torch.arange(1, n + 1, device=dev, dtype=torch.float64) / (n + 1))
+    b[..., 1] = 0.0
+    b[..., 2] = x[:, None, None] * x[:, None] * x
+    g = torch.from_numpy(_rhs(n, k, 360 + n)).to(dev) * 1e-3
+    g[..., 3] = mgir.Solver(3, n, prec, residual_scaling=kw["residual_scaling"]).solve(b[..., 3].contiguous())[0]
+    ms = mgir.MultiSolver(n, k, prec, **kw)
+    u, res, _ = ms.solve(b, g.clone(), check=False)
+    assert res[3].iterations == 0 and not u[..., 1].any()
+    for j in (0, 2, 3, k // 2 + 1, k - 1):
+        u1, r1 = mgir.Solver(3, n, prec, **kw).solve(b[..., j].contiguous(), g[..., j].contiguous(), check=False)
+        assert r1.iterations == res[j].iterations, j
+        assert torch.equal(u[..., j].contiguous(), u1), j
+        assert abs(res[j].rel_residual - r1.rel_residual) <= 1e-9 * r1.rel_residual, j
+    ms = mgir.MultiSolver(n, k, prec, **dict(kw, use_initial_guess=False))
+    u, res, _ = ms.solve(b, check=False)
+    over = b.clone()
+    ms.solve(over, over, check=False)
+    assert torch.equal(over, u)
