@@ -572,12 +572,11 @@ hipError_t enq_vcycle_down(mg_ctx *h, hipStream_t st, RhsMode mode, int l, const
         h->cur[0] = 0;
         return hipSuccess;
     }
-    if (l == 0 && mode == RHS_ALIAS_R && h->fused_sr) {
+    if (l == 0 && (mode == RHS_ALIAS_R || mode == RHS_B) && h->fused_sr) {
         LevelPlan &L = h->lv[0], &C = h->lv[1];
         const double N = (double)points(h->dim, L.n);
-        RUN(h, st, "smooth_restrict", 0, N * 16 + (double)points(h->dim, C.n) * sb(C.prec),
-            launch_smooth_restrict_b(P_F64, C.prec, L.P, Rbuf(h), cbuf(h, 0, 0), bbuf(h, 1), h->opt.omega, h->srsh,
-                                     st));
+        RUN(h, st, "smooth_restrict", 0, N * 2 * sb(L.prec) + (double)points(h->dim, C.n) * sb(C.prec),
+            launch_smooth_restrict_b(L.prec, C.prec, L.P, rhs, cbuf(h, 0, 0), bbuf(h, 1), h->opt.omega, h->srsh, st));
         h->cur[0] = 0;
         return hipSuccess;
     }

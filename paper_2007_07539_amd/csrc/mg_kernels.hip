@@ -1497,27 +1497,48 @@ template <class T> __global__ __launch_bounds__(256) void k_group_flush(const Gr
                         g.n8[i], g.ctr[i], g.zero[i]);
 }
 
-template <int D, class TS, class TD>
-__global__ __launch_bounds__(256) void k_pack(const TS *__restrict__ src, TD *__restrict__ dst, int n, int P, long N) {
-    const Grid<D> g{P};
-    for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += (long)gridDim.x * blockDim.x) {
-        const int x = (int)(idx % n) + 1;
-        const long rest = idx / n;
-        const int y = D == 3 ? (int)(rest % n) + 1 : 0;
-        const int z = D == 3 ? (int)(rest / n) + 1 : (int)rest + 1;
-        dst[g.at(x, y, z)] = Store<TD>::from_f64((double)widen(src[idx]));
-    }
-}
+// Dense <-> padded copies, converting.  One thread moves PV consecutive points
+// of a row with one load and one store (16 bytes of a 2-byte format; neither side
+// is aligned: dense rows have odd lengths, padded ones start at x = 1); the last
+// thread of a row overlaps the one before it instead of moving single points.
+// Rows shorter than PV: one point per thread (PV = 1).  Bound by memory: 255^3 in
+// FP16 36 us with one point per thread, 12 with eight (67 MB).
+template <int N, class T> struct UnalignedRow {
+    typedef T vec __attribute__((ext_vector_type(N), aligned(alignof(T))));
+};
+template <class T> struct RawOf { typedef T type; };
+template <> struct RawOf<f16> { typedef unsigned short type; };
+template <> struct RawOf<bf16> { typedef unsigned short type; };
 
-template <int D, class TS, class TD>
-__global__ __launch_bounds__(256) void k_unpack(const TS *__restrict__ src, TD *__restrict__ dst, int n, int P, long N) {
-    const Grid<D> g{P};
-    for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += (long)gridDim.x * blockDim.x) {
-        const int x = (int)(idx % n) + 1;
-        const long rest = idx / n;
-        const int y = D == 3 ? (int)(rest % n) + 1 : 0;
-        const int z = D == 3 ? (int)(rest / n) + 1 : (int)rest + 1;
-        dst[idx] = Store<TD>::from_f64((double)widen(src[g.at(x, y, z)]));
+template <class TS, class TD, int PV, bool UNPACK>
+__global__ __launch_bounds__(256) void k_pack(const TS *__restrict__ src, TD *__restrict__ dst, int n, int P,
+                                              int rows, int per, int D) {
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int row = (int)(t / per), c = (int)(t % per);
+    if (row >= rows) return;
+    const int x = min(c * PV, n - PV);
+    const size_t dense = (size_t)row * n + x;
+    const size_t padded = (D == 3 ? ((size_t)(row / n + 1) * P + row % n + 1) : (size_t)(row + 1)) * P + 1 + x;
+    const TS *s = src + (UNPACK ? padded : dense);
+    TD *d = dst + (UNPACK ? dense : padded);
+    if constexpr (PV == 1) {
+        *d = Store<TD>::from_f64((double)widen(*s));
+    } else {
+        typedef typename RawOf<TS>::type RS;
+        typedef typename RawOf<TD>::type RD;
+        typename UnalignedRow<PV, RS>::vec v = *reinterpret_cast<const typename UnalignedRow<PV, RS>::vec *>(s);
+        typename UnalignedRow<PV, RD>::vec o;
+#pragma unroll
+        for (int i = 0; i < PV; ++i) {
+            if constexpr (std::is_same<TS, TD>::value) {
+                o[i] = v[i];
+            } else {
+                const RS e = v[i];
+                const TD q = Store<TD>::from_f64((double)widen(__builtin_bit_cast(TS, e)));
+                o[i] = __builtin_bit_cast(RD, q);
+            }
+        }
+        *reinterpret_cast<typename UnalignedRow<PV, RD>::vec *>(d) = o;
     }
 }
 
@@ -2019,17 +2040,22 @@ hipError_t launch_finalize(const double *part, int nparts, double *scal, int sca
 
 template <class TS, class TD>
 static hipError_t pack_t(int D, bool unpack, int n, int P, const void *src, void *dst, hipStream_t st) {
-    const long N = D == 3 ? (long)n * n * n : (long)n * n;
-    const int blocks = flat_blocks(N);
+    // (16 bytes of the wider type, at most eight points)
+    constexpr int PV = 16 / (sizeof(TS) > sizeof(TD) ? sizeof(TS) : sizeof(TD));
     const TS *s = static_cast<const TS *>(src);
     TD *d = static_cast<TD *>(dst);
-    if (D == 3) {
-        if (unpack) hipLaunchKernelGGL((k_unpack<3, TS, TD>), dim3(blocks), dim3(256), 0, st, s, d, n, P, N);
-        else hipLaunchKernelGGL((k_pack<3, TS, TD>), dim3(blocks), dim3(256), 0, st, s, d, n, P, N);
+    const int rows = D == 3 ? n * n : n;
+    const int v = n >= PV ? PV : 1, per = (n + v - 1) / v;
+    const unsigned blocks = (unsigned)(((long)rows * per + 255) / 256);
+#define MG_PK(V, U) hipLaunchKernelGGL((k_pack<TS, TD, V, U>), dim3(blocks), dim3(256), 0, st, s, d, n, P, rows, per, D)
+    if (v == 1) {
+        if (unpack) MG_PK(1, true);
+        else MG_PK(1, false);
     } else {
-        if (unpack) hipLaunchKernelGGL((k_unpack<2, TS, TD>), dim3(blocks), dim3(256), 0, st, s, d, n, P, N);
-        else hipLaunchKernelGGL((k_pack<2, TS, TD>), dim3(blocks), dim3(256), 0, st, s, d, n, P, N);
+        if (unpack) MG_PK(PV, true);
+        else MG_PK(PV, false);
     }
+#undef MG_PK
     return hipGetLastError();
 }
 
