@@ -277,6 +277,10 @@ template <int D> struct Grid {
     __device__ __forceinline__ size_t at(int x, int y, int z) const {
         return D == 3 ? ((size_t)z * P + (size_t)y) * P + (size_t)x : (size_t)z * P + (size_t)x;
     }
+    // at() in two parts: a plane's start (from a plane index the whole wave shares,
+    // on the scalar unit) and the 32-bit offset within it (3-D)
+    __device__ __forceinline__ size_t plane(int z) const { return (size_t)(unsigned)z * (unsigned)(P * P); }
+    __device__ __forceinline__ unsigned in_plane(int x, int y) const { return (unsigned)(y * P + x); }
     // true for rows that lie on the boundary or outside the interior
     __device__ __forceinline__ bool ghost_row(int y, int z) const {
         return z <= 0 || z >= P || (D == 3 && (y <= 0 || y >= P));

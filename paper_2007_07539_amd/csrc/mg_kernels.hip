@@ -406,6 +406,14 @@ __global__ __launch_bounds__(256) void k_stencil(F f, E e, int P, int zc, int nc
 // iteration ahead ("fetch" into raw registers, "value" converts), so they are
 // in flight across the barrier and the arithmetic.
 //
+// Bound by instruction issue in the 2-byte formats, so addresses are a plane's
+// start (scalar) plus a 32-bit offset kept per thread, ghost rows are read as the
+// zeros they hold instead of branched around, and the three planes change roles
+// instead of registers: 142 vector and 47 scalar instructions per eight points
+// of an FP16 sweep (178 and 54 with copies and branches), 223 and 80 for the
+// prolongation (301 and 172).  Prolongation + sweep in FP16: 255^3 33 us -> 23,
+// 127^3 x 32 124 -> 89 (4.6 TB/s).
+//
 // Policies (templated on V): a field provides Raw, fetch(), value() and the
 // LDS storage type lds_t (field values are exactly representable in it); an
 // emit provides Raw (per-row inputs of the output), fetch(), emit(), finish().
@@ -418,11 +426,7 @@ template <class T, class A, int V> struct PArr {
     typedef RawRow<T, V> Raw;
     const T *__restrict__ p;
     __device__ __forceinline__ void fetch(const Grid<3> &g, int x0, int y, int z, Raw &r) const {
-        if (g.ghost_row(y, z)) {
-            zero_row(r);
-            return;
-        }
-        fetch_row<T, V>(p + g.at(x0, y, z), r);
+        fetch_row<T, V>(p + g.plane(z) + g.in_plane(x0, y), r);
     }
     __device__ __forceinline__ void value(const Raw &r, int, int, int, A (&o)[V], A (&)[V]) const {
         widen_row<T, V>(r, o);
@@ -440,11 +444,7 @@ template <class T, int V> struct PJac0Arr {
     const T *__restrict__ b;
     acc k;
     __device__ __forceinline__ void fetch(const Grid<3> &g, int x0, int y, int z, Raw &r) const {
-        if (g.ghost_row(y, z)) {
-            zero_row(r);
-            return;
-        }
-        fetch_row<T, V>(b + g.at(x0, y, z), r);
+        fetch_row<T, V>(b + g.plane(z) + g.in_plane(x0, y), r);
     }
     __device__ __forceinline__ void value(const Raw &r, int, int, int, acc (&o)[V], acc (&aux)[V]) const {
         widen_row<T, V>(r, aux);
@@ -469,7 +469,7 @@ template <class T, int V> struct PJac0Scaled {
             zero_row(rr);
             return;
         }
-        fetch_row<double, V>(r + g.at(x0, y, z), rr);
+        fetch_row<double, V>(r + g.plane(z) + g.in_plane(x0, y), rr);
     }
     __device__ __forceinline__ void value(const Raw &rr, int, int, int, acc (&o)[V], acc (&aux)[V]) const {
         const double inv = scal[1];
@@ -487,6 +487,9 @@ template <class T, int V> struct PJac0Scaled {
 };
 
 // Corrected correction round_TF(c + 4 P e_c); same arithmetic as FProl::row.
+// Values are formed plane by plane in order, so the widened coarse rows of the
+// last two coarse planes stay in registers (w): a coarse plane is read once for
+// the two or three fine planes that use it, ahead of the odd one.
 template <class TF, class TC, int V> struct PProl {
     typedef acc_t<TF> acc;
     typedef TF lds_t;
@@ -494,81 +497,90 @@ template <class TF, class TC, int V> struct PProl {
     static constexpr int H = V / 2;
     struct Raw {
         RawRow<TF, V> c;
-        RawRow<TC, H> seg[4];  // coarse row (Z_a, Y_b) at a * 2 + b
-        TC last[4];
+        RawRow<TC, H> seg[2];  // coarse rows Y_b of plane (z + 1) / 2 (z odd)
+        TC last[2];
     };
     const TF *__restrict__ c;
     const TC *__restrict__ ec;
     int Pc;
-    // Coarse rows (Z_a, Y_b) for a < nz, b < ny; a row on a ghost plane or
-    // ghost row is fetched as zeros (it adds nothing to the sums).
-    __device__ __forceinline__ void fetch(const Grid<3> &g, int x0, int y, int z, Raw &r) const {
-        if (g.ghost_row(y, z)) {  // all zeros: the row's value is zero
-            zero_row(r.c);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) zero_row(r.seg[k]), r.last[k] = zero_of<TC>();
-            return;
+    PA w[2][2][H + 1];  // coarse rows b, planes floor(z / 2) and (z odd) the next
+    unsigned at0, at1;  // coarse rows Y_0 and (y odd) Y_1 at X0, within a plane
+    bool two;           // y odd: two coarse rows
+    // Coarse plane Z (ghost planes, rows and columns hold zeros).
+    __device__ __forceinline__ void fetch_coarse(int Z, Raw &r) const {
+        const TC *base = ec + Grid<3>{Pc}.plane(Z);
+        fetch_row<TC, H>(base + at0, r.seg[0]);
+        r.last[0] = base[at0 + H];
+        if (two) {
+            fetch_row<TC, H>(base + at1, r.seg[1]);
+            r.last[1] = base[at1 + H];
         }
-        fetch_row<TF, V>(c + g.at(x0, y, z), r.c);
+    }
+    __device__ __forceinline__ void widen_coarse(const Raw &r) {
+#pragma unroll
+        for (int bb = 0; bb < 2; ++bb) {
+            if (bb == 1 && !two) continue;
+            PA u[H];
+            widen_row<TC, H>(r.seg[bb], u);
+#pragma unroll
+            for (int j = 0; j <= H; ++j) w[bb][0][j] = w[bb][1][j];
+#pragma unroll
+            for (int j = 0; j < H; ++j) w[bb][1][j] = u[j];
+            w[bb][1][H] = (PA)widen(r.last[bb]);
+        }
+    }
+    // before the first value(), of plane z
+    __device__ __forceinline__ void begin(int x0, int y, int z) {
+        two = (y & 1) != 0;
         const Grid<3> gc{Pc};
-        int Zs[2], Ys[2];
-        const int nz = FProl<TF, TC>::split(z, Zs);
-        const int ny = FProl<TF, TC>::split(y, Ys);
-        const int X0 = x0 >> 1;
+        at0 = gc.in_plane(x0 >> 1, y >> 1);
+        at1 = gc.in_plane(x0 >> 1, min((y >> 1) + 1, Pc));
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
+        for (int bb = 0; bb < 2; ++bb)
 #pragma unroll
-            for (int bb = 0; bb < 2; ++bb) {
-                const int idx = a * 2 + bb;
-                if (a < nz && bb < ny) {
-                    if (Zs[a] >= 1 && Zs[a] < Pc && Ys[bb] >= 1 && Ys[bb] < Pc) {
-                        const TC *base = ec + gc.at(X0, Ys[bb], Zs[a]);
-                        fetch_row<TC, H>(base, r.seg[idx]);
-                        r.last[idx] = (X0 + H < Pc) ? base[H] : zero_of<TC>();
-                    } else {
-                        zero_row(r.seg[idx]);
-                        r.last[idx] = zero_of<TC>();
-                    }
-                }
-            }
-        }
+            for (int j = 0; j <= H; ++j) w[bb][0][j] = w[bb][1][j] = PA(0);
+        Raw r;
+        fetch_coarse(z >> 1, r);
+        widen_coarse(r);
+    }
+    __device__ __forceinline__ void fetch(const Grid<3> &g, int x0, int y, int z, Raw &r) const {
+        fetch_row<TF, V>(c + g.plane(z) + g.in_plane(x0, y), r.c);
+        if (z & 1) fetch_coarse((z >> 1) + 1, r);
     }
     // The canonical sums with the weights applied once: S(X) = (e(Z_0, Y_0) +
     // e(Z_1, Y_0)) + (e(Z_0, Y_1) + e(Z_1, Y_1)) over the present terms, then
     // c + 4 w_Z w_Y S at even x and c + 4 w_Z w_Y (S(X) + S(X+1)) / 2 at odd x.
     // nz is the same for the whole block (one plane), ny for a whole row.
-    __device__ __forceinline__ void value(const Raw &r, int x0, int y, int z, acc (&o)[V], acc (&)[V]) const {
-        const int nz = (z & 1) ? 2 : 1;
-        const int ny = (y & 1) ? 2 : 1;
-        PA t[2][H + 1];
+    __device__ __forceinline__ void value(const Raw &r, int x0, int, int z, acc (&o)[V], acc (&)[V]) {
+        PA S[H + 1];
+        const bool odd = (z & 1) != 0;
+        if (odd) {
+            widen_coarse(r);
 #pragma unroll
-        for (int bb = 0; bb < 2; ++bb) {
-            if (bb < ny) {
-                PA u[H];
-                widen_row<TC, H>(r.seg[bb], u);
+            for (int j = 0; j <= H; ++j) S[j] = w[0][0][j] + w[0][1][j];
+            if (two) {
 #pragma unroll
-                for (int j = 0; j < H; ++j) t[bb][j] = u[j];
-                t[bb][H] = (PA)widen(r.last[bb]);
-                if (nz == 2) {
-                    PA v[H];
-                    widen_row<TC, H>(r.seg[2 + bb], v);
+                for (int j = 0; j <= H; ++j) S[j] = S[j] + (w[1][0][j] + w[1][1][j]);
+            }
+        } else {
 #pragma unroll
-                    for (int j = 0; j < H; ++j) t[bb][j] += v[j];
-                    t[bb][H] += (PA)widen(r.last[2 + bb]);
-                }
+            for (int j = 0; j <= H; ++j) S[j] = w[0][1][j];
+            if (two) {
+#pragma unroll
+                for (int j = 0; j <= H; ++j) S[j] = S[j] + w[1][1][j];
             }
         }
-        PA S[H + 1];
-#pragma unroll
-        for (int j = 0; j <= H; ++j) S[j] = ny == 2 ? t[0][j] + t[1][j] : t[0][j];
-        const PA k0 = PA(4) * (nz == 2 ? PA(0.5) : PA(1)) * (ny == 2 ? PA(0.5) : PA(1));
+        const PA k0 = PA(odd ? 2 : 4) * (two ? PA(0.5) : PA(1));
         const PA k1 = PA(0.5) * k0;
         acc cv[V];
         widen_row<TF, V>(r.c, cv);
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const PA q = (i & 1) ? S[i >> 1] + S[(i >> 1) + 1] : S[i >> 1];
-            o[i] = round_to<TF>((PA)cv[i] + ((i & 1) ? k1 : k0) * q);
+            const PA k = (i & 1) ? k1 : k0;
+            // (powers of two: with FP16 coarse values k q is exact, so one fused operation rounds alike)
+            if constexpr (std::is_same<TC, f16>::value) o[i] = round_to<TF>(fmaT<PA>(k, q, (PA)cv[i]));
+            else o[i] = round_to<TF>((PA)cv[i] + k * q);
         }
         if (x0 == 0) o[0] = acc(0);
     }
@@ -655,7 +667,7 @@ template <class TF, class TC, int V> struct PProlS {
             zero_row(r);
             return;
         }
-        fetch_row<TF, V>(c + g.at(x0, y, z), r);
+        fetch_row<TF, V>(c + g.plane(z) + g.in_plane(x0, y), r);
     }
     __device__ __forceinline__ void value(const Raw &r, int x0, int y, int z, acc (&o)[V], acc (&)[V]) const {
         const Grid<3> g{2 * Pc};
@@ -707,7 +719,7 @@ template <class T, int V, bool RHS_AUX, bool WRITE_B> struct PSweep {
     __device__ __forceinline__ void init(State &) const {}
     __device__ __forceinline__ void finish(State &, double *, long) const {}
     __device__ __forceinline__ void fetch(const Grid<3> &g, int x0, int y, int z, Raw &r) const {
-        if constexpr (!RHS_AUX) fetch_row<T, V>(b + g.at(x0, y, z), r);
+        if constexpr (!RHS_AUX) fetch_row<T, V>(b + g.plane(z) + g.in_plane(x0, y), r);
     }
     __device__ __forceinline__ void emit(const Grid<3> &g, State &, int x0, int y, int z, const A (&c)[V],
                                          const A (&nb)[V], const A (&aux)[V], const Raw &r) const {
@@ -721,14 +733,13 @@ template <class T, int V, bool RHS_AUX, bool WRITE_B> struct PSweep {
             o[i] = Store<T>::from_acc(fmaT<A>(k, bi - lc, c[i]));
         }
         if (x0 == 0) o[0] = zero_of<T>();
-        const size_t at = g.at(x0, y, z);
-        store_row<T, V>(out + at, o);
+        store_row<T, V>(out + g.plane(z) + g.in_plane(x0, y), o);
         if constexpr (WRITE_B) {
             T bo[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) bo[i] = Store<T>::from_acc(aux[i]);
             if (x0 == 0) bo[0] = zero_of<T>();
-            store_row<T, V>(bout + at, bo);
+            store_row<T, V>(bout + g.plane(z) + g.in_plane(x0, y), bo);
         }
     }
 };
@@ -749,9 +760,8 @@ template <int V> struct POuter {
     double *__restrict__ part;
     __device__ __forceinline__ void init(State &s) const { s.ss = 0.0, s.mx = 0.0; }
     __device__ __forceinline__ void fetch(const Grid<3> &g, int x0, int y, int z, Raw &r) const {
-        const size_t at = g.at(x0, y, z);
-        fetch_row<double, V>(R + at, r.r);
-        fetch_row<double, V>(U + at, r.u);
+        fetch_row<double, V>(R + g.plane(z) + g.in_plane(x0, y), r.r);
+        fetch_row<double, V>(U + g.plane(z) + g.in_plane(x0, y), r.u);
     }
     __device__ __forceinline__ void emit(const Grid<3> &g, State &st, int x0, int y, int z, const A (&c)[V],
                                          const A (&nb)[V], const A (&)[V], const Raw &rw) const {
@@ -772,9 +782,8 @@ template <int V> struct POuter {
             st.ss += r[i] * r[i];
             st.mx = nanmax(st.mx, fabs(r[i]));
         }
-        const size_t at = g.at(x0, y, z);
-        store_row<double, V>(R + at, r);
-        store_row<double, V>(U + at, u);
+        store_row<double, V>(R + g.plane(z) + g.in_plane(x0, y), r);
+        store_row<double, V>(U + g.plane(z) + g.in_plane(x0, y), u);
     }
     __device__ __forceinline__ void finish(State &s, double *lds, long pidx) const {
         block_reduce(s.ss, s.mx, lds);
@@ -791,6 +800,10 @@ template <class F, class = void> struct StageOf {
 template <class F> struct StageOf<F, typename std::enable_if<F::kStaged>::type> {
     typedef typename F::Stage type;
 };
+
+// Fields that carry state from plane to plane (begin()).
+template <class F, class = void> struct has_begin : std::false_type {};
+template <class F> struct has_begin<F, decltype((void)&F::begin)> : std::true_type {};
 
 // DP: field and emit rows of DP planes ahead are in flight while a plane is
 // computed (the loads for plane z + 1 + DP are issued in iteration z).
@@ -810,16 +823,22 @@ __device__ __forceinline__ void march_body(const F &f_in, const E &e, int P, int
     const int y0 = 1 + yt * TY;
     const int z0 = 1 + zch * zc;
     const int z1 = min(z0 + zc, P);
-    const int xc = threadIdx.x % TXR, gi = threadIdx.x / TXR;
-    const int y = y0 - 1 + gi;
-    const bool out_row = gi >= 1 && gi <= TY && y <= P - 1;
+    const int xc = threadIdx.x % TXR;
+    int gi = threadIdx.x / TXR;
+    // rows of one parity first, so that few waves mix rows with one and with
+    // two coarse rows
+    if constexpr (has_begin<F>::value) gi = gi < (G + 1) / 2 ? 2 * gi : 2 * (gi - (G + 1) / 2) + 1;
+    const bool out_row = gi >= 1 && gi <= TY && y0 - 1 + gi <= P - 1;
+    const int y = min(y0 - 1 + gi, P);  // (rows beyond the grid read its zero ghost row)
     const int x0 = xc * V;
     const size_t slot = (size_t)G * P;
     typename E::State st;
     e.init(st);
     typename F::Raw fr, fq[DP];
     typename E::Raw eq[DP];
-    A cm[V], cc[V], cp[V], ac[V], ap[V];
+    // field values and their aux on three consecutive planes; the roles rotate,
+    // so that none is copied
+    A c0[V], c1[V], c2[V], a0[V], a1[V], a2[V];
     F f = f_in;
     const int nthr = blockDim.x;
     typename StageOf<F>::type S;
@@ -831,14 +850,15 @@ __device__ __forceinline__ void march_body(const F &f_in, const E &e, int P, int
         f.stage_fetch(z0 + 2, threadIdx.x, nthr, S);
         __syncthreads();
     }
+    if constexpr (has_begin<F>::value) f.begin(x0, y, z0 - 1);
     f.fetch(g, x0, y, z0 - 1, fr);
-    f.value(fr, x0, y, z0 - 1, cm, ac);
+    f.value(fr, x0, y, z0 - 1, c0, a0);
     f.fetch(g, x0, y, z0, fr);
-    f.value(fr, x0, y, z0, cc, ac);
+    f.value(fr, x0, y, z0, c1, a1);
     {
         LT t[V];
 #pragma unroll
-        for (int i = 0; i < V; ++i) t[i] = store_as<LT>(cc[i]);
+        for (int i = 0; i < V; ++i) t[i] = store_as<LT>(c1[i]);
         LR::store(lds + (size_t)gi * P, xc, TXR, t);
     }
     // queues: fq[d] holds field plane z + 1 + d, eq[d] the emit rows of plane z + d
@@ -848,7 +868,7 @@ __device__ __forceinline__ void march_body(const F &f_in, const E &e, int P, int
         if (out_row && z0 + d < z1) e.fetch(g, x0, y, z0 + d, eq[d]);
     }
     if constexpr (F::kStaged) __syncthreads();  // prologue reads of the staged slots are done
-    for (int z = z0; z < z1; ++z) {
+    auto step = [&](int z, A(&cm)[V], A(&cc)[V], A(&cp)[V], A(&ac)[V], A(&ap)[V]) {
         const int it = z - z0;
         f.value(fq[0], x0, y, z + 1, cp, ap);
         if constexpr (F::kStaged) {
@@ -884,18 +904,18 @@ __device__ __forceinline__ void march_body(const F &f_in, const E &e, int P, int
             }
             e.emit(g, st, x0, y, z, cc, nb, ac, ecur);
         }
-        {
-            LT t[V];
+        LT t[V];
 #pragma unroll
-            for (int i = 0; i < V; ++i) t[i] = store_as<LT>(cp[i]);
-            LR::store(lds + (size_t)((it + 1) & 1) * slot + (size_t)gi * P, xc, TXR, t);
-        }
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
-            cm[i] = cc[i];
-            cc[i] = cp[i];
-            ac[i] = ap[i];
-        }
+        for (int i = 0; i < V; ++i) t[i] = store_as<LT>(cp[i]);
+        LR::store(lds + (size_t)((it + 1) & 1) * slot + (size_t)gi * P, xc, TXR, t);
+    };
+    for (int z = z0;;) {
+        step(z, c0, c1, c2, a1, a2);
+        if (++z >= z1) break;
+        step(z, c1, c2, c0, a2, a0);
+        if (++z >= z1) break;
+        step(z, c2, c0, c1, a0, a1);
+        if (++z >= z1) break;
     }
     e.finish(st, red, pidx);
 }
@@ -1090,8 +1110,8 @@ __device__ __forceinline__ void restrict2_body(const TF *__restrict__ b, const T
     const int Z1 = min(Z0 + zcc, Pc);
     const int tid = threadIdx.x;
     const int xc = tid % TXR, gi = tid / TXR;
-    const int y = 2 * Y0 - 2 + gi;
-    const bool res_row = gi >= 1 && gi <= G - 2 && y <= P - 1;
+    const bool res_row = gi >= 1 && gi <= G - 2 && 2 * Y0 - 2 + gi <= P - 1;
+    const int y = min(2 * Y0 - 2 + gi, P);  // (rows beyond the grid read its zero ghost row)
     const int x0 = xc * V;
     const bool coarse = gi < tyc && Y0 + gi < Pc;
     const int Yc = Y0 + gi;
@@ -1119,7 +1139,7 @@ __device__ __forceinline__ void restrict2_body(const TF *__restrict__ b, const T
 #pragma unroll
     for (int d = 0; d < DP; ++d) {
         if (zf0 + 1 + d <= zf1 + 1) f.fetch(g, x0, y, zf0 + 1 + d, fq[d]);
-        if (res_row && zf0 + d <= zf1) fetch_row<TF, V>(b + g.at(x0, y, zf0 + d), bq[d]);
+        if (res_row && zf0 + d <= zf1) fetch_row<TF, V>(b + g.plane(zf0 + d) + g.in_plane(x0, y), bq[d]);
     }
 
     // coarse step: fold the residual rows of fine plane zf (in slot s) into acc
@@ -1178,7 +1198,7 @@ __device__ __forceinline__ void restrict2_body(const TF *__restrict__ b, const T
             bq[d] = bq[d + 1];
         }
         if (zf + 1 + DP <= zf1 + 1) f.fetch(g, x0, y, zf + 1 + DP, fq[DP - 1]);
-        if (res_row && zf + DP <= zf1) fetch_row<TF, V>(b + g.at(x0, y, zf + DP), bq[DP - 1]);
+        if (res_row && zf + DP <= zf1) fetch_row<TF, V>(b + g.plane(zf + DP) + g.in_plane(x0, y), bq[DP - 1]);
         __syncthreads();
         if (coarse && it > 0) coarse_step(zf - 1, (it - 1) & 1);
         if (res_row) {
