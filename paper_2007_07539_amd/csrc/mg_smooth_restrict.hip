@@ -36,6 +36,12 @@ template <class T> constexpr int prec_of_t() {
     return sizeof(T) == 8 ? P_F64 : sizeof(T) == 4 ? P_F32 : std::is_same<T, f16>::value ? P_F16 : P_BF16;
 }
 
+// 0.25 (a + c) + 0.5 b: the products with powers of two are exact, so one fused
+// operation rounds as the separate ones.
+template <class A> __device__ __forceinline__ A fw121(A a, A b, A c) {
+    return fmaT<A>(A(0.5), b, A(0.25) * (a + c));
+}
+
 // SCALED: the right-hand side is the scaled-and-cast FP64 residual (the
 // finest level inside a refinement step; b is also written out); otherwise
 // it is the level's stored b (a coarser level, or a V-cycle on its own).
@@ -89,17 +95,12 @@ __device__ __forceinline__ void sr_body(const void *__restrict__ src, double inv
     const bool coarse = gi < tyc && Y0 + gi < Pc;
     const int Yc = Y0 + gi;
     const A k = (A)(omega / 6.0);
-    // offsets of the own row (plane 0) and of plane z, the latter uniform
-    const size_t roff = (size_t)(long)y * P + x0;
-    const size_t PP = (size_t)P * P;
-    auto at = [&](int z) { return (size_t)z * PP + roff; };
-
+    // the own row within a plane; rows and planes outside the interior read the
+    // zero ghost row y = P (or 0) or ghost plane P (or 0)
+    const Grid<3> gf{P};
+    const unsigned roff = gf.in_plane(x0, min(max(y, 0), P));
     auto fetch_r = [&](int z, RawRow<S, V> &rr) {
-        if (!row_in || z < 1 || z > P - 1) {
-            zero_row(rr);
-            return;
-        }
-        fetch_row<S, V>(static_cast<const S *>(src) + at(z), rr);
+        fetch_row<S, V>(static_cast<const S *>(src) + gf.plane(min(max(z, 0), P)) + roff, rr);
     };
     // b of the own row (zero outside the interior), as stored (braw) and
     // widened (bw): round_T(r / alpha), or the stored b itself
@@ -167,7 +168,7 @@ __device__ __forceinline__ void sr_body(const void *__restrict__ src, double inv
 #pragma unroll
                 for (int jj = 0; jj < VC; ++jj) {
                     const A lm = jj > 0 ? r[2 * jj - 1] : left;
-                    xs[oy][jj] = A(0.25) * (lm + r[2 * jj + 1]) + A(0.5) * r[2 * jj];
+                    xs[oy][jj] = fw121<A>(lm, r[2 * jj], r[2 * jj + 1]);
                 }
                 if (xc == 0) xs[oy][0] = A(0);
             }
@@ -180,13 +181,13 @@ __device__ __forceinline__ void sr_body(const void *__restrict__ src, double inv
         for (int jx = 0; jx < VC; ++jx) {
             const int X = X0 + jx;
             A q = A(0);
-            if (X >= 1) q = A(0.25) * (xs[0][jx] + xs[2][jx]) + A(0.5) * xs[1][jx];
+            if (X >= 1) q = fw121<A>(xs[0][jx], xs[1][jx], xs[2][jx]);
             if (j == 0) {
                 acc[jx] = A(0.25) * q;
             } else if (!last_of_z) {
-                acc[jx] += A(0.5) * q;
+                acc[jx] = fmaT<A>(A(0.5), q, acc[jx]);
             } else {
-                out[jx] = store_as<TC>(acc[jx] + A(0.25) * q);
+                out[jx] = store_as<TC>(fmaT<A>(A(0.25), q, acc[jx]));
                 acc[jx] = A(0.25) * q;
             }
         }
@@ -209,7 +210,7 @@ __device__ __forceinline__ void sr_body(const void *__restrict__ src, double inv
         if constexpr (SCALED) {
             if (own_row && own_plane(t + 2)) {
                 if (x0 == 0) braw[0] = zero_of<T>();
-                store_row<T, V>(bout + at(t + 2), braw);
+                store_row<T, V>(bout + gf.plane(t + 2) + roff, braw);
             }
         }
         __syncthreads();
@@ -244,7 +245,7 @@ __device__ __forceinline__ void sr_body(const void *__restrict__ src, double inv
                 for (int i = 0; i < V; ++i) craw[i] = zero_of<T>(), c2[i] = A(0);
             }
             LR::store(c2s + (size_t)(p & 1) * cslot + (size_t)gi * P, xc, TXR, c2);
-            if (own_row && own_plane(p)) store_row<T, V>(cout + at(p), craw);
+            if (own_row && own_plane(p)) store_row<T, V>(cout + gf.plane(p) + roff, craw);
         }
         // residual of plane t on rows gi = 2 .. G-3, x weights in the thread
         if (t >= zf0) {
@@ -283,7 +284,7 @@ __device__ __forceinline__ void sr_body(const void *__restrict__ src, double inv
 #pragma unroll
                 for (int j = 0; j < VC; ++j) {
                     const A lm = j > 0 ? r[2 * j - 1] : left;
-                    xq[j] = A(0.25) * (lm + r[2 * j + 1]) + A(0.5) * r[2 * j];
+                    xq[j] = fw121<A>(lm, r[2 * j], r[2 * j + 1]);
                 }
                 if (x0 == 0) xq[0] = A(0);
                 if (res_slot) LRC::store(rs + (size_t)(t & 1) * rslot + (size_t)(gi - 2) * RW, xc, TXR, xq);
