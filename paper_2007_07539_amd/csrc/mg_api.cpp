@@ -1978,7 +1978,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
         HIPCHK(finest_resid(h, b, nullptr, Rbuf(h), nullptr, st));
         // with postponed updates nothing reads u before the first flush,
         // which then starts from zero (enq_flush)
-        if (h->defer) h->u_zero = true;
+        if (defers(h)) h->u_zero = true;
         else HIPCHK(launch_fill_zero(Ubuf(h), align_up(L.elems * sizeof(double), 16), st));
     }
     const int fparts = flat_blocks(points(D, L.n));
