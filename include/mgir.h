@@ -117,7 +117,9 @@ typedef struct {
                                 the LDS-staged 3-D kernels, see "Q1 handles" under
                                 mg_set_shape); single-grid handles only, as rescale_half. */
     int defer_update;        /* 0 (default): ir_solve adds alpha c to u in every step, as
-                                Algorithm 2 writes it.  k in 1..64: the step's update
+                                Algorithm 2 writes it, except on large grids (2^22 points
+                                and more, FP16/BF16 and 3-D finite-difference FP32 finest
+                                levels), where it is 8.  k in 1..64: the step's update
                                 kernel (3-D finite differences with the fused last
                                 sweep + update, MG_SHAPE_FUSE in use; or the Q1 update,
                                 2-D and 3-D) stores c in the finest level's
@@ -407,7 +409,7 @@ typedef enum {
                                An FP64 finest level without residual scaling, whose
                                right-hand side is r itself, takes only from_r = 1.
                                Default: 1 for FP32/FP64 finest levels and 2-byte ones
-                               of n >= 511 without defer_update, else 0; the
+                               of n >= 511 updating u in every step, else 0; the
                                autotuner times both.  Not used when nu2 < 2.
                                Reading returns whether it is in use and its shape. */
     MG_SHAPE_FUSE_SR = 8    /* 3-D, level l below the base: {on (0|1)[, tyc, zcc[, lds16]]}.  When
