@@ -486,6 +486,11 @@ __global__ __launch_bounds__(kThreads) void k_q1_outer_march(const T *__restrict
 // residual rows go to LDS (two slots), and after the plane's barrier the
 // coarse threads form the x and y sums and carry the z sums in registers, in
 // the order of k_q1_restrict (the same result).
+// Bound by LDS reads and instruction issue: plane addresses are scalar, ghost rows
+// are read as the zeros they hold and the three planes change roles instead of
+// being copied (103 vector instructions per four points of an FP16 sweep, 141 with
+// copies; 191^3 12.5 us, 14.4 with).  Reading a row's x0 - 1 in one access with the
+// four values (12 misaligned bytes) costs more than the separate read: 17.7 us.
 template <class T, int MODE, bool DEFER = false, class TC = T>
 __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const T *__restrict__ c,
                                                  void *__restrict__ out, int n, int P, int TY, int zc, int ytiles,
@@ -509,12 +514,12 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
     const int z0 = 1 + zch * zc, z1 = min(z0 + zc - (FR ? 0 : 1), n);
     const int tx = (int)threadIdx.x % TX, gi = (int)threadIdx.x / TX;
     const int x0 = 4 * tx;
-    const int y = y0 - 1 + gi;
-    const bool row_in = y >= 1 && y <= n;  // other rows are zero ghosts
+    const int y = min(y0 - 1 + gi, n + 1);  // (rows beyond the grid read its zero ghost row)
     const bool outr = gi >= 1 && gi <= TY + (FR ? 1 : 0) && y <= n;
     A pm = A(0), p0 = A(0);  // mode 4: the coarse thread's y/x sums of planes 2Z - 1 and 2Z
     const bool first = x0 == 0;
     const Grid<3> g{P};
+    const unsigned at = g.in_plane(x0, y);
     double ss = 0.0, mx = 0.0;
     T *cd = nullptr;
     double a = 0.0;
@@ -527,10 +532,7 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
         }
     }
     for (int i = threadIdx.x; i < 2 * 8; i += blockDim.x) lds[(i / 8) * slot + (size_t)G * P + (i % 8)] = zero_of<T>();
-    auto fetch = [&](int z, RawRow<T, 4> &r) {
-        if (row_in) fetch_row<T, 4>(c + g.at(x0, y, z), r);
-        else zero_row(r);
-    };
+    auto fetch = [&](int z, RawRow<T, 4> &r) { fetch_row<T, 4>(c + g.plane(z) + at, r); };
     auto publish = [&](int s, const RawRow<T, 4> &r) {
         typedef typename RawRow<T, 4>::C C;
         C *dst = reinterpret_cast<C *>(lds + (size_t)s * slot + (size_t)gi * P + x0);
@@ -555,29 +557,30 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
 #pragma unroll
         for (int k = 0; k < 6; ++k) Av[k] = sv[k] + tv[k];
     };
-    A Am[6], Cm[6], A0[6], C0[6], Ap[6], Cp[6];
+    // rows of planes z - 1, z, z + 1, whose roles rotate, so that none is copied
+    A As[3][6], Cs[3][6];
     RawRow<T, 4> rr;
     fetch(z0 - 1, rr);
     publish(0, rr);
     fetch(z0, rr);
     __syncthreads();
-    if (outr) rows(0, Am, Cm);
+    if (outr) rows(0, As[0], Cs[0]);
     publish(1, rr);
     fetch(z0 + 1, rr);
     __syncthreads();
-    if (outr) rows(1, A0, C0);
+    if (outr) rows(1, As[1], Cs[1]);
     publish(0, rr);  // slot 0's plane z0 - 1 was read before the last barrier
     if (z0 + 2 <= z1 + 1) fetch(z0 + 2, rr);
     constexpr bool READS_B = MODE <= 1 || MODE == 4;
     RawRow<T, 4> bq;
-    if (READS_B && outr) fetch_row<T, 4>(b + g.at(x0, y, z0), bq);
+    if (READS_B && outr) fetch_row<T, 4>(b + g.plane(z0) + at, bq);
     RawRow<double, 4> rq, uq;
     if (MODE == 2 && outr) {
-        fetch_row<double, 4>(R + g.at(x0, y, z0), rq);
-        if (!DEFER) fetch_row<double, 4>(U + g.at(x0, y, z0), uq);
+        fetch_row<double, 4>(R + g.plane(z0) + at, rq);
+        if (!DEFER) fetch_row<double, 4>(U + g.plane(z0) + at, uq);
     }
     __syncthreads();
-    for (int z = z0; z <= z1; ++z) {
+    auto step = [&](int z, const A(&Am)[6], const A(&Cm)[6], const A(&A0)[6], const A(&C0)[6], A(&Ap)[6], A(&Cp)[6]) {
         const int it = z - z0;
         const int sp = it & 1;  // slot of plane z + 1
         RawRow<T, 4> bcur = bq;
@@ -585,13 +588,13 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
         if (outr) {
             rows(sp, Ap, Cp);
             if (z + 1 <= z1) {
-                if (READS_B) fetch_row<T, 4>(b + g.at(x0, y, z + 1), bq);
+                if (READS_B) fetch_row<T, 4>(b + g.plane(z + 1) + at, bq);
                 if (MODE == 2) {
-                    fetch_row<double, 4>(R + g.at(x0, y, z + 1), rq);
-                    if (!DEFER) fetch_row<double, 4>(U + g.at(x0, y, z + 1), uq);
+                    fetch_row<double, 4>(R + g.plane(z + 1) + at, rq);
+                    if (!DEFER) fetch_row<double, 4>(U + g.plane(z + 1) + at, uq);
                 }
             }
-            const size_t o = g.at(x0, y, z);
+            const size_t oz = g.plane(z);
             A sc[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -608,14 +611,14 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     ov[i] = (i == 0 && first) ? zero_of<T>() : Store<T>::from_acc(fmaT<A>(w, bv[i] - sc[i], C0[i + 1]));
-                store_row<T, 4>(static_cast<T *>(out) + o, ov);
+                store_row<T, 4>(static_cast<T *>(out) + oz + at, ov);
             } else if constexpr (MODE == 1 || MODE == 4) {
                 A bv[4];
                 widen_row<T, 4>(bcur, bv);
                 A ov[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) ov[i] = (i == 0 && first) ? A(0) : bv[i] - sc[i];
-                if constexpr (MODE == 1) store_row<A, 4>(static_cast<A *>(out) + o, ov);
+                if constexpr (MODE == 1) store_row<A, 4>(static_cast<A *>(out) + oz + at, ov);
                 else store_row<A, 4>(rbuf + (size_t)(it & 1) * rslot + (size_t)(gi - 1) * P + x0, ov);
             } else if constexpr (MODE == 3) {
                 // dense b and out: point (x, y, z) at ((z-1) n + (y-1)) n + x-1
@@ -625,15 +628,15 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const bool ghost = i == 0 && first;
-                    const size_t at = d + (size_t)(ghost ? 0 : x0 + i - 1);
-                    const double bv = reinterpret_cast<const double *>(b)[at];
+                    const size_t di = d + (size_t)(ghost ? 0 : x0 + i - 1);
+                    const double bv = reinterpret_cast<const double *>(b)[di];
                     const double r = ghost ? 0.0 : bv - f * sc[i];
                     rv[i] = r;
                     ss += r * r;
                     mx = nanmax(mx, fabs(r));
-                    if (out && !ghost) static_cast<double *>(out)[at] = C0[i + 1];
+                    if (out && !ghost) static_cast<double *>(out)[di] = C0[i + 1];
                 }
-                store_row<double, 4>(R + o, rv);
+                store_row<double, 4>(R + oz + at, rv);
             } else {
                 double rv[4], uv[4] = {};
                 widen_row<double, 4>(rcur, rv);
@@ -647,14 +650,14 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
                     ss += r * r;
                     mx = nanmax(mx, fabs(r));
                 }
-                store_row<double, 4>(R + o, rv);
+                store_row<double, 4>(R + oz + at, rv);
                 if constexpr (DEFER) {
                     T cv[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) cv[i] = (i == 0 && first) ? zero_of<T>() : store_as<T>(C0[i + 1]);
-                    store_row<T, 4>(cd + o, cv);
+                    store_row<T, 4>(cd + oz + at, cv);
                 } else {
-                    store_row<double, 4>(U + o, uv);
+                    store_row<double, 4>(U + oz + at, uv);
                 }
             }
         }
@@ -685,11 +688,14 @@ __global__ __launch_bounds__(1024) void k_q1_lds(const T *__restrict__ b, const 
                 }
             }
         }
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            Am[k] = A0[k], Cm[k] = C0[k];
-            A0[k] = Ap[k], C0[k] = Cp[k];
-        }
+    };
+    for (int z = z0; z <= z1;) {
+        step(z, As[0], Cs[0], As[1], Cs[1], As[2], Cs[2]);
+        if (++z > z1) break;
+        step(z, As[1], Cs[1], As[2], Cs[2], As[0], Cs[0]);
+        if (++z > z1) break;
+        step(z, As[2], Cs[2], As[0], Cs[0], As[1], Cs[1]);
+        ++z;
     }
     if constexpr (MODE == 2 || MODE == 3) {
         block_reduce(ss, mx, red);
