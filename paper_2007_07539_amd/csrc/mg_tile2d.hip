@@ -16,11 +16,13 @@
 // The rim of the halo goes stale one ring per stage and is not used after that.
 //
 // What bounds it: launch latency up to about 1000^2 (4.6 us a launch), above
-// that memory for the FP64 streams of the update (2047^2 FP16: down 17.7 us,
-// 51 MB; up with the update 40 us, 152 MB) and FP64 arithmetic with Q1 elements
-// (4095^2 FP16: 66 and 136 us).  Before, the same stages took 39 + 43 us at
-// 2047^2 and 100 + 126 us at 4095^2, and four to seven launches of 3.5-6 us on
-// every smaller level.
+// that memory for the FP64 streams of the update and instruction issue
+// (finest level, down and up with the update: 2047^2 FP16 14 and 34 us for 51 and
+// 152 MB, 4095^2 Q1 FP16 54 and 103 us).  Formats chosen at run time made each
+// load wait for its own conversion (4095^2 Q1: 67 and 138 us), and a segment's
+// neighbours read together with it conflicted in LDS (66 and 124 us).  As separate
+// kernels the same stages took 39 + 43 us at 2047^2 and 100 + 126 us at 4095^2, and
+// four to seven launches of 3.5-6 us on every smaller level.
 //
 // The arithmetic is that of the separate kernels, operation for operation, so
 // results are bitwise theirs (the norms up to their summation order).
@@ -34,6 +36,14 @@ namespace {
 constexpr int kThreads = 1024;
 constexpr int V = 4;
 
+// The level's format is a template parameter: chosen at run time, each load waited
+// for its own conversion before the next one was issued.
+template <int PF> struct AccOf {
+    typedef typename std::conditional<PF == P_F64, double, float>::type type;
+    typedef typename std::conditional<PF == P_F16, f16, typename std::conditional<PF == P_BF16, bf16, type>::type>::type
+        store;
+};
+
 // Tile geometry: SX segments per row (one of halo each side), rows of LS
 // elements in LDS with a segment of padding each side, and a row above and
 // below: every neighbour a thread reads lies in the block's LDS.
@@ -42,6 +52,9 @@ struct Tile {
     int x0, y;       // first point
     bool in;         // inside the grid (x0 = 0 holds the ghost in element 0)
     int at;          // LDS index of the segment
+    int lf, rt;      // ... of its left and right neighbours, opaque to the compiler: it
+                     // would merge them with the segment's 16-byte access into
+                     // misaligned pairs with four-way bank conflicts
 };
 __device__ __forceinline__ Tile tile_of(int TX, int rows, int X0, int Y0, int top, int P, int LS) {
     Tile t;
@@ -52,6 +65,8 @@ __device__ __forceinline__ Tile tile_of(int TX, int rows, int X0, int Y0, int to
     t.y = Y0 - top + t.r;
     t.in = t.r < rows && t.y >= 1 && t.y < P && t.x0 >= 0 && t.x0 < P;
     t.at = (t.r + 1) * LS + V * (t.s + 1);
+    t.lf = t.at - 1, t.rt = t.at + V;
+    asm("" : "+v"(t.lf), "+v"(t.rt));
     return t;
 }
 
@@ -63,7 +78,7 @@ __device__ __forceinline__ void apply2(const A *c, const Tile &t, int LS, const 
         A s[V], n[V];
         load_row<A, V>(p - LS, s);
         load_row<A, V>(p + LS, n);
-        const C xl = (C)p[-1], xr = (C)p[V];
+        const C xl = (C)c[t.lf], xr = (C)c[t.rt];
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             C nb = (i > 0 ? (C)cc[i - 1] : xl) + (i < V - 1 ? (C)cc[i + 1] : xr);
@@ -72,21 +87,21 @@ __device__ __forceinline__ void apply2(const A *c, const Tile &t, int LS, const 
             lc[i] = fmaT<C>(C(4), (C)cc[i], -nb);
         }
     } else {
-        auto row = [&](const A *q, C (&r)[V + 2]) {
+        auto row = [&](int off, C (&r)[V + 2]) {
             A m[V];
-            load_row<A, V>(q, m);
-            r[0] = (C)q[-1];
+            load_row<A, V>(p + off, m);
+            r[0] = (C)c[t.lf + off];
 #pragma unroll
             for (int i = 0; i < V; ++i) r[i + 1] = (C)m[i];
-            r[V + 1] = (C)q[V];
+            r[V + 1] = (C)c[t.rt + off];
         };
         C s[V + 2], n[V + 2], m[V + 2];
-        row(p - LS, s);
-        row(p + LS, n);
-        m[0] = (C)p[-1];
+        row(-LS, s);
+        row(LS, n);
+        m[0] = (C)c[t.lf];
 #pragma unroll
         for (int i = 0; i < V; ++i) m[i + 1] = (C)cc[i];
-        m[V + 1] = (C)p[V];
+        m[V + 1] = (C)c[t.rt];
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const C nb = ((s[i] + s[i + 1]) + (s[i + 2] + m[i])) + ((m[i + 2] + n[i]) + (n[i + 1] + n[i + 2]));
@@ -99,13 +114,15 @@ struct DownK {
     const void *b;
     const double *R, *scal;
     void *bout, *cout, *bc;
-    int P, prec, pc, nu, TX, TY, xtiles;
+    int P, pc, nu, TX, TY, xtiles;
     double k;
 };
 
-template <int OP, class A> __global__ __launch_bounds__(kThreads) void k_tile2d_down(const DownK a) {
+template <int OP, int PF> __global__ __launch_bounds__(kThreads) void k_tile2d_down(const DownK a) {
+    typedef typename AccOf<PF>::type A;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int P = a.P, p = a.prec, top = a.nu + 1, rows = a.TY + top + a.nu, LS = a.TX + 4 * V;
+    constexpr int p = PF;
+    const int P = a.P, top = a.nu + 1, rows = a.TY + top + a.nu, LS = a.TX + 4 * V;
     A *const L0 = reinterpret_cast<A *>(smem), *const L1 = L0 + (rows + 2) * LS;
     const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
     const int yt = blk / a.xtiles, X0 = (blk - yt * a.xtiles) * a.TX, Y0 = yt * a.TY;
@@ -144,8 +161,8 @@ template <int OP, class A> __global__ __launch_bounds__(kThreads) void k_tile2d_
             apply2<OP, A, A>(src, t, LS, c, lc);
 #pragma unroll
             for (int i = 0; i < V; ++i) {
-                const A r = b[i] - lc[i];
-                v[i] = !t.in ? A(0) : res ? r : rnd(fmaT<A>(k, r, c[i]), p);
+                const A r = b[i] - lc[i], w = rnd(fmaT<A>(k, r, c[i]), p);  // (both: no branch per value)
+                v[i] = !t.in ? A(0) : res ? r : w;
             }
             if (t.x0 == 0) v[0] = A(0);
             if (res && own) mem_store<A, V>(a.cout, o, p, c);
@@ -157,12 +174,12 @@ template <int OP, class A> __global__ __launch_bounds__(kThreads) void k_tile2d_
     }
     // full weighting: the threads of the even rows form two coarse values each
     if (own && (t.y & 1) == 0 && t.y >= 2) {
-        const A *q = ((a.nu & 1) ? L1 : L0) + t.at;
+        const A *q = (a.nu & 1) ? L1 : L0;
         constexpr int H = V / 2;
-        auto row = [&](const A *e, A (&w)[H]) {
+        auto row = [&](int off, A (&w)[H]) {
             A m[V];
-            load_row<A, V>(e, m);
-            A left = e[-1];
+            load_row<A, V>(q + t.at + off, m);
+            A left = q[t.lf + off];
 #pragma unroll
             for (int j = 0; j < H; ++j) {
                 if (OP == 0) w[j] = A(0.25) * (left + m[2 * j + 1]) + A(0.5) * m[2 * j];
@@ -171,9 +188,9 @@ template <int OP, class A> __global__ __launch_bounds__(kThreads) void k_tile2d_
             }
         };
         A u[H], m[H], d[H], v[H];
-        row(q - LS, u);
-        row(q, m);
-        row(q + LS, d);
+        row(-LS, u);
+        row(0, m);
+        row(LS, d);
 #pragma unroll
         for (int j = 0; j < H; ++j) {
             if (OP == 0) {
@@ -200,35 +217,19 @@ struct UpK {
     size_t cstride;
     double *adef, *part;
     double k, f;
-    int P, prec, pc, nu, TX, TY, xtiles;
+    int P, pc, nu, TX, TY, xtiles;
 };
 
-// c + 4 P e of a segment, in W, rounded into format p.
+// c + 4 P e of a segment, in W, rounded into format p; S, a: coarse rows
+// floor(y / 2) and ceil(y / 2) from x0 / 2.
 template <int OP, class A, class W>
-__device__ __forceinline__ void prolong2(const void *ec, int pc, const Tile &t, int Pc, const A (&c)[V], int p,
-                                         A (&out)[V]) {
+__device__ __forceinline__ void prolong2(W (&S)[V / 2 + 1], const W (&a)[V / 2 + 1], const Tile &t, const A (&c)[V],
+                                         int p, A (&out)[V]) {
     constexpr int H = V / 2;
-    const int X0 = t.x0 >> 1;
-    auto crow = [&](int Z, W (&v)[H + 1]) {
-        const size_t q = (size_t)Z * Pc + X0;
-        W two[H], last[1];
-        mem_load<W, H>(ec, q, pc, two);
-        mem_load<W, 1>(ec, q + H, pc, last);  // beyond the row: the next row's zero ghost
-#pragma unroll
-        for (int j = 0; j < H; ++j) v[j] = two[j];
-        v[H] = last[0];
-    };
-    W S[H + 1], a[H + 1];
     const bool odd = t.y & 1;
-    crow(t.y >> 1, S);
-    if (odd) crow((t.y + 1) >> 1, a);
-    else
-#pragma unroll
-        for (int j = 0; j <= H; ++j) a[j] = S[j];
     if constexpr (OP == 0) {
-        if (odd)
 #pragma unroll
-            for (int j = 0; j <= H; ++j) S[j] = S[j] + a[j];
+        for (int j = 0; j <= H; ++j) S[j] = odd ? S[j] + a[j] : S[j];
         const W k0 = odd ? W(2) : W(4), k1 = W(0.5) * k0;
 #pragma unroll
         for (int i = 0; i < V; ++i) {
@@ -244,10 +245,32 @@ __device__ __forceinline__ void prolong2(const void *ec, int pc, const Tile &t, 
     if (t.x0 == 0) out[0] = A(0);
 }
 
-template <int OP, class A, bool UPD> __global__ __launch_bounds__(kThreads) void k_tile2d_up(const UpK a) {
+// The same from a coarse level in another format than the fine one's.
+template <int OP, class A, class W>
+__device__ __forceinline__ void prolong2_mixed(const void *ec, int pc, const Tile &t, int Pc, const A (&c)[V], int p,
+                                               A (&out)[V]) {
+    constexpr int H = V / 2;
+    auto crow = [&](int Z, W (&v)[H + 1]) {
+        const size_t q = (size_t)Z * Pc + (t.x0 >> 1);
+        W two[H], last[1];
+        mem_load<W, H>(ec, q, pc, two);
+        mem_load<W, 1>(ec, q + H, pc, last);  // beyond the row: the next row's zero ghost
+#pragma unroll
+        for (int j = 0; j < H; ++j) v[j] = two[j];
+        v[H] = last[0];
+    };
+    W S[H + 1], a[H + 1];
+    crow(t.y >> 1, S);
+    crow((t.y + 1) >> 1, a);
+    prolong2<OP, A, W>(S, a, t, c, p, out);
+}
+
+template <int OP, int PF, bool UPD> __global__ __launch_bounds__(kThreads) void k_tile2d_up(const UpK a) {
+    typedef typename AccOf<PF>::type A;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[2 * kThreads / 64];
-    const int P = a.P, p = a.prec, top = a.nu + (UPD ? 1 : 0), rows = a.TY + 2 * top, LS = a.TX + 4 * V;
+    constexpr int p = PF;
+    const int P = a.P, top = a.nu + (UPD ? 1 : 0), rows = a.TY + 2 * top, LS = a.TX + 4 * V;
     A *L0 = reinterpret_cast<A *>(smem), *L1 = L0 + (rows + 2) * LS;
     const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
     const int yt = blk / a.xtiles, X0 = (blk - yt * a.xtiles) * a.TX, Y0 = yt * a.TY;
@@ -261,17 +284,45 @@ template <int OP, class A, bool UPD> __global__ __launch_bounds__(kThreads) void
 #pragma unroll
     for (int i = 0; i < V; ++i) b[i] = c[i] = A(0), r[i] = u[i] = 0.0;
     if (t.in) {
-        A cv[V];
-        mem_load<A, V>(a.c, o, p, cv);
-        mem_load<A, V>(a.b, o, p, b);
+        // every load is issued before the first is waited for
+        constexpr int H = V / 2;
+        typedef typename AccOf<PF>::store T;
+        RawRow<T, H> e0, e1;
+        RawRow<T, V> cr, br;
+        T l0{}, l1{};
+        const bool same = a.pc == PF;
+        if (same) {
+            const T *ec = static_cast<const T *>(a.ec) + (t.x0 >> 1);
+            const T *r0 = ec + (size_t)(t.y >> 1) * (P / 2), *r1 = ec + (size_t)((t.y + 1) >> 1) * (P / 2);
+            fetch_row<T, H>(r0, e0);
+            fetch_row<T, H>(r1, e1);
+            l0 = r0[H], l1 = r1[H];  // beyond the row: the next row's zero ghost
+        }
+        fetch_row<T, V>(static_cast<const T *>(a.c) + o, cr);
+        fetch_row<T, V>(static_cast<const T *>(a.b) + o, br);
         if (UPD && own) {  // in flight during the sweeps
             load_row<double, V>(a.R + o, r);
             if (a.U) load_row<double, V>(a.U + o, u);
         }
-        if (!std::is_same<A, double>::value && a.pc == P_F64)
-            prolong2<OP, A, double>(a.ec, a.pc, t, P / 2, cv, p, c);
-        else
-            prolong2<OP, A, A>(a.ec, a.pc, t, P / 2, cv, p, c);
+        A cv[V];
+        widen_row<T, V>(cr, cv);
+        if (same) {
+            A S[H + 1], n[H + 1], w[H];
+            widen_row<T, H>(e0, w);
+#pragma unroll
+            for (int j = 0; j < H; ++j) S[j] = w[j];
+            S[H] = widen(l0);
+            widen_row<T, H>(e1, w);
+#pragma unroll
+            for (int j = 0; j < H; ++j) n[j] = w[j];
+            n[H] = widen(l1);
+            prolong2<OP, A, A>(S, n, t, cv, p, c);
+        } else if (!std::is_same<A, double>::value && a.pc == P_F64) {
+            prolong2_mixed<OP, A, double>(a.ec, P_F64, t, P / 2, cv, p, c);
+        } else {
+            prolong2_mixed<OP, A, A>(a.ec, a.pc, t, P / 2, cv, p, c);
+        }
+        widen_row<T, V>(br, b);
     }
     if (row_in) store_row<A, V>(L0 + t.at, c);
     __syncthreads();
@@ -280,7 +331,10 @@ template <int OP, class A, bool UPD> __global__ __launch_bounds__(kThreads) void
             A lc[V];
             apply2<OP, A, A>(L0, t, LS, c, lc);
 #pragma unroll
-            for (int i = 0; i < V; ++i) c[i] = t.in ? rnd(fmaT<A>(k, b[i] - lc[i], c[i]), p) : A(0);
+            for (int i = 0; i < V; ++i) {
+                const A w = rnd(fmaT<A>(k, b[i] - lc[i], c[i]), p);
+                c[i] = t.in ? w : A(0);
+            }
             if (t.x0 == 0) c[0] = A(0);
             if (UPD || s + 1 < a.nu) store_row<A, V>(L1 + t.at, c);
         }
@@ -327,22 +381,23 @@ template <int OP, class A, bool UPD> __global__ __launch_bounds__(kThreads) void
 }
 
 // Tile sizes.  Small levels take small tiles, so that there are about as many
-// blocks as CUs; from pitch 512 on 64 by 16, from 4096 on 128 by 16 points
-// (taller tiles of up to 1024 threads do less halo work but measured slower:
-// 4095^2 Q1 FP16 373 us a step at 128 by 24 and 361 at 128 by 16, 2047^2 FP64
-// 158 and 150; two to four blocks per CU overlap their barriers).
+// blocks as CUs; from pitch 512 on 64 by 16, from 2048 on 64 by 20 points
+// (us of the finest level's two kernels at 64 by 16, 64 by 20, 128 by 16: 4095^2
+// Q1 FP16 184, 163, 171; 2047^2 FP16 51.5, 49.6, 53.7, FP64 58.3, 54.8, 61.3;
+// 1023^2 FP16 21.6, -, 20.5.  Several blocks of few waves per CU overlap their
+// barriers; 32 by 32 does less halo work and takes 176 at 4095^2).
 struct Geo {
     int TX, TY, xtiles, blocks, threads;
     size_t lds;
 };
 Geo geo(int P, int halo_rows, size_t sa) {
     Geo g;
-    g.TX = P >= 4096 ? 128 : P >= 512 ? 64 : 32;
+    g.TX = P >= 512 ? 64 : 32;
     const int SX = g.TX / V + 2;
     // rows by threads, and by the 64 KB of LDS of two tiles (FP64)
     const int lds_rows = (int)((65536 - 512) / (2 * (g.TX + 4 * V) * sa)) - 2;
     const int most = (std::min(kThreads / SX, lds_rows) - halo_rows) & ~1;
-    g.TY = std::max(2, std::min(P >= 512 ? 16 : 8, most));
+    g.TY = std::max(2, std::min(P >= 2048 ? 20 : P >= 512 ? 16 : 8, most));
     g.xtiles = (P + g.TX - 1) / g.TX;
     g.blocks = g.xtiles * ((P + g.TY - 1) / g.TY);
     const int rows = g.TY + halo_rows;
@@ -369,10 +424,15 @@ hipError_t launch_tile2d_down(const Tile2dArgs &t, hipStream_t st) {
     const Geo g = geo(t.P, 2 * t.nu + 1, f64 ? 8 : 4);
     DownK a{};
     a.b = t.b, a.R = t.R, a.scal = t.scal, a.bout = t.bout, a.cout = t.cout, a.bc = t.bc;
-    a.P = t.P, a.prec = t.prec, a.pc = t.pc, a.nu = t.nu, a.TX = g.TX, a.TY = g.TY, a.xtiles = g.xtiles;
+    a.P = t.P, a.pc = t.pc, a.nu = t.nu, a.TX = g.TX, a.TY = g.TY, a.xtiles = g.xtiles;
     a.k = t.q1 ? t.omega * 0.375 : t.omega / 4.0;
-    auto fn = t.q1 ? (f64 ? k_tile2d_down<1, double> : k_tile2d_down<1, float>)
-                   : (f64 ? k_tile2d_down<0, double> : k_tile2d_down<0, float>);
+#define MG_DOWN(OP)                                                       \
+    (f64                 ? k_tile2d_down<OP, P_F64>                       \
+     : t.prec == P_F16   ? k_tile2d_down<OP, P_F16>                       \
+     : t.prec == P_BF16  ? k_tile2d_down<OP, P_BF16>                      \
+                         : k_tile2d_down<OP, P_F32>)
+    auto fn = t.q1 ? MG_DOWN(1) : MG_DOWN(0);
+#undef MG_DOWN
     hipLaunchKernelGGL(fn, dim3(g.blocks), dim3(g.threads), g.lds, st, a);
     return hipGetLastError();
 }
@@ -390,10 +450,13 @@ hipError_t launch_tile2d_up(const Tile2dArgs &t, hipStream_t st) {
     a.b = t.b, a.c = t.cin, a.ec = t.ec, a.cout = t.cout;
     a.R = t.R, a.Rout = t.Rout, a.U = t.cdefer ? nullptr : t.U, a.scal = t.scal;
     a.cd = t.cdefer, a.ctr = t.ctr, a.cstride = t.cstride, a.adef = t.adef, a.part = t.part, a.f = t.f;
-    a.P = t.P, a.prec = t.prec, a.pc = t.pc, a.nu = t.nu, a.TX = g.TX, a.TY = g.TY, a.xtiles = g.xtiles;
+    a.P = t.P, a.pc = t.pc, a.nu = t.nu, a.TX = g.TX, a.TY = g.TY, a.xtiles = g.xtiles;
     a.k = t.q1 ? t.omega * 0.375 : t.omega / 4.0;
-#define MG_UP(OP, A) (upd ? k_tile2d_up<OP, A, true> : k_tile2d_up<OP, A, false>)
-    auto fn = t.q1 ? (f64 ? MG_UP(1, double) : MG_UP(1, float)) : (f64 ? MG_UP(0, double) : MG_UP(0, float));
+#define MG_UP(OP, PF) (upd ? k_tile2d_up<OP, PF, true> : k_tile2d_up<OP, PF, false>)
+#define MG_UPS(OP) \
+    (f64 ? MG_UP(OP, P_F64) : t.prec == P_F16 ? MG_UP(OP, P_F16) : t.prec == P_BF16 ? MG_UP(OP, P_BF16) : MG_UP(OP, P_F32))
+    auto fn = t.q1 ? MG_UPS(1) : MG_UPS(0);
+#undef MG_UPS
 #undef MG_UP
     hipLaunchKernelGGL(fn, dim3(g.blocks), dim3(g.threads), g.lds, st, a);
     return hipGetLastError();
