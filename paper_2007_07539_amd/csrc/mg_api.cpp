@@ -51,6 +51,7 @@ struct LevelPlan {
     size_t off_cg = 0;     // CG vectors of a multi-point base level
     // fused first smoothing + restriction from the stored b (levels >= 1)
     bool fsr_on = true, fsr = false;
+    bool p2 = true;  // prolongation + two sweeps as one kernel where it applies (no shape of either set by hand)
     RShape fsrsh{8, 2, 16, 3};
     bool rescale = false;  // restrictions into this level rescale (half-precision level, rescale_half)
     size_t off_t = 0;      // its restricted residual / scaled correction in the finer accumulator format
@@ -525,10 +526,10 @@ hipError_t enq_prolong(mg_ctx *h, hipStream_t st, int l, const void *b) {
     return hipSuccess;
 }
 
-hipError_t enq_post(mg_ctx *h, hipStream_t st, int l, const void *b, bool skip_last = false) {
+hipError_t enq_post(mg_ctx *h, hipStream_t st, int l, const void *b, bool skip_last = false, int done = 1) {
     LevelPlan &L = h->lv[l];
     const double N = (double)points(h->dim, L.n);
-    for (int k = 1; k < h->opt.nu2 - (skip_last ? 1 : 0); ++k) {
+    for (int k = done; k < h->opt.nu2 - (skip_last ? 1 : 0); ++k) {
         const int cur = h->cur[l];
         RUN(h, st, "sweep", l, N * 3 * sb(L.prec), level_sweep(h, l, L.prec, b, cbuf(h, l, cur), cbuf(h, l, cur ^ 1), st));
         h->cur[l] = cur ^ 1;
@@ -695,6 +696,16 @@ hipError_t enq_down(mg_ctx *h, hipStream_t st, RhsMode mode, int l, const void *
 hipError_t enq_up(mg_ctx *h, hipStream_t st, int l, const void *rhs, bool skip) {
     if (skip && h->fused2) return hipSuccess;
     if (tile2(h, l)) return enq_tile2_up(h, st, l, rhs);
+    LevelPlan &L = h->lv[l], &C = h->lv[l + 1];
+    if (h->dim == 3 && !h->q1 && !C.rescale && L.p2 && h->opt.nu2 - (skip ? 1 : 0) >= 2 &&
+        prolong_sweep2_ok(L.P, L.prec)) {
+        const int cur = h->cur[l];
+        RUN(h, st, "prolong_sweep2", l, (double)points(3, L.n) * 3 * sb(L.prec) + (double)points(3, C.n) * sb(C.prec),
+            launch_prolong_sweep2(L.prec, C.prec, L.P, cbuf(h, l, cur), cbuf(h, l + 1, h->cur[l + 1]), rhs,
+                                  cbuf(h, l, cur ^ 1), h->opt.omega, st));
+        h->cur[l] = cur ^ 1;
+        return enq_post(h, st, l, rhs, skip, 2);
+    }
     const hipError_t e = enq_prolong(h, st, l, rhs);
     return e != hipSuccess ? e : enq_post(h, st, l, rhs, skip);
 }
@@ -2191,7 +2202,9 @@ mg_status_t mg_set_shape(mg_handle h, int level, int kind, const int *p, int np)
             set_fused(h, h->fused);
         } else if (kind == MG_SHAPE_STENCIL) {
             L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = s;
+            L.p2 = false;
         } else {
+            L.p2 = L.p2 && kind == MG_SHAPE_SMOOTH;
             L.shs[kind == MG_SHAPE_SMOOTH ? SH_SMOOTH : kind == MG_SHAPE_SWEEP ? SH_SWEEP : SH_PROLONG] = s;
         }
     } else if (kind == MG_SHAPE_RESTRICT) {

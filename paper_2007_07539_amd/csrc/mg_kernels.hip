@@ -935,6 +935,128 @@ __global__ __launch_bounds__(1024) void k_march(F f_in, E e, int P, int TY, int 
 }
 
 // ===========================================================================
+// Prolongation + the first two post-sweeps of a level in one pass:
+//   p = round(c + 4 P e),  s = round(p + k (b - (6 p - nb(p)))),  c_out likewise
+// from s, the roundings of the separate kernels (bitwise equal).
+//
+// A block owns TY rows of zc planes and holds TY + 4 rows: p is needed two rows
+// and planes further out than c_out, s one.  Iteration t forms p of plane t + 2
+// (from registers, as the march does), s of plane t + 1 and c_out of plane t; p
+// and s pass through double-buffered LDS slots with one barrier per plane: the
+// slot of a plane is written in the iteration before the one that reads it.
+// The second sweep's pass over memory (4 + b of 6 bytes per point in FP16) and its
+// launch are saved; the halo costs (1 + 4/TY) (1 + 4/zc) of the arithmetic, so
+// this is for levels whose launches, not their arithmetic, take the time.
+// ===========================================================================
+template <int V, class TF, class TC>
+__global__ __launch_bounds__(512) void k_prolong_sweep2(const TF *__restrict__ c, const TC *__restrict__ ec,
+                                                        const TF *__restrict__ b, TF *__restrict__ cout, int P, int TY,
+                                                        int zc, int ytiles, acc_t<TF> k) {
+    typedef acc_t<TF> A;
+    typedef PProl<TF, TC, V> F;
+    typedef LdsRun<TF, V> LR;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int TXR = P / V, G = TY + 4;
+    const size_t slot = (size_t)G * P;
+    TF *const ps = reinterpret_cast<TF *>(smem_raw), *const ss = ps + 2 * slot;
+    const Grid<3> g{P};
+    const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const int y0 = 1 + blk % ytiles * TY;
+    const int z0 = 1 + blk / ytiles * zc, z1 = min(z0 + zc, P);
+    const int xc = threadIdx.x % TXR;
+    int gi = threadIdx.x / TXR;
+    gi = gi < (G + 1) / 2 ? 2 * gi : 2 * (gi - (G + 1) / 2) + 1;  // rows of one parity first, as in the march
+    const int yr = y0 - 2 + gi, y = min(max(yr, 0), P);
+    const bool row_in = yr >= 1 && yr <= P - 1;
+    const bool s_row = gi >= 1 && gi <= G - 2, out_row = gi >= 2 && gi <= G - 3 && row_in;
+    const int x0 = xc * V;
+    const unsigned at = g.in_plane(x0, y);
+    F f{c, ec, P / 2};
+    typename F::Raw fq;
+    RawRow<TF, V> bq, b1;  // b of planes t + 2 (in flight) and t + 1
+    A p0[V], p1[V], p2[V], s0[V], s1[V], s2[V], bw[V];
+    A none[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) p0[i] = s0[i] = s1[i] = bw[i] = A(0);
+    // p of planes z0 - 2 (or 0: plane -1 is not used) and z0 - 1
+    f.begin(x0, y, max(z0 - 2, 0));
+    if (z0 >= 2) {
+        f.fetch(g, x0, y, z0 - 2, fq);
+        f.value(fq, x0, y, z0 - 2, p0, none);
+    }
+    f.fetch(g, x0, y, z0 - 1, fq);
+    f.value(fq, x0, y, z0 - 1, p1, none);
+    LR::store(ps + (size_t)((z0 - 1) & 1) * slot + (size_t)gi * P, xc, TXR, p1);
+    f.fetch(g, x0, y, z0, fq);
+    fetch_row<TF, V>(b + g.plane(z0 - 1) + at, bq);
+    auto nbsum = [&](const TF *row, const A(&cm)[V], const A(&cc)[V], const A(&cp)[V], A(&nb)[V]) {
+        const A xl = x0 > 0 ? (A)widen(LR::left_of(row, xc, TXR)) : A(0);
+        const A xr = x0 + V < P ? (A)widen(LR::right_of(row, xc, TXR)) : A(0);
+        A ym[V], yp[V];
+        LR::load(row - P, xc, TXR, ym);
+        LR::load(row + P, xc, TXR, yp);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            nb[i] = (i > 0 ? cc[i - 1] : xl) + (i < V - 1 ? cc[i + 1] : xr);
+            nb[i] += ym[i];
+            nb[i] += yp[i];
+            nb[i] += cm[i];
+            nb[i] += cp[i];
+        }
+    };
+    // (the three planes of p and of s change roles)
+    auto step = [&](int t, const A(&pm)[V], const A(&pc)[V], A(&pp)[V], const A(&sm)[V], const A(&sc)[V], A(&sp)[V]) {
+        if (t + 2 <= P) f.value(fq, x0, y, t + 2, pp, none);
+        b1 = bq;
+        if (t + 3 <= P && t + 2 <= z1) f.fetch(g, x0, y, t + 3, fq);
+        if (t + 2 <= z1) fetch_row<TF, V>(b + g.plane(t + 2) + at, bq);
+        __syncthreads();
+        A b0[V];  // b of plane t, then t + 1
+#pragma unroll
+        for (int i = 0; i < V; ++i) b0[i] = bw[i];
+        widen_row<TF, V>(b1, bw);
+        const int z = t + 1;
+        if (s_row) {
+            if (row_in && z >= 1 && z <= P - 1) {
+                A nb[V];
+                nbsum(ps + (size_t)(z & 1) * slot + (size_t)gi * P, pm, pc, pp, nb);
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    const A lc = fmaT<A>(A(6), pc[i], -nb[i]);
+                    sp[i] = round_to<TF>(fmaT<A>(k, bw[i] - lc, pc[i]));
+                }
+                if (x0 == 0) sp[0] = A(0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < V; ++i) sp[i] = A(0);
+            }
+            LR::store(ss + (size_t)(z & 1) * slot + (size_t)gi * P, xc, TXR, sp);
+        }
+        if (out_row && t >= z0) {
+            A nb[V];
+            nbsum(ss + (size_t)(t & 1) * slot + (size_t)gi * P, sm, sc, sp, nb);
+            TF o[V];
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                const A lc = fmaT<A>(A(6), sc[i], -nb[i]);
+                o[i] = Store<TF>::from_acc(fmaT<A>(k, b0[i] - lc, sc[i]));
+            }
+            if (x0 == 0) o[0] = zero_of<TF>();
+            store_row<TF, V>(cout + g.plane(t) + at, o);
+        }
+        LR::store(ps + (size_t)(t & 1) * slot + (size_t)gi * P, xc, TXR, pp);
+    };
+    for (int t = z0 - 2;;) {
+        step(t, p0, p1, p2, s0, s1, s2);
+        if (++t >= z1) break;
+        step(t, p1, p2, p0, s1, s2, s0);
+        if (++t >= z1) break;
+        step(t, p2, p0, p1, s2, s0, s1);
+        if (++t >= z1) break;
+    }
+}
+
+// ===========================================================================
 // Residual + full-weighting restriction + cast (the residual transfer of
 // Algorithm 1).  A block
 // owns `tyc` coarse rows (3-D) and `zcc` coarse planes.  Its threads first act
@@ -1869,6 +1991,62 @@ hipError_t launch_prolong(int D, int pf, int pc, int P, const void *c, const voi
                           double omega, bool sweep, const Shape &s, hipStream_t st) {
     MG_DISPATCH_T(pf, return prolong_tf<TT>(D, pc, P, c, ec, b, c_out, omega, sweep, s, st));
     return hipErrorInvalidValue;
+}
+
+// Rows and planes per block.  A block's planes follow one another, so a small
+// level takes one plane per block although each then forms four halo planes
+// (FP16, us: 31^3 7.0 with one plane, 7.6 with two; 63^3 7.6 and 8.4).
+static void prolong_sweep2_shape(int P, int *ty, int *zc) {
+    *ty = P >= 128 ? 12 : P >= 64 ? 8 : 4;
+    *zc = P >= 128 ? 2 : 1;
+}
+
+template <int V, class TF, class TC>
+static hipError_t prolong_sweep2_run(int P, const void *c, const void *ec, const void *b, void *cout, double omega,
+                                     hipStream_t st) {
+    int ty, zc;
+    prolong_sweep2_shape(P, &ty, &zc);
+    const int ytiles = ceil_div(P - 1, ty), blocks = ytiles * ceil_div(P - 1, zc);
+    const size_t lds = 4 * (size_t)(ty + 4) * P * sizeof(TF);
+    hipLaunchKernelGGL((k_prolong_sweep2<V, TF, TC>), dim3(blocks), dim3((P / V) * (ty + 4)), lds, st,
+                       static_cast<const TF *>(c), static_cast<const TC *>(ec), static_cast<const TF *>(b),
+                       static_cast<TF *>(cout), P, ty, zc, ytiles, (acc_t<TF>)(omega / 6.0));
+    return hipGetLastError();
+}
+
+template <class TF, class TC>
+static hipError_t prolong_sweep2_v(int P, const void *c, const void *ec, const void *b, void *cout, double omega,
+                                   hipStream_t st) {
+    if constexpr (sizeof(TF) == 8) return prolong_sweep2_run<4, TF, TC>(P, c, ec, b, cout, omega, st);
+    else if (P < 128) return prolong_sweep2_run<4, TF, TC>(P, c, ec, b, cout, omega, st);
+    else return prolong_sweep2_run<8, TF, TC>(P, c, ec, b, cout, omega, st);
+}
+
+// Up to 63^3, and 127^3 in FP16 and FP32: beyond, the halo's arithmetic (BF16: its
+// roundings) costs more than the launch and the pass (us, against the two kernels:
+// FP16 31^3 5.4, 9.2; 63^3 5.6, 8.5; 127^3 10.7, 11.0; 255^3 64, 41; FP64 63^3 6.0, 9.0;
+// 127^3 25, 20; a solve of 127^3 in FP32 1634, 1689).
+bool prolong_sweep2_ok(int P, int pf) { return P >= 16 && P <= (pf == P_F16 || pf == P_F32 ? 128 : 64); }
+
+hipError_t launch_prolong_sweep2(int pf, int pc, int P, const void *c, const void *ec, const void *b, void *cout,
+                                 double omega, hipStream_t st) {
+    if (!prolong_sweep2_ok(P, pf)) return hipErrorInvalidValue;
+#define MG_P2(TF)                                                                     \
+    switch (pc) {                                                                     \
+    case P_F64: return prolong_sweep2_v<TF, double>(P, c, ec, b, cout, omega, st);    \
+    case P_F32: return prolong_sweep2_v<TF, float>(P, c, ec, b, cout, omega, st);     \
+    case P_F16: return prolong_sweep2_v<TF, f16>(P, c, ec, b, cout, omega, st);       \
+    case P_BF16: return prolong_sweep2_v<TF, bf16>(P, c, ec, b, cout, omega, st);     \
+    default: return hipErrorInvalidValue;                                             \
+    }
+    switch (pf) {
+    case P_F64: MG_P2(double)
+    case P_F32: MG_P2(float)
+    case P_F16: MG_P2(f16)
+    case P_BF16: MG_P2(bf16)
+    default: return hipErrorInvalidValue;
+    }
+#undef MG_P2
 }
 
 template <int D, int V, class TF, class TC>

@@ -310,6 +310,12 @@ hipError_t launch_batched_sweep_update(int pf, bool defer, const BDesc *d, const
                                        const int *active, double omega, double *part, int grid, int threads,
                                        size_t lds, hipStream_t st);
 
+// Prolongation + the first two post-sweeps of a 3-D level (bitwise those of
+// launch_prolong with a sweep and launch_sweep).
+bool prolong_sweep2_ok(int P, int pf);
+hipError_t launch_prolong_sweep2(int pf, int pc, int P, const void *c, const void *ec, const void *b, void *cout,
+                                 double omega, hipStream_t st);
+
 // ---- groups of grids in one launch (start and end of a batched solve) ---------
 // Per-grid pointers passed by value, so that the caller's arrays need no copy
 // to the device.
