@@ -924,11 +924,20 @@ dim3 q1_grid4(int D, int n, int P) {
     const unsigned bx = (unsigned)((P / 4 + q1_bx4(P) - 1) / q1_bx4(P));
     return D == 3 ? dim3(bx, (unsigned)n, (unsigned)n) : dim3(bx, (unsigned)n, 1);
 }
-// Planes marched by one thread of k_q1_march4, and its grid.
-constexpr int kMarchZ = 16;
+// Planes marched by one thread of k_q1_march4, and its grid.  Planes follow one
+// another (about 0.5 us each), so a level with few blocks marches fewer: at 16
+// throughout, a sweep of 27^3 or 55^3 in FP32 took 13 us, 6 with two; 111^3 15
+// and 11 with eight.  About four blocks per CU.
+int q1_march_z(int n, int P) {
+    const long bx = (P / 4 + q1_bx4(P) - 1) / q1_bx4(P);
+    for (int mz : {16, 8, 4})
+        if (bx * n * ((n + mz - 1) / mz) >= 1024) return mz;
+    return 2;
+}
 dim3 q1_grid4z(int n, int P) {
     const unsigned bx = (unsigned)((P / 4 + q1_bx4(P) - 1) / q1_bx4(P));
-    return dim3(bx, (unsigned)n, (unsigned)((n + kMarchZ - 1) / kMarchZ));
+    const int mz = q1_march_z(n, P);
+    return dim3(bx, (unsigned)n, (unsigned)((n + mz - 1) / mz));
 }
 dim3 q1_grid(int D, int n) {
     const unsigned bx = (unsigned)((n + q1_bx(n) - 1) / q1_bx(n));
@@ -1078,7 +1087,7 @@ hipError_t sweep_t(int D, int n, int P, const void *b, const void *c, void *cout
         const dim3 g4 = q1_grid4(D, n, P);
         if (D == 3)
             hipLaunchKernelGGL((k_q1_march4<T, false>), q1_grid4z(n, P), dim3(q1_bx4(P)), 0, st,
-                               static_cast<const T *>(b), static_cast<const T *>(c), cout, n, P, kMarchZ, w);
+                               static_cast<const T *>(b), static_cast<const T *>(c), cout, n, P, q1_march_z(n, P), w);
         else
             hipLaunchKernelGGL((k_q1_sweep4<2, T>), g4, dim3(q1_bx4(P)), 0, st, static_cast<const T *>(b),
                                static_cast<const T *>(c), static_cast<T *>(cout), P, w);
@@ -1123,7 +1132,7 @@ hipError_t restrict_t(int D, int n, int P, const void *b, const void *c, void *r
         } else if (D == 3)
             hipLaunchKernelGGL((k_q1_march4<T, true>), q1_grid4z(n, P), dim3(q1_bx4(P)), 0, st,
                                static_cast<const T *>(b), static_cast<const T *>(c), static_cast<void *>(r), n, P,
-                               kMarchZ, A(0));
+                               q1_march_z(n, P), A(0));
         else
             hipLaunchKernelGGL((k_q1_resid4<2, T>), g4, dim3(q1_bx4(P)), 0, st, static_cast<const T *>(b),
                                static_cast<const T *>(c), r, P);
