@@ -1377,7 +1377,7 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
                 if (t < best) best = t, bo = s;
             }
             L.osh = bo;
-            h->outer_parts = stencil_blocks(D, L.P, bo);
+            set_fused(h, h->fused);  // the partials of the update in use (2-D: the tiles')
             // the fused last sweep + update against the two kernels it replaces
             // (both ways of getting the right-hand side where both apply)
             if (fusion_possible(h)) {

@@ -67,3 +67,21 @@ def test_tile_update_is_the_step(n, disc, name, defer):
     assert torch.equal(u, (alpha * f) * c)
     r = oracle.residual(b, u.cpu().numpy(), disc)
     assert abs(res.history[1] / (oracle.norm2(r) / oracle.norm2(b)) - 1.0) <= 1e-12
+
+
+@pytest.mark.parametrize("n,name,scaling", [(127, "f16", True), (255, "f64", False), (511, "f32", True),
+                                            (2047, "f16", True)])
+def test_autotuned_tiles_have_the_same_history(n, name, scaling, tmp_path, monkeypatch):
+    """An autotuned 2-D handle sums the norm partials of every tile: u and the
+    iterations are the untuned handle's, freshly timed and read from the tuning
+    cache, and so are the norms, up to their summation order (n^2 eps at most, far
+    below 1e-8)."""
+    print(f"autotuned 2-D tiles n={n} {name}", flush=True)
+    monkeypatch.setenv("MGIR_TUNE_CACHE", str(tmp_path / "tune.txt"))
+    prec = W.precision_map(name, mgir.full_levels(n))
+    b = torch.from_numpy(W.uniform_rhs(2, n, seed=6)).to("cuda")
+    u0, r0 = mgir.Solver(2, n, prec, residual_scaling=scaling).solve(b)
+    for fresh in (True, False):
+        u, r = mgir.Solver(2, n, prec, residual_scaling=scaling, autotune=True).solve(b)
+        assert r.iterations == r0.iterations and torch.equal(u, u0), fresh
+        assert np.allclose(r.history, r0.history, rtol=1e-8, atol=0.0), (fresh, r.history, r0.history)
