@@ -1116,7 +1116,9 @@ std::vector<Shape> stencil_candidates(const mg_ctx *h, const LevelPlan &L, bool 
 // instead of timing again.  The key holds everything the choice depends on:
 // device architecture and CU count, the library's tuning version, dimension,
 // grid, level formats and the options that change the kernels.
-constexpr int kTuneVersion = 4;
+// The version goes up with every change of the kernels or of their dispatch
+// behind the shapes, so that a choice made for other kernels is not applied.
+constexpr int kTuneVersion = 5;
 
 // The device part of a key: tuning version, architecture, CU count ("" when
 // no device is current).
@@ -1141,7 +1143,7 @@ std::string tune_key(const mg_ctx *h) {
     return std::string(buf);
 }
 
-// The integers stored under key in the MGIR_TUNE_CACHE file (false: none).
+// The integers last stored under key in the MGIR_TUNE_CACHE file (false: none).
 bool cache_read(const std::string &key, std::vector<int> &v) {
     const char *path = std::getenv("MGIR_TUNE_CACHE");
     if (!path || !*path || key.empty()) return false;
@@ -1150,7 +1152,7 @@ bool cache_read(const std::string &key, std::vector<int> &v) {
     std::string line;
     bool found = false;
     char chunk[4096];
-    while (!found && std::fgets(chunk, sizeof chunk, f)) {
+    while (std::fgets(chunk, sizeof chunk, f)) {
         line += chunk;
         if (line.empty() || line.back() != '\n') continue;  // a line longer than the chunk
         const size_t tab = line.find('\t');
@@ -2955,7 +2957,13 @@ bool apply_batched_state(mg_ctx *h, const std::vector<int> &v) {
 mg_status_t autotune_batched(mg_ctx *h, hipStream_t st) {
     const std::string key = batched_tune_key(h);
     std::vector<int> v;
-    if (cache_read(key, v) && apply_batched_state(h, v)) return batched_upload(h);
+    // (a plan that does not fit its room, e.g. from an edited line, is tuned anew)
+    const auto inst = h->inst;
+    if (cache_read(key, v) && apply_batched_state(h, v)) {
+        const mg_status_t s = batched_upload(h);
+        if (s != MG_ERR_WORKSPACE) return s;
+        h->inst = inst;
+    }
     const int ni = (int)h->inst.size();
     for (int i = 0; i < ni; ++i) h->host_active[i] = 1;
     HIPCHK(hipMemcpy(h->ws + h->off_active, h->host_active, sizeof(int) * ni, hipMemcpyHostToDevice));

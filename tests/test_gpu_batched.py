@@ -215,3 +215,31 @@ def test_batched_postponed_updates_around_the_ring(dev, name, steps):
         u, r = one.solve(bs[i], check=False)
         assert res[i].iterations == r.iterations
         assert torch.equal(us[i], u), i
+
+
+def test_tuned_line_beyond_the_plan_room_is_tuned_anew(dev, tmp_path, monkeypatch):
+    """A cached choice whose work lists exceed the room reserved for them (one
+    plane and one row per tile) is not an error of the handle: it is tuned anew,
+    the new line is the one read from then on, and lines of an earlier version of
+    the kernels are not read at all."""
+    sizes = [31] * 3
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("MGIR_TUNE_CACHE", str(path))
+    prec = W.precision_map("f16", W.levels_for(31))
+    kw = dict(nu1=3, autotune=True)
+    print("tuned line beyond the plan room", flush=True)
+    mgir.BatchedSolver(sizes, prec, **kw)
+    key, ints = path.read_text().splitlines()[0].split("\t")
+    assert int(key.split("|")[0][1:]) > 4
+    v = [int(x) for x in ints.split()]
+    per = len(v) // 2  # classes of pitch 32 and 16, each {P, format, V, zc, ty, V, tyc, zcc, pipe, ..}
+    for c in range(2):
+        v[c * per + 2 : c * per + 9] = [4, 1, 1, 4, 1, 1, 0]
+    path.write_text(key + "\t" + " ".join(map(str, v)) + "\n")
+    s = mgir.BatchedSolver(sizes, prec, **kw)
+    assert s.get_shape(0, 0, mgir.SHAPE_SWEEP)[:5] != [4, 1, 256, 1, 1]
+    lines = path.read_text().splitlines()
+    assert len(lines) == 2 and lines[1].startswith(key + "\t")
+    again = mgir.BatchedSolver(sizes, prec, **kw)
+    assert path.read_text().splitlines() == lines
+    assert again.get_shape(0, 0, mgir.SHAPE_SWEEP) == s.get_shape(0, 0, mgir.SHAPE_SWEEP)
