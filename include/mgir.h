@@ -447,8 +447,7 @@ typedef enum {
 mg_status_t mg_set_shape(mg_handle h, int level, int kind, const int *params, int nparams);
 /* Reading a shape: the values mg_set_shape takes (up to nparams).  On a
  * many-right-hand-side handle, the stencil kinds and MG_SHAPE_RESTRICT of
- * levels below the base (only zc, and zcc of the restriction, shape those
- * kernels).  A batched handle's shapes are read per instance with
+ * every level but the base, the same for every right-hand side.  A batched handle's shapes are read per instance with
  * mg_get_instance_shape. */
 mg_status_t mg_get_shape(mg_handle h, int level, int kind, int *params, int nparams);
 

@@ -2228,7 +2228,9 @@ mg_status_t mg_get_shape(mg_handle h, int level, int kind, int *p, int np) {
     if (h->batched) return fail(MG_ERR_STATE, "a batched handle's shapes are read with mg_get_instance_shape");
     if (h->nrhs) {
         if (level < 0 || level >= h->nl - 1) return fail(MG_ERR_ARG, "level %d has no launch shape", level);
-        return level_shape(h->lv[level], level, kind, p, np);
+        LevelPlan L = h->inst[0].lv[level];
+        L.osh = h->inst[0].osh;
+        return level_shape(L, level, kind, p, np);
     }
     if (kind == MG_SHAPE_TAIL) {
         if (np < 1) return fail(MG_ERR_ARG, "too few values");
@@ -3510,8 +3512,7 @@ mg_status_t mg_setup_multi(mg_handle *out, int dim, int n, int nrhs, const mg_pr
     h->bprec = prec;
     plan_instances(h, std::vector<int>(nrhs, n));
     h->col_stride = h->inst[1].off_R - h->inst[0].off_R;
-    h->lv = h->inst[0].lv;  // (the shapes that mg_get_shape reports)
-    h->lv[0].osh = h->inst[0].osh;
+    h->lv = h->inst[0].lv;  // (the level sizes)
     *out = h;
     return MG_OK;
 }

@@ -215,3 +215,21 @@ def test_multi_split_and_join_edges(dev, n, k, name):
     over = b.clone()
     ms.solve(over, over, check=False)
     assert torch.equal(over, u)
+
+
+def test_multi_reports_the_shapes_in_use(dev, tmp_path, monkeypatch):
+    """get_shape returns the shapes that a tuned handle runs with, not the built-in ones."""
+    n, k = 31, 8
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("MGIR_TUNE_CACHE", str(path))
+    prec = W.precision_map("f16", W.levels_for(n))
+    print("multi shapes in use", flush=True)
+    mgir.MultiSolver(n, k, prec, autotune=True)
+    key, ints = path.read_text().splitlines()[0].split("\t")
+    v = [int(x) for x in ints.split()]
+    assert v[0] == 32  # {P, format, V, zc, ty, V, tyc, zcc, pipe, ..} of the largest class
+    v[2:9] = [4, 7, 3, 4, 2, 5, 1]
+    path.write_text(key + "\t" + " ".join(map(str, v)) + "\n")
+    s = mgir.MultiSolver(n, k, prec, autotune=True)
+    assert s.get_shape(0, mgir.SHAPE_SWEEP)[:5] == [4, 7, 256, 1, 3]
+    assert s.get_shape(0, mgir.SHAPE_RESTRICT) == [4, 2, 5, 1]
