@@ -116,10 +116,8 @@ typedef struct {
                                 kernels (no fused forms; the launch shapes are those of
                                 the LDS-staged 3-D kernels, see "Q1 handles" under
                                 mg_set_shape); single-grid handles only, as rescale_half. */
-    int defer_update;        /* 0 (default): ir_solve adds alpha c to u in every step, as
-                                Algorithm 2 writes it, except on large grids (2^22 points
-                                and more, FP16/BF16 and 3-D finite-difference FP32 finest
-                                levels), where it is 8.  k in 1..64: the step's update
+    int defer_update;        /* k in 1..64: ir_solve does not add alpha c to u in every
+                                step, as Algorithm 2 writes it.  The step's update
                                 kernel (3-D finite differences with the fused last
                                 sweep + update, MG_SHAPE_FUSE in use; or the Q1 update,
                                 2-D and 3-D) stores c in the finest level's
@@ -132,7 +130,15 @@ typedef struct {
                                 only needs r.  The workspace grows by k finest-level
                                 vectors of that format.  Pays where the format is
                                 narrower than FP64 (FP16: 2 instead of 16 bytes per
-                                point and step).  Single-grid handles only. */
+                                point and step).  Single-grid handles only.
+                                -1: u is updated in every step, no ring.
+                                0 (default): 8 on grids of 2^22 points and more whose
+                                finest level is FP16, BF16 or (3-D finite differences)
+                                FP32, and for the FP16 and BF16 instances of a batch
+                                and columns, if the bound workspace has room for it;
+                                else as -1.  mg_workspace_size includes that ring;
+                                mg_bind_workspace also takes a workspace of the size
+                                that -1 asks for. */
 } mg_options_t;
 
 typedef struct {
@@ -174,12 +180,15 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
 
 /* Bytes of device workspace the handle needs (all levels' right-hand side and
  * correction vectors in their storage formats, the FP64 solution and residual
- * of the finest level, reduction partials). */
+ * of the finest level, reduction partials), with the room that the library's
+ * default uses to postpone updates (opt.defer_update = 0) and, on a 2-D handle
+ * with an FP64 finest level and no residual scaling, a second residual. */
 mg_status_t mg_workspace_size(mg_handle h, size_t *bytes);
 
-/* Bind caller-owned device memory (at least mg_workspace_size bytes, 256-byte
- * aligned).  Zero-fills it on stream and waits for that; with opt.autotune it
- * also times launch shapes.  May be called again with another buffer; the
+/* Bind caller-owned device memory (mg_workspace_size bytes, 256-byte aligned;
+ * without the optional parts named there, the handle runs without them, with
+ * the same results).  Clears it on stream and waits for that; with opt.autotune
+ * it also times launch shapes.  May be called again with another buffer; the
  * previous one is no longer referenced afterwards. */
 mg_status_t mg_bind_workspace(mg_handle h, void *dev_ptr, size_t bytes, void *stream);
 

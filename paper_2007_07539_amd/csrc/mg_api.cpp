@@ -79,6 +79,12 @@ struct mg_ctx {
     int ascale = 0;
     std::vector<LevelPlan> lv;
     size_t off_R = 0, off_U = 0, off_part = 0, off_scal = 0, ws_need = 0;
+    // The workspace ends in what a step is only faster with: a ring of postponed
+    // updates that the options leave to the library, or the second residual array
+    // of a 2-D grid.  A workspace that ends at ws_min is taken without them.
+    size_t ws_min = 0;
+    size_t clear_end = 0;  // the part of the workspace that is cleared whole (the rings: their ghost cells)
+    size_t off_R2_opt = 0;  // where the optional second residual array would be
     size_t vc_bytes = 0;  // the leading part of the workspace a lone V-cycle uses
     size_t off_rs = 0, off_rpart = 0;  // per-level {s, 1/s} and the partial maxima of the rescaling
     int max_parts = 0;
@@ -99,6 +105,7 @@ struct mg_ctx {
     int rpar = 0;       // 1: the current residual is in the second array
     // postponed solution updates (opt.defer_update)
     int defer = 0;      // ring depth in use; 0: u is updated every step
+    int defer_plan = 0;  // ... that the full workspace has room for
     size_t off_cdef = 0, cdef_stride = 0, off_adef = 0, off_dctr = 0;
     int pending = 0;    // corrections in the ring not yet added to u
     bool u_zero = false;  // u is zero and not yet stored (a solve from zero with postponed updates)
@@ -130,8 +137,9 @@ struct mg_ctx {
         int lt = 0;          // first level of the fused coarse end (nl - 1: none)
         bool su = false;     // last sweep + update fused (shape fsh)
         Shape fsh{4, 16, 256, 1, 4};
-        // postponed updates: ring of `defer` corrections (0: u updated every step)
-        int defer = 0, pending = 0;
+        // postponed updates: ring of `defer` corrections (0: u updated every step),
+        // defer_plan of them in the full workspace
+        int defer = 0, defer_plan = 0, pending = 0;
         bool u_zero = false;
         size_t off_cd = 0, cstride = 0, off_adef = 0;
     };
@@ -1039,6 +1047,24 @@ mg_status_t need_ws(mg_ctx *h) {
 int level_prec_code(int p) { return p; }
 
 
+// Clear the workspace: ghost cells must read zero and padding must be finite.
+// The rings' slots are written before they are read, but for their ghost cells.
+hipError_t clear_ws(mg_ctx *h, hipStream_t st) {
+    hipError_t e = hipMemsetAsync(h->ws, 0, h->clear_end, st);
+    if (e == hipSuccess && h->off_R2_opt && h->off_R2)
+        e = hipMemsetAsync(h->ws + h->off_R2, 0, align_up(h->lv[0].elems * sizeof(double), 256), st);
+    if (e == hipSuccess && h->defer) {
+        const LevelPlan &L = h->lv[0];
+        e = hipMemsetAsync(h->ws + h->off_adef, 0, h->off_cdef - h->off_adef, st);
+        if (e == hipSuccess)
+            e = launch_ring_ghosts(h->dim, L.prec, L.P, h->ws + h->off_cdef, h->cdef_stride, h->defer, st);
+    }
+    for (const auto &I : h->inst)
+        if (e == hipSuccess && I.defer)
+            e = launch_ring_ghosts(3, I.lv[0].prec, I.lv[0].P, h->ws + I.off_cd, I.cstride, I.defer, st);
+    return e;
+}
+
 // ---- autotuner ------------------------------------------------------------
 // Times candidate launch shapes of each level with HIP events on the caller's
 // stream and keeps the fastest.  Every shape forms the same roundings, so the
@@ -1408,7 +1434,7 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
             }
         }
     }
-    HIPCHK(hipMemsetAsync(h->ws, 0, h->ws_need, st));
+    HIPCHK(clear_ws(h, st));
     HIPCHK(hipStreamSynchronize(st));
     return MG_OK;
 }
@@ -1478,7 +1504,7 @@ mg_status_t autotune_q1(mg_ctx *h, hipStream_t st) {
         }
     }
     set_fused(h, h->fused);
-    HIPCHK(hipMemsetAsync(h->ws, 0, h->ws_need, st));
+    HIPCHK(clear_ws(h, st));
     HIPCHK(hipStreamSynchronize(st));
     v.clear();
     for (int l = 0; l + 1 < h->nl; ++l)
@@ -1591,8 +1617,8 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
     if (!(o.rtol >= 0.0)) return fail(MG_ERR_ARG, "rtol must be >= 0");
     if (o.cycles_per_step < 1 || o.cycles_per_step > 16)
         return fail(MG_ERR_ARG, "cycles_per_step must be in 1..16 (got %d)", o.cycles_per_step);
-    if (o.defer_update < 0 || o.defer_update > kMaxDefer)
-        return fail(MG_ERR_ARG, "defer_update must be in 0..%d (got %d)", kMaxDefer, o.defer_update);
+    if (o.defer_update < -1 || o.defer_update > kMaxDefer)
+        return fail(MG_ERR_ARG, "defer_update must be in -1..%d (got %d)", kMaxDefer, o.defer_update);
     std::vector<int> prec(m, P_F64);
     if (level_prec)
         for (int i = 0; i < m; ++i) {
@@ -1681,12 +1707,12 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
     const bool fusable = dim == 3 && !q1 && m >= 2;
     // Postponed updates of u: the depth asked for, or by default a ring of eight
     // where the step's vectors no longer fit the last-level cache, so that 10 bytes
-    // less per point and step (2-byte formats) are that much less traffic, and
-    // the ring's memory is no concern (us per solve, u in place against eight:
+    // less per point and step (2-byte formats) are that much less traffic (us per
+    // solve, u in place against eight:
     // 255^3 FP16 4958 -> 4392, FP32 5693 -> 5449; 511^3 FP16 27981 -> 25297; Q1 4095^2
     // FP16 3855 -> 3537; 127^3 FP16 1740 -> 1763, Q1 191^3 FP32 3855 -> 3880).
-    int depth = o.defer_update;
-    if (depth == 0 && points(dim, n) >= (1 << 22) && off <= (size_t)64 << 30 &&
+    int depth = std::max(0, o.defer_update);
+    if (o.defer_update == 0 && points(dim, n) >= (1 << 22) &&
         (half_prec(prec[0]) || (fusable && prec[0] == P_F32)))
         depth = 8;
     if (fusable) {
@@ -1696,22 +1722,6 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
         h->su_r = prec_bytes(prec[0]) >= 4 || (n >= 511 && depth == 0);
         h->off_R2 = off;
         off += fin;
-    }
-    // the 2-D update reads r as the right-hand side on its tiles' halos too
-    if (dim == 2 && prec[0] == P_F64 && !o.residual_scaling && tile2(h, 0)) {
-        h->off_R2 = off;
-        off += fin;
-    }
-    if ((fusable || q1) && depth > 0) {
-        const LevelPlan &L = h->lv[0];
-        h->defer = depth;
-        h->cdef_stride = align_up(L.elems * prec_bytes(L.prec), 256) / prec_bytes(L.prec);
-        h->off_cdef = off;
-        off += (size_t)h->defer * h->cdef_stride * prec_bytes(L.prec);
-        h->off_adef = off;
-        off += align_up((size_t)h->defer * sizeof(double), 256);
-        h->off_dctr = off;
-        off += 256;
     }
     if (m > 1) {
         h->outer_parts = stencil_blocks(dim, h->lv[0].P, h->lv[0].osh);
@@ -1736,6 +1746,25 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
     off += align_up((size_t)maxp * 2 * sizeof(double), 256);
     h->off_scal = off;
     off += 256;
+    h->clear_end = off;
+    if ((fusable || q1) && depth > 0) {
+        const LevelPlan &L = h->lv[0];
+        h->defer = h->defer_plan = depth;
+        h->off_adef = off;
+        off += align_up((size_t)depth * sizeof(double), 256);
+        h->off_dctr = off;
+        off += 256;
+        h->cdef_stride = align_up(L.elems * prec_bytes(L.prec), 256) / prec_bytes(L.prec);
+        h->off_cdef = off;
+        off += (size_t)depth * h->cdef_stride * prec_bytes(L.prec);
+    }
+    h->ws_min = o.defer_update > 0 ? off : h->clear_end;
+    // the 2-D update reads r as the right-hand side on its tiles' halos too
+    // (such a level is FP64: it has no ring but one that was asked for)
+    if (dim == 2 && prec[0] == P_F64 && !o.residual_scaling && tile2(h, 0)) {
+        h->off_R2 = h->off_R2_opt = off;
+        off += fin;
+    }
     h->ws_need = off;
     if (tail_prepare() != hipSuccess) h->tail_on = false;
     if (m > 1) {
@@ -1767,14 +1796,20 @@ mg_status_t mg_workspace_size(mg_handle h, size_t *bytes) {
 
 mg_status_t mg_bind_workspace(mg_handle h, void *dev_ptr, size_t bytes, void *stream) {
     if (!h || !dev_ptr) return fail(MG_ERR_ARG, "null argument");
-    if (bytes < h->ws_need) return fail(MG_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", bytes, h->ws_need);
+    if (bytes < h->ws_min) return fail(MG_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", bytes, h->ws_min);
     if (reinterpret_cast<uintptr_t>(dev_ptr) % 256) return fail(MG_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!h->host_scal) HIPCHK(hipHostMalloc((void **)&h->host_scal, 4 * sizeof(double), hipHostMallocCoherent));
     drop_graph(h);
     h->ws = static_cast<char *>(dev_ptr);
     h->ws_bytes = bytes;
-    HIPCHK(hipMemsetAsync(h->ws, 0, h->ws_need, st));
+    const bool full = bytes >= h->ws_need;
+    h->rpar = h->pending = 0;
+    h->defer = full || h->opt.defer_update > 0 ? h->defer_plan : 0;
+    for (auto &I : h->inst) I.defer = full ? I.defer_plan : 0;
+    if (h->off_R2_opt) h->off_R2 = full ? h->off_R2_opt : 0;
+    if (!h->batched && !h->nrhs && h->nl > 1) set_fused(h, h->fused);
+    HIPCHK(clear_ws(h, st));
     HIPCHK(hipStreamSynchronize(st));
     for (int l = 0; l < h->nl; ++l) h->cur[l] = 0;
     if (h->batched || h->nrhs) {
@@ -3008,7 +3043,7 @@ mg_status_t autotune_batched(mg_ctx *h, hipStream_t st) {
     }
     mg_status_t s = batched_upload(h);
     if (s != MG_OK) return s;
-    HIPCHK(hipMemsetAsync(h->ws, 0, h->ws_need, st));
+    HIPCHK(clear_ws(h, st));
     HIPCHK(hipStreamSynchronize(st));
     s = batched_upload(h);  // (the descriptors lie in the workspace just cleared)
     if (s == MG_OK) cache_write(key, v);
@@ -3077,17 +3112,15 @@ void plan_instances(mg_ctx *h, const std::vector<int> &n) {
     // Postponed updates of u for 2-byte formats: each step stores its correction
     // (2 bytes per point) in a ring of eight and a pass per eight steps adds
     // them, 6 instead of 16 bytes per point and step; u is bit for bit the same.
-    // The ring adds 16 bytes per point to the workspace's 16 and the levels', so
-    // very large batches go without.
+    // The rings add 16 bytes per point to the workspace's 16 and the levels', so
+    // very large batches go without, and so does a workspace too small for them.
     constexpr int kRing = 8;
-    if (off <= (size_t)64 << 30) {
+    if (off <= (size_t)64 << 30 && o.defer_update >= 0) {
         for (auto &I : h->inst) {
             const LevelPlan &L = I.lv[0];
             if (!I.su || prec_bytes(L.prec) != 2) continue;
-            I.defer = kRing;
+            I.defer = I.defer_plan = kRing;
             I.cstride = align_up(L.elems * 2, 256) / 2;
-            I.off_cd = off, off += kRing * I.cstride * 2;
-            I.off_adef = off, off += 256;
         }
     }
     h->off_bctr = off, off += align_up((size_t)ninst * sizeof(int), 256);
@@ -3101,6 +3134,12 @@ void plan_instances(mg_ctx *h, const std::vector<int> &n) {
     // with shorter plane chunks have more work items)
     h->bmeta_cap = align_up(4 * h->bmeta_bytes, 256);
     off += h->bmeta_cap;
+    h->clear_end = h->ws_min = off;
+    for (auto &I : h->inst) {
+        if (!I.defer) continue;
+        I.off_adef = off, off += 256;
+        I.off_cd = off, off += (size_t)I.defer * I.cstride * 2;
+    }
     h->ws_need = off;
 }
 
@@ -3183,7 +3222,8 @@ mg_status_t mg_setup_batched(mg_handle *out, int dim, int ninst, const int *n, c
     mg_default_options(&o);
     if (opt) o = *opt;
     if (o.rescale_half) return fail(MG_ERR_ARG, "rescale_half is only available on single-grid handles");
-    if (o.defer_update) return fail(MG_ERR_ARG, "defer_update is only available on single-grid handles");
+    if (o.defer_update != 0 && o.defer_update != -1)
+        return fail(MG_ERR_ARG, "defer_update other than 0 and -1 is only available on single-grid handles");
     if (o.discretization != MG_DISC_FD)
         return fail(MG_ERR_ARG, "the Q1 discretisation is only available on single-grid handles");
     if (o.cycles_per_step != 1)
@@ -3479,7 +3519,8 @@ mg_status_t mg_setup_multi(mg_handle *out, int dim, int n, int nrhs, const mg_pr
     mg_default_options(&o);
     if (opt) o = *opt;
     if (o.rescale_half) return fail(MG_ERR_ARG, "rescale_half is only available on single-grid handles");
-    if (o.defer_update) return fail(MG_ERR_ARG, "defer_update is only available on single-grid handles");
+    if (o.defer_update != 0 && o.defer_update != -1)
+        return fail(MG_ERR_ARG, "defer_update other than 0 and -1 is only available on single-grid handles");
     if (o.discretization != MG_DISC_FD)
         return fail(MG_ERR_ARG, "the Q1 discretisation is only available on single-grid handles");
     if (o.cycles_per_step != 1)

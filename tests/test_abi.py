@@ -317,3 +317,36 @@ def test_noalloc_vcycle_refusals_without_a_gpu(lib):
     assert b"mg_vcycle_noalloc holds" in lib.mg_last_error()
     lib.mg_destroy(h)
     assert lib.mg_vcycle_noalloc(None, dummy, dummy, None) == mgir.MG_ERR_ARG
+
+
+def test_postponed_updates_are_optional(lib):
+    """defer_update 0 adds room for a ring of eight on large grids of narrow formats; -1 takes none (also on batches
+    and columns, where other depths are refused), and below that is refused; without a ring the sizes are the same."""
+    def size(setup, prec, defer, *args):
+        h, o, nb = ctypes.c_void_p(), mgir.default_options(), ctypes.c_size_t()
+        assert o.defer_update == 0
+        o.defer_update = defer
+        o.residual_scaling = int(prec != "f64")
+        arr = (ctypes.c_int * 12)(*[mgir.PREC[prec]] * 12)
+        st = setup(ctypes.byref(h), *args, arr, ctypes.byref(o))
+        if st != mgir.MG_OK:
+            return st
+        try:
+            assert lib.mg_workspace_size(h, ctypes.byref(nb)) == mgir.MG_OK
+            return nb.value
+        finally:
+            lib.mg_destroy(h)
+
+    slot = (255 + 3) * 256 * 256  # padded points of 255^3
+    for prec, esize in (("f16", 2), ("bf16", 2), ("f32", 4)):
+        a, b, c = (size(lib.mg_setup, prec, d, 3, 255, 0) for d in (-1, 0, 8))
+        assert b == c and 0 <= b - a - 8 * slot * esize <= 1024, prec
+    for dim, n, prec in ((3, 255, "f64"), (3, 127, "f16"), (2, 2047, "f16"), (2, 255, "f64")):
+        assert size(lib.mg_setup, prec, -1, dim, n, 0) == size(lib.mg_setup, prec, 0, dim, n, 0)
+    assert size(lib.mg_setup, "f16", -2, 3, 255, 0) == mgir.MG_ERR_ARG
+    sizes = (ctypes.c_int * 3)(63, 31, 63)
+    for setup, args in ((lib.mg_setup_batched, (3, 3, sizes)), (lib.mg_setup_multi, (3, 63, 8))):
+        assert size(setup, "f16", -1, *args) <= size(setup, "f16", 0, *args)  # (no rings without a GPU)
+        assert size(setup, "f64", -1, *args) == size(setup, "f64", 0, *args)
+        for d in (-2, 4):
+            assert size(setup, "f16", d, *args) == mgir.MG_ERR_ARG
