@@ -421,7 +421,7 @@ typedef enum {
                                of n >= 511 updating u in every step, else 0; the
                                autotuner times both.  Not used when nu2 < 2.
                                Reading returns whether it is in use and its shape. */
-    MG_SHAPE_FUSE_SR = 8    /* 3-D, level l below the base: {on (0|1)[, tyc, zcc[, lds16]]}.  When
+    MG_SHAPE_FUSE_SR = 8,   /* 3-D, level l below the base: {on (0|1)[, tyc, zcc[, lds16]]}.  When
                                on, the level's first pre-smoothing (two sweeps from zero)
                                and the residual + restriction of its result run as one
                                kernel (same result).  Level 0: the finest level inside
@@ -438,6 +438,18 @@ typedef enum {
                                fit a CU; three values set lds16 = 0.  Reading returns
                                whether it is in use and its shape (lds16 as a fourth value
                                when nparams >= 4). */
+    MG_SHAPE_FUSE_LEVEL = 9 /* level l below the base, both discretisations: {on (0|1)}.
+                               When on (the default), the level runs the fused kernels that
+                               take no shape, where they apply (same result).  2-D, pitch a
+                               multiple of 4, nu1 and nu2 up to 3, not into a rescaled
+                               level: pre-smoothing, residual and restriction in one kernel,
+                               prolongation and post-smoothing in another, on level 0 inside
+                               ir_solve with the refinement update.  3-D finite differences,
+                               pitch up to 64 (FP16 and FP32: 128): the prolongation and the
+                               first two post-sweeps.  Setting a shape of a kernel that they
+                               replace on that level (2-D: any; 3-D: STENCIL, SWEEP, PROLONG)
+                               turns them off, so that the kernel with that shape runs.
+                               Reading returns whether they apply and are on. */
 } mg_shape_kind_t;
 /* Q1 handles: the levels stored in a 2-byte format on a 3-D grid of pitch a
  * multiple of 4 run their sweep, their residual (ahead of the restriction) and,
@@ -450,7 +462,7 @@ typedef enum {
  * The residual runs fused with its restriction (the fine residual kept in LDS,
  * bitwise the same coarse b): its shape takes even ty and zc and (ty + 3) P / 4
  * threads; {ty, zc, 1} runs residual and restriction as two kernels instead.
- * The other kinds return MG_ERR_STATE.  opt.autotune times these shapes per
+ * The other kinds but MG_SHAPE_FUSE_LEVEL return MG_ERR_STATE.  opt.autotune times these shapes per
  * level and kernel against the built-in one (cached as for finite differences).
  * Reading returns the {ty, zc} in use, {0, 0} on levels without such kernels. */
 mg_status_t mg_set_shape(mg_handle h, int level, int kind, const int *params, int nparams);

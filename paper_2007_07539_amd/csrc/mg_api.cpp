@@ -51,7 +51,9 @@ struct LevelPlan {
     size_t off_cg = 0;     // CG vectors of a multi-point base level
     // fused first smoothing + restriction from the stored b (levels >= 1)
     bool fsr_on = true, fsr = false;
-    bool p2 = true;  // prolongation + two sweeps as one kernel where it applies (no shape of either set by hand)
+    // the fused kernels without a shape of their own, where they apply (MG_SHAPE_FUSE_LEVEL): the tiles of
+    // a 2-D level, prolongation + two sweeps of a 3-D one; setting a shape of what they replace turns them off
+    bool fuse = true;
     RShape fsrsh{8, 2, 16, 3};
     bool rescale = false;  // restrictions into this level rescale (half-precision level, rescale_half)
     size_t off_t = 0;      // its restricted residual / scaled correction in the finer accumulator format
@@ -645,8 +647,16 @@ int tail_level(const mg_ctx *h, int first) {
 
 // Whether level l of a 2-D grid runs its fused tile kernels (mg_tile2d.hip).
 bool tile2(const mg_ctx *h, int l) {
-    return h->dim == 2 && l + 1 < h->nl && !h->lv[l + 1].rescale &&
+    return h->dim == 2 && l + 1 < h->nl && h->lv[l].fuse && !h->lv[l + 1].rescale &&
            tile2d_ok(h->lv[l].P, h->opt.nu1, h->opt.nu2);
+}
+
+// Whether level l of a 3-D grid runs its prolongation and two of `sweeps`
+// post-sweeps as one kernel.
+bool prolong2(const mg_ctx *h, int l, int sweeps) {
+    const LevelPlan &L = h->lv[l];
+    return h->dim == 3 && !h->q1 && l + 1 < h->nl && L.fuse && !h->lv[l + 1].rescale && sweeps >= 2 &&
+           prolong_sweep2_ok(L.P, L.prec);
 }
 
 Tile2dArgs tile2_args(mg_ctx *h, int l) {
@@ -705,8 +715,7 @@ hipError_t enq_up(mg_ctx *h, hipStream_t st, int l, const void *rhs, bool skip) 
     if (skip && h->fused2) return hipSuccess;
     if (tile2(h, l)) return enq_tile2_up(h, st, l, rhs);
     LevelPlan &L = h->lv[l], &C = h->lv[l + 1];
-    if (h->dim == 3 && !h->q1 && !C.rescale && L.p2 && h->opt.nu2 - (skip ? 1 : 0) >= 2 &&
-        prolong_sweep2_ok(L.P, L.prec)) {
+    if (prolong2(h, l, h->opt.nu2 - (skip ? 1 : 0))) {
         const int cur = h->cur[l];
         RUN(h, st, "prolong_sweep2", l, (double)points(3, L.n) * 3 * sb(L.prec) + (double)points(3, C.n) * sb(C.prec),
             launch_prolong_sweep2(L.prec, C.prec, L.P, cbuf(h, l, cur), cbuf(h, l + 1, h->cur[l + 1]), rhs,
@@ -2148,6 +2157,14 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
 mg_status_t mg_set_shape(mg_handle h, int level, int kind, const int *p, int np) {
     if (!h || !p) return fail(MG_ERR_ARG, "null argument");
     if (h->batched || h->nrhs) return fail(MG_ERR_STATE, "not available on a batched or many-right-hand-side handle");
+    if (kind == MG_SHAPE_FUSE_LEVEL) {
+        if (level < 0 || level >= h->nl - 1) return fail(MG_ERR_ARG, "level %d has no fused kernels", level);
+        if (np != 1 || (p[0] != 0 && p[0] != 1)) return fail(MG_ERR_ARG, "the level's fused kernels: {on (0|1)}");
+        h->lv[level].fuse = p[0] != 0;
+        set_fused(h, h->fused);
+        drop_graph(h);
+        return MG_OK;
+    }
     if (h->q1) {
         // the LDS-staged kernels' {ty, zc}: the sweep (MG_SHAPE_SWEEP), the
         // residual (MG_SHAPE_RESTRICT), the update (MG_SHAPE_UPDATE, level 0)
@@ -2236,12 +2253,9 @@ mg_status_t mg_set_shape(mg_handle h, int level, int kind, const int *p, int np)
         if (kind == MG_SHAPE_UPDATE) {
             if (stencil_blocks(D, L.P, s) > h->max_parts) return fail(MG_ERR_ARG, "too many blocks");
             L.osh = s;
-            set_fused(h, h->fused);
         } else if (kind == MG_SHAPE_STENCIL) {
             L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = s;
-            L.p2 = false;
         } else {
-            L.p2 = L.p2 && kind == MG_SHAPE_SMOOTH;
             L.shs[kind == MG_SHAPE_SMOOTH ? SH_SMOOTH : kind == MG_SHAPE_SWEEP ? SH_SWEEP : SH_PROLONG] = s;
         }
     } else if (kind == MG_SHAPE_RESTRICT) {
@@ -2254,6 +2268,9 @@ mg_status_t mg_set_shape(mg_handle h, int level, int kind, const int *p, int np)
     } else {
         return fail(MG_ERR_ARG, "unknown shape kind %d", kind);
     }
+    // the kernel whose shape was asked for is the one that runs
+    L.fuse = L.fuse && D == 3 && (kind == MG_SHAPE_SMOOTH || kind == MG_SHAPE_RESTRICT || kind == MG_SHAPE_UPDATE);
+    set_fused(h, h->fused);
     drop_graph(h);
     return MG_OK;
 }
@@ -2270,6 +2287,12 @@ mg_status_t mg_get_shape(mg_handle h, int level, int kind, int *p, int np) {
     if (kind == MG_SHAPE_TAIL) {
         if (np < 1) return fail(MG_ERR_ARG, "too few values");
         p[0] = h->tail_on ? 1 : 0;
+        return MG_OK;
+    }
+    if (kind == MG_SHAPE_FUSE_LEVEL) {
+        if (level < 0 || level >= h->nl - 1) return fail(MG_ERR_ARG, "level %d has no fused kernels", level);
+        if (np < 1) return fail(MG_ERR_ARG, "too few values");
+        p[0] = tile2(h, level) || prolong2(h, level, h->opt.nu2) ? 1 : 0;
         return MG_OK;
     }
     if (h->q1) {

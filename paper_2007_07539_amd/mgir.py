@@ -41,7 +41,7 @@ EXPORTS = ("mg_default_options", "mg_setup", "mg_workspace_size", "mg_bind_works
            "mg_setup_batched", "ir_solve_batched", "mg_instances", "mg_setup_multi", "ir_solve_multi",
            "mg_rhs_count", "mg_alpha_shift", "mg_vcycle_noalloc", "mg_get_instance_shape")
 SHAPE_STENCIL, SHAPE_RESTRICT, SHAPE_UPDATE, SHAPE_SMOOTH, SHAPE_SWEEP, SHAPE_PROLONG, SHAPE_TAIL, SHAPE_FUSE, \
-    SHAPE_FUSE_SR = 0, 1, 2, 3, 4, 5, 6, 7, 8
+    SHAPE_FUSE_SR, SHAPE_FUSE_LEVEL = 0, 1, 2, 3, 4, 5, 6, 7, 8, 9
 
 
 class MgError(RuntimeError):
@@ -287,9 +287,9 @@ class Solver:
         ({ty, zc}) on a Q1 handle)."""
         arr = (ctypes.c_int * 7)()
         _check(self.lib.mg_get_shape(self._h, level, kind, arr, 7), "mg_get_shape")
-        if count is None and getattr(self, "disc", "fd") == "q1":
+        if count is None and kind != SHAPE_FUSE_LEVEL and getattr(self, "disc", "fd") == "q1":
             count = 2
-        n = {SHAPE_RESTRICT: 4, SHAPE_TAIL: 1, SHAPE_FUSE: 5, SHAPE_FUSE_SR: 3}.get(kind, 6) if count is None else count
+        n = {SHAPE_RESTRICT: 4, SHAPE_TAIL: 1, SHAPE_FUSE_LEVEL: 1, SHAPE_FUSE: 5, SHAPE_FUSE_SR: 3}.get(kind, 6) if count is None else count
         return list(arr[:n])
 
     def profile_step(self, stream=None, cap: int = 512):

@@ -85,3 +85,70 @@ def test_autotuned_tiles_have_the_same_history(n, name, scaling, tmp_path, monke
         u, r = mgir.Solver(2, n, prec, residual_scaling=scaling, autotune=True).solve(b)
         assert r.iterations == r0.iterations and torch.equal(u, u0), fresh
         assert np.allclose(r.history, r0.history, rtol=1e-8, atol=0.0), (fresh, r.history, r0.history)
+
+
+def _names(s, level):
+    return {r[0] for r in s.profile_step() if r[1] == level} - {"norm_finalize", "defer_flush"}
+
+
+TILES = {"smooth_restrict", "prolong_smooth", "prolong_smooth_update", "prolong_smooth_update_defer"}
+
+
+@pytest.mark.parametrize("n,disc,name", [(255, "fd", "f16"), (255, "fd", "f64"), (191, "q1", "f16"), (575, "q1", "f64")])
+def test_tiles_off_and_shapes_in_effect(n, disc, name):
+    """A level's tile kernels can be turned off and on again, and a shape set for a
+    2-D level is the shape of a kernel that runs: with the same u, V-cycle and
+    correction, and the norms in another order of summation (n^2 eps, far below 1e-9)."""
+    print(f"tiles off n={n} {disc} {name}", flush=True)
+    prec = W.precision_map(name, mgir.full_levels(n))
+    kw = dict(disc=disc, residual_scaling=name != "f64", max_iter=3, rtol=0.0)
+    b = torch.from_numpy(W.uniform_rhs(2, n, seed=7)).to("cuda")
+    bh = b.to(mgir.TORCH_DTYPE[prec[0]])
+    s = mgir.Solver(2, n, prec, **kw)
+    u0, r0 = s.solve(b, check=False)
+    c0 = s.vcycle(bh)
+    on = _names(s, 0)
+    assert on <= TILES and s.get_shape(0, mgir.SHAPE_FUSE_LEVEL) == [1]
+
+    def check(off):
+        assert s.get_shape(0, mgir.SHAPE_FUSE_LEVEL) == [0 if off else 1]
+        u, r = s.solve(b, check=False)
+        assert torch.equal(u, u0) and np.allclose(r.history, r0.history, rtol=1e-9, atol=0.0)
+        assert torch.equal(s.vcycle(bh), c0)
+        assert (not _names(s, 0) & TILES) if off else _names(s, 0) == on
+        assert _names(s, 1) <= TILES
+
+    s.set_shape(0, mgir.SHAPE_FUSE_LEVEL, [0])
+    check(True)
+    s.set_shape(0, mgir.SHAPE_FUSE_LEVEL, [1])
+    check(False)
+    if disc == "fd":
+        for kind, shape in ((mgir.SHAPE_SMOOTH, [4, 5, 128, 0, 0]), (mgir.SHAPE_SWEEP, [8, 3, 256, 1, 0]),
+                            (mgir.SHAPE_PROLONG, [4, 16, 64, 1, 0]), (mgir.SHAPE_RESTRICT, [4, 1, 7, 0]),
+                            (mgir.SHAPE_UPDATE, [4, 6, 256, 1, 0]), (mgir.SHAPE_STENCIL, [4, 2, 256, 1, 0])):
+            s.set_shape(0, kind, shape)
+            check(True)
+            s.set_shape(0, mgir.SHAPE_FUSE_LEVEL, [1])
+        check(False)
+
+
+def test_prolong_two_sweeps_off_and_on():
+    """3-D: a shape of the sweeps turns the fused prolongation + two sweeps of that
+    level off, a shape of another kernel does not, and it can be turned on again."""
+    n = 63
+    print("prolong + 2 sweeps off and on", flush=True)
+    s = mgir.Solver(3, n, W.precision_map("f16", mgir.full_levels(n)))
+    s.solve(torch.from_numpy(W.uniform_rhs(3, n, seed=8)).to("cuda"))
+    fused = lambda: "prolong_sweep2" in _names(s, 1)
+    assert fused() and s.get_shape(1, mgir.SHAPE_FUSE_LEVEL) == [1]
+    for kind, off in ((mgir.SHAPE_SMOOTH, False), (mgir.SHAPE_RESTRICT, False), (mgir.SHAPE_SWEEP, True),
+                      (mgir.SHAPE_PROLONG, True), (mgir.SHAPE_STENCIL, True)):
+        s.set_shape(1, kind, s.get_shape(1, kind))
+        assert fused() != off and s.get_shape(1, mgir.SHAPE_FUSE_LEVEL) == [1 - off], kind
+        s.set_shape(1, mgir.SHAPE_FUSE_LEVEL, [1])
+        assert fused()
+    for bad in ([2], [1, 1]):
+        with pytest.raises(mgir.MgError):
+            s.set_shape(1, mgir.SHAPE_FUSE_LEVEL, bad)
+    with pytest.raises(mgir.MgError):
+        s.set_shape(s.nlevels - 1, mgir.SHAPE_FUSE_LEVEL, [1])
