@@ -93,6 +93,7 @@ struct mg_ctx {
     char *ws = nullptr;
     size_t ws_bytes = 0;
     int cur[32] = {0};
+    int cur_step[32] = {0};  // ... as the captured cycle of a refinement step leaves them
     double *host_scal = nullptr;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -1013,6 +1014,7 @@ mg_status_t ensure_graph(mg_ctx *h) {
         for (int part = 0; part < 2; ++part) {
             HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
             hipError_t e = part == 0 ? enq_cycle(h, h->cap_stream) : enq_update(h, h->cap_stream);
+            if (part == 0) std::memcpy(h->cur_step, h->cur, sizeof h->cur);
             hipGraph_t g = nullptr;
             hipError_t e2 = hipStreamEndCapture(h->cap_stream, &g);
             if (e != hipSuccess) {
@@ -2084,6 +2086,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
     double rel = h->host_scal[2] / nb;
     auto launch = [&](bool cycle) -> hipError_t {
         if (graph) {
+            if (cycle) std::memcpy(h->cur, h->cur_step, sizeof h->cur);
             if (h->rpar) return hipGraphLaunch(cycle ? h->gexec_p1 : h->gexec2_p1, st);
             return hipGraphLaunch(cycle ? h->gexec : h->gexec2, st);
         }

@@ -71,3 +71,18 @@ def test_cycles_compose_with_fusions_and_graphs(dev, name, n):
     u2, r2 = mgir.Solver(3, n, prec, cycles_per_step=2, use_graph=False).solve(b)
     assert r2.iterations == ref_r.iterations and torch.equal(u2, ref_u)
     assert r2.history == ref_r.history
+
+
+@pytest.mark.parametrize("n,name,nu2", [(31, "f16", 3), (63, "f32", 2), (127, "f64", 2)])
+def test_level_vectors_after_a_cycle_between_solves(n, name, nu2):
+    """3-D: the correction read after a solve is that of the solve, whatever ran on the handle before it."""
+    print(f"3-D level vectors n={n} {name} nu2={nu2}", flush=True)
+    prec = W.precision_map(name, mgir.full_levels(n))
+    b = torch.from_numpy(W.uniform_rhs(3, n, seed=10)).to("cuda")
+    s = mgir.Solver(3, n, prec, nu2=nu2, residual_scaling=name != "f64", max_iter=3, rtol=0.0)
+    s.solve(b, check=False)
+    c = [s.read(l, mgir.BUF_COR) for l in range(s.nlevels)]
+    s.vcycle(torch.ones_like(b).to(mgir.TORCH_DTYPE[prec[0]]))
+    s.solve(b, check=False)
+    for l in range(s.nlevels):
+        assert torch.equal(s.read(l, mgir.BUF_COR), c[l]), l
