@@ -353,9 +353,9 @@ mg_status_t mg_level_write(mg_handle h, int level, mg_buffer_t buf, const void *
                            mg_prec_t src_prec, void *stream);
 
 /* Copy a level buffer out to a dense device array in format dst_prec
- * (rounding to nearest even if narrower).  Async.  After ir_solve, level 0's
- * correction is that before the sweeps which the fused update of the last step
- * applied (3-D: MG_SHAPE_FUSE; 2-D: all post-smoothing). */
+ * (rounding to nearest even if narrower).  Async.  After ir_solve on a 3-D
+ * handle with the fused update in use (MG_SHAPE_FUSE), level 0's correction is
+ * that before its last post-smoothing sweep, which that kernel applies. */
 mg_status_t mg_level_read(mg_handle h, int level, mg_buffer_t buf, void *dst, mg_prec_t dst_prec,
                           void *stream);
 
@@ -424,8 +424,10 @@ typedef enum {
     MG_SHAPE_FUSE_SR = 8,   /* 3-D, level l below the base: {on (0|1)[, tyc, zcc[, lds16]]}.  When
                                on, the level's first pre-smoothing (two sweeps from zero)
                                and the residual + restriction of its result run as one
-                               kernel (same result).  Level 0: the finest level inside
-                               ir_solve, from the scaled residual (on by default).  Level
+                               kernel (same result).  Level 0 (on by default): the finest level,
+                               in ir_solve from the scaled residual, in mg_vcycle from its
+                               right-hand side; the SMOOTH and RESTRICT shapes of level 0
+                               are those of the kernels that run when it is off.  Level
                                l >= 1: that level, from its stored right-hand side (off by
                                default).  The autotuner keeps it only where it is faster.
                                Needs nu1 = 2 and P/8 dividing 64 (an FP64 level: one

@@ -94,6 +94,10 @@ struct mg_ctx {
     size_t ws_bytes = 0;
     int cur[32] = {0};
     int cur_step[32] = {0};  // ... as the captured cycle of a refinement step leaves them
+    // fused2: which right-hand side level 0's correction awaits its prolongation
+    // and post-smoothing from, which the update did on its own (finish_finest):
+    // its own (0), the first or second residual array (1, 2); -1: none
+    int open_rhs = -1;
     double *host_scal = nullptr;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -898,6 +902,20 @@ hipError_t enq_cycle(mg_ctx *h, hipStream_t st) {
     return hipSuccess;
 }
 
+// The finest level's correction, as a cycle without the fused 2-D update
+// leaves it: for those who look at it after a refinement step.
+hipError_t finish_finest(mg_ctx *h, hipStream_t st) {
+    if (h->open_rhs < 0) return hipSuccess;
+    const void *rhs = h->open_rhs == 0 ? bbuf(h, 0) : (const void *)(h->ws + (h->open_rhs == 1 ? h->off_R : h->off_R2));
+    h->open_rhs = -1;
+    return enq_tile2_up(h, st, 0, rhs);
+}
+
+// Host bookkeeping when a step's V-cycles have been queued.
+void after_cycle(mg_ctx *h) {
+    if (h->fused2) h->open_rhs = finest_alias(h) ? 1 + h->rpar : 0;
+}
+
 // The update part: u, r, norms, alpha, the norms to the host (with the fused
 // form, also the last post-smoothing sweep of the finest level).
 hipError_t enq_update(mg_ctx *h, hipStream_t st) {
@@ -1009,6 +1027,7 @@ mg_status_t ensure_graph(mg_ctx *h) {
     drop_graph(h);
     if (!h->cap_stream) HIPCHK(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
     const int keep = h->rpar;
+    h->open_rhs = -1;  // (capturing moves the roles of the level vectors)
     for (int par = 0; par < (two ? 2 : 1); ++par) {
         h->rpar = par;
         for (int part = 0; part < 2; ++part) {
@@ -1816,6 +1835,7 @@ mg_status_t mg_bind_workspace(mg_handle h, void *dev_ptr, size_t bytes, void *st
     h->ws_bytes = bytes;
     const bool full = bytes >= h->ws_need;
     h->rpar = h->pending = 0;
+    h->open_rhs = -1;
     h->defer = full || h->opt.defer_update > 0 ? h->defer_plan : 0;
     for (auto &I : h->inst) I.defer = full ? I.defer_plan : 0;
     if (h->off_R2_opt) h->off_R2 = full ? h->off_R2_opt : 0;
@@ -1897,6 +1917,7 @@ mg_status_t mg_level_write(mg_handle h, int level, mg_buffer_t buf, const void *
     if (!valid_prec(src_prec)) return fail(MG_ERR_PREC, "src_prec %d", (int)src_prec);
     void *p;
     int prec;
+    if (level == 0 || level == 1) HIPCHK(finish_finest(h, static_cast<hipStream_t>(stream)));
     if ((s = buffer_of(h, level, buf, &p, &prec)) != MG_OK) return s;
     HIPCHK(launch_pack(h->dim, src_prec, prec, h->lv[level].n, h->lv[level].P, src, p,
                        static_cast<hipStream_t>(stream)));
@@ -1911,6 +1932,7 @@ mg_status_t mg_level_read(mg_handle h, int level, mg_buffer_t buf, void *dst, mg
     if (!valid_prec(dst_prec)) return fail(MG_ERR_PREC, "dst_prec %d", (int)dst_prec);
     void *p;
     int prec;
+    if (level == 0 && buf == MG_BUF_COR) HIPCHK(finish_finest(h, static_cast<hipStream_t>(stream)));
     if ((s = buffer_of(h, level, buf, &p, &prec)) != MG_OK) return s;
     HIPCHK(launch_unpack(h->dim, prec, dst_prec, h->lv[level].n, h->lv[level].P, p, dst,
                          static_cast<hipStream_t>(stream)));
@@ -1925,6 +1947,7 @@ mg_status_t mg_stage(mg_handle h, mg_stage_t stage, int level, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool base = level == h->nl - 1;
     hipError_t e = hipSuccess;
+    HIPCHK(finish_finest(h, st));
     switch (stage) {
     case MG_STAGE_SMOOTH_FIRST:
         if (base) return fail(MG_ERR_ARG, "the base level is solved, not smoothed");
@@ -1964,6 +1987,7 @@ mg_status_t mg_vcycle(mg_handle h, const void *b, void *c, void *stream) {
     if (!b || !c) return fail(MG_ERR_ARG, "null argument");
     hipStream_t st = static_cast<hipStream_t>(stream);
     LevelPlan &L = h->lv[0];
+    h->open_rhs = -1;
     HIPCHK(launch_pack(h->dim, L.prec, L.prec, L.n, L.P, b, bbuf(h, 0), st));
     HIPCHK(enq_vcycle(h, st, RHS_B));
     HIPCHK(launch_unpack(h->dim, L.prec, L.prec, L.n, L.P, cbuf(h, 0, h->cur[0]), c, st));
@@ -2038,6 +2062,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
 
     // ||b||_2 first (and the initial residual when u starts at zero)
     h->rpar = 0;
+    if (h->open_rhs > 0) h->open_rhs = -1;  // (its right-hand side is overwritten)
     h->pending = 0;
     h->u_zero = false;
     if (h->defer) HIPCHK(launch_fill_zero(h->ws + h->off_dctr, 16, st));
@@ -2086,11 +2111,23 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
     double rel = h->host_scal[2] / nb;
     auto launch = [&](bool cycle) -> hipError_t {
         if (graph) {
-            if (cycle) std::memcpy(h->cur, h->cur_step, sizeof h->cur);
+            if (cycle) {
+                std::memcpy(h->cur, h->cur_step, sizeof h->cur);
+                after_cycle(h);
+            }
             if (h->rpar) return hipGraphLaunch(cycle ? h->gexec_p1 : h->gexec2_p1, st);
             return hipGraphLaunch(cycle ? h->gexec : h->gexec2, st);
         }
-        return cycle ? enq_cycle(h, st) : enq_update(h, st);
+        if (!cycle) return enq_update(h, st);
+        const hipError_t e = enq_cycle(h, st);
+        after_cycle(h);
+        return e;
+    };
+    // r = b - A u, with u out.  A queued cycle's right-hand side may be r: the
+    // new one then goes to the other array.
+    auto true_resid = [&]() -> hipError_t {
+        if (h->open_rhs == 1 + h->rpar) h->rpar ^= 1;
+        return finest_resid(h, b, Ubuf(h), Rbuf(h), u, st);
     };
     for (;;) {
         const double rn = h->host_scal[2];
@@ -2106,7 +2143,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
             // only wrote level vectors and is discarded)
             cycle_queued = false;
             HIPCHK(enq_flush(h, st));
-            HIPCHK(finest_resid(h, b, Ubuf(h), Rbuf(h), u, st));
+            HIPCHK(true_resid());
             HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st, nullptr, h->host_scal));
             HIPCHK(hipStreamSynchronize(st));
             recursive = false;
@@ -2149,7 +2186,7 @@ mg_status_t ir_solve(mg_handle h, const double *b, double *u, mg_stats_t *stats,
     if (cycle_queued) HIPCHK(hipStreamSynchronize(st));
     // final: recompute the true residual and copy u out
     HIPCHK(enq_flush(h, st));
-    HIPCHK(finest_resid(h, b, Ubuf(h), Rbuf(h), u, st));
+    HIPCHK(true_resid());
     HIPCHK(launch_finalize(part(h), fparts, scal(h), scaling, st, nullptr, h->host_scal));
     HIPCHK(hipStreamSynchronize(st));
     rel = h->host_scal[2] / nb;
@@ -2373,6 +2410,7 @@ mg_status_t mg_profile_step(mg_handle h, void *stream, int cap, int *count, cons
     if (e == hipSuccess && !grouped) {
         // a postponed update is added to u at once, so that the step leaves
         // the state a real one would after its flush (timed as defer_flush)
+        after_cycle(h);
         e = after_update(h, st);
         if (e == hipSuccess) e = enq_flush(h, st);
     }

@@ -152,3 +152,37 @@ def test_prolong_two_sweeps_off_and_on():
             s.set_shape(1, mgir.SHAPE_FUSE_LEVEL, bad)
     with pytest.raises(mgir.MgError):
         s.set_shape(s.nlevels - 1, mgir.SHAPE_FUSE_LEVEL, [1])
+
+
+@pytest.mark.parametrize("n,disc,name,kw", [
+    (127, "fd", "f16", {}), (255, "fd", "f64", {}), (255, "fd", "f64", dict(use_graph=False, cycles_per_step=2)),
+    (511, "fd", "hsd", dict(nu2=3)), (131, "q1", "f16", dict(defer_update=3)), (191, "q1", "f64", {}),
+    (191, "q1", "f64", dict(nu1=1, nu2=1))])
+def test_level_vectors_after_a_solve(n, disc, name, kw):
+    """After a solve by the tile kernels, whose update does the finest level's
+    prolongation and post-smoothing on its own, the level vectors are those of the
+    stage kernels, also where the next step's cycle was queued before the solve
+    stopped, after a V-cycle in between, and read twice."""
+    print(f"2-D level vectors after a solve n={n} {disc} {name} {kw}", flush=True)
+    prec = W.precision_map(name, mgir.full_levels(n))
+    b = torch.from_numpy(W.uniform_rhs(2, n, seed=9)).to("cuda")
+    bh = torch.ones_like(b).to(mgir.TORCH_DTYPE[prec[0]])
+    for stop in (dict(max_iter=1), dict(max_iter=4, rtol=0.0), dict(rtol=1e-2), dict()):
+        got, want = (mgir.Solver(2, n, prec, disc=disc, residual_scaling=name != "f64", **stop, **kw) for _ in range(2))
+        for l in range(want.nlevels - 1):
+            want.set_shape(l, mgir.SHAPE_FUSE_LEVEL, [0])
+        for again in range(2):
+            u, r = got.solve(b, check=False)
+            v, q = want.solve(b, check=False)
+            assert r.iterations == q.iterations and torch.equal(u, v)
+            for l in range(got.nlevels):
+                for buf in (mgir.BUF_COR, mgir.BUF_RHS, mgir.BUF_COR):
+                    if l == 0 and buf == mgir.BUF_RHS and name == "f64":
+                        continue  # (the residual itself)
+                    assert torch.equal(got.read(l, buf), want.read(l, buf)), (stop, again, l, buf)
+            for buf in (mgir.BUF_RES, mgir.BUF_SOL):
+                assert torch.equal(got.read(0, buf), want.read(0, buf)), (stop, again, buf)
+            got.stage(mgir.STAGE_SWEEP, 0)  # (on the correction; for f64 with whatever right-hand side is stored)
+            want.stage(mgir.STAGE_SWEEP, 0)
+            assert torch.equal(got.read(0, mgir.BUF_COR), want.read(0, mgir.BUF_COR))
+            assert torch.equal(got.vcycle(bh), want.vcycle(bh))
