@@ -1242,8 +1242,8 @@ void cache_write(const std::string &key, const std::vector<int> &v) {
 }
 
 // The tuned state as integers: per level the three stencil shapes, the
-// update shape, the restriction shape and the coarse fused form; then the
-// finest-level fused forms.
+// update shape, the restriction shape, the coarse fused form and whether the
+// fused kernels without a shape are used; then the finest-level fused forms.
 void tune_state(const mg_ctx *h, std::vector<int> &v) {
     auto sh = [&](const Shape &s) { v.insert(v.end(), {s.V, s.zc, s.bs, s.xcd, s.ty, s.dp, s.sg}); };
     auto rs = [&](const RShape &r) { v.insert(v.end(), {r.V, r.tyc, r.zcc, r.pipe}); };
@@ -1254,6 +1254,7 @@ void tune_state(const mg_ctx *h, std::vector<int> &v) {
         rs(L.rsh);
         rs(L.fsrsh);
         v.push_back(L.fsr ? 1 : 0);
+        v.push_back(L.fuse ? 1 : 0);
     }
     rs(h->srsh);
     v.push_back(h->fused_sr ? 1 : 0);
@@ -1265,7 +1266,7 @@ void tune_state(const mg_ctx *h, std::vector<int> &v) {
 // Apply a state read from the cache; false (and nothing changed) when any
 // shape is not valid for this handle.
 bool apply_tune_state(mg_ctx *h, const std::vector<int> &v) {
-    const size_t per = 4 * 7 + 4 + 4 + 1, need = per * (h->nl - 1) + 4 + 1 + 7 + 1 + 1;
+    const size_t per = 4 * 7 + 4 + 4 + 1 + 1, need = per * (h->nl - 1) + 4 + 1 + 7 + 1 + 1;
     if (v.size() != need) return false;
     size_t i = 0;
     auto sh = [&]() {
@@ -1288,6 +1289,7 @@ bool apply_tune_state(mg_ctx *h, const std::vector<int> &v) {
         if (!restrict_ok(h, L, L.rsh)) return false;
         L.fsrsh = rs();
         fsr[l] = v[i++] != 0;
+        L.fuse = L.fuse && v[i++] != 0;
     }
     const RShape srsh = rs();
     const bool fused_sr = v[i++] != 0;
@@ -1326,17 +1328,25 @@ mg_status_t autotune(mg_ctx *h, hipStream_t st) {
     return s;
 }
 
+// Only shapes that a launch reads are timed: not those of levels inside the
+// fused coarse end, nor (but for the way down of a further cycle of a step) of
+// 2-D levels that run by tiles.
 mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
     const int D = h->dim;
+    const bool more_cycles = h->opt.cycles_per_step > 1;
+    const int lt = tail_level(h, more_cycles ? 1 : 0);
     for (int l = 0; l + 1 < h->nl; ++l) {
         LevelPlan &L = h->lv[l];
-        if (L.P < 8) continue;
+        const bool in_tail = l >= lt, tiles = !in_tail && tile2(h, l);
+        const bool warm = l == 0 && more_cycles;  // its sweeps and restriction are launches of their own
+        if (l > 0 && (L.P < 8 || in_tail || tiles)) continue;
         // each smoothing-family kernel separately; on the finest level the
         // first pre-smoothing is timed in the form the refinement loop uses
         const bool scaled0 = l == 0 && !finest_alias(h);
         const void *b0 = (l == 0 && finest_alias(h)) ? (const void *)Rbuf(h) : bbuf(h, l);
         float fam_best[3] = {0.f, 0.f, 0.f};
         for (int fam = 0; fam < 3; ++fam) {
+            if (L.P < 8 || in_tail || (tiles && !(warm && fam == SH_SWEEP))) continue;
             float best = 1e30f;
             Shape bs = L.shs[fam];
             for (const Shape &s : stencil_candidates(h, L, false, fam == SH_PROLONG)) {
@@ -1356,15 +1366,30 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
             L.shs[fam] = bs;
             fam_best[fam] = best;
         }
+        // the prolongation and two sweeps in one kernel against the two kernels
+        float t_p2 = 0.f;
+        if (!in_tail && prolong2(h, l, h->opt.nu2)) {
+            t_p2 = time_ms(st, [&]() {
+                return launch_prolong_sweep2(L.prec, h->lv[l + 1].prec, L.P, cbuf(h, l, 1), cbuf(h, l + 1, 0), b0,
+                                             cbuf(h, l, 0), h->opt.omega, st);
+            }, 5);
+            L.fuse = t_p2 < fam_best[SH_PROLONG] + fam_best[SH_SWEEP];
+        }
+        // time of the way up with k post-sweeps
+        auto up = [&](int k) {
+            return prolong2(h, l, k) ? t_p2 + (k - 2) * fam_best[SH_SWEEP]
+                                     : fam_best[SH_PROLONG] + (k - 1) * fam_best[SH_SWEEP];
+        };
         // residual + restriction
         float best = 1e30f;
         RShape br = L.rsh;
+        const bool restricts = L.P >= 8 && !in_tail && (!tiles || warm);
         for (int V : {4, 8})
             for (int tyc : {1, 2, 3, 4, 5, 7})
                 for (int zcc : {2, 4, 8, 16, 32})
                     for (int pipe : {0, 1, 2, 3, 4}) {
                     RShape r{V, tyc, zcc, pipe};
-                    if (!restrict_ok(h, L, r)) continue;
+                    if (!restricts || !restrict_ok(h, L, r)) continue;
                     const float t = time_ms(st, [&]() {
                         return launch_restrict(D, L.prec, h->lv[l + 1].prec, L.P, bbuf(h, l), cbuf(h, l, 0),
                                                bbuf(h, l + 1), r, st);
@@ -1372,7 +1397,7 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
                     if (t < best) best = t, br = r;
                 }
         L.rsh = br;
-        if (l == 0 ? fusion_sr_possible(h) : fusion_srb_possible(h, l)) {
+        if (restricts && (l == 0 ? fusion_sr_possible(h) : fusion_srb_possible(h, l))) {
             // the fused first smoothing + restriction against the two kernels
             float bf = 1e30f;
             RShape bsr = l == 0 ? h->srsh : L.fsrsh;
@@ -1422,7 +1447,7 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
                 set_fused_srb(h, l, win);
             }
         }
-        if (l == 0) {
+        if (l == 0 && L.P >= 8 && !h->fused2) {
             best = 1e30f;
             Shape bo = L.osh;
             const double hh = 1.0 / (double)(L.n + 1);
@@ -1460,7 +1485,8 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
                         }
                 h->fsh = bsu;
                 h->su_r = bsr;
-                set_fused(h, bf < best + fam_best[SH_SWEEP]);
+                // (in the coarse end a sweep more costs next to nothing)
+                set_fused(h, in_tail ? bf < best : up(h->opt.nu2 - 1) + bf < up(h->opt.nu2) + best);
             }
         }
     }
@@ -1504,7 +1530,7 @@ mg_status_t autotune_q1(mg_ctx *h, hipStream_t st) {
     const int D = h->dim;
     for (int l = 0; l + 1 < h->nl; ++l) {
         LevelPlan &L = h->lv[l];
-        if (!q1_lds_level(D, L.prec, L.n, L.P)) continue;
+        if (!q1_lds_level(D, L.prec, L.n, L.P) || l >= tail_level(h, h->opt.cycles_per_step > 1 ? 1 : 0)) continue;
         for (int k = 0; k < (l == 0 ? 3 : 2); ++k) {
             auto run = [&](const Q1Shape &q) -> hipError_t {
                 if (k == 0)

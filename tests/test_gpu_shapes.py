@@ -352,3 +352,37 @@ def test_fused_smooth_restrict_coarse_levels_bitwise(dev, name, n):
     u_off, r_off = s.solve(b64)
     assert r_off.iterations == r_on.iterations and torch.equal(u_off, u_on)
     assert r_off.history == r_on.history
+
+
+@pytest.mark.parametrize("dim,n,name,kw", [(2, 255, "f16", {}), (2, 255, "f16", dict(cycles_per_step=2)),
+                                           (2, 127, "f64", {}), (3, 63, "f16", {}), (3, 15, "f16", {})])
+def test_autotuner_times_what_runs(dev, dim, n, name, kw, tmp_path, monkeypatch):
+    """Shapes that no launch of the handle reads (levels in the fused coarse end, 2-D
+    levels that run by tiles) stay the built-in ones when a handle is tuned, whether
+    the fused prolongation is used is part of the choice, and the tuned and the
+    cached handle return the untuned one's iterates."""
+    print(f"autotuner {dim}-D n={n} {name} {kw}", flush=True)
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("MGIR_TUNE_CACHE", str(path))
+    m = mgir.full_levels(n)
+    prec = W.precision_map(name, m)
+    kw = dict(kw, residual_scaling=name != "f64", max_iter=4, rtol=0.0)
+    b = torch.from_numpy(W.uniform_rhs(dim, n, seed=12)).to(dev)
+    plain, tuned = mgir.Solver(dim, n, prec, **kw), mgir.Solver(dim, n, prec, autotune=True, **kw)
+    kinds = (mgir.SHAPE_SMOOTH, mgir.SHAPE_SWEEP, mgir.SHAPE_PROLONG, mgir.SHAPE_RESTRICT)
+    for l in range(m - 1):
+        if (n + 1) >> l <= (16 if dim == 3 else 64) or (dim == 2 and not (l == 0 and kw.get("cycles_per_step"))):
+            for k in kinds:
+                assert tuned.get_shape(l, k) == plain.get_shape(l, k), (l, k)
+    u = plain.solve(b, check=False)[0]
+    assert torch.equal(tuned.solve(b, check=False)[0], u)
+    key, ints = path.read_text().splitlines()[0].split("\t")
+    v = [int(x) for x in ints.split()]
+    per = 38  # integers per level, the last one whether its fused kernels are used
+    for l in range(m - 1):
+        assert v[per * l + per - 1] >= tuned.get_shape(l, mgir.SHAPE_FUSE_LEVEL)[0], l
+        v[per * l + per - 1] = 0
+    path.write_text(key + "\t" + " ".join(map(str, v)) + "\n")
+    off = mgir.Solver(dim, n, prec, autotune=True, **kw)
+    assert all(off.get_shape(l, mgir.SHAPE_FUSE_LEVEL) == [0] for l in range(m - 1))
+    assert torch.equal(off.solve(b, check=False)[0], u)
