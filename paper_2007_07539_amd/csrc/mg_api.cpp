@@ -2584,6 +2584,11 @@ TailArgs batched_tail_args(const mg_ctx *h, int i, int l) {
     return t;
 }
 
+// Whether a level runs its two pre-sweeps, residual and restriction as one kernel.
+bool batched_fsr(const mg_ctx *h, const LevelPlan &L) {
+    return h->opt.nu1 == 2 && smooth_restrict_ok(L.P, L.prec, L.fsrsh);
+}
+
 // Work items of one instance's stencil launch with shape s.
 int batched_stencil_blocks(int P, const Shape &s) {
     if (s.ty > 0) return ((P - 1 + s.ty - 1) / s.ty) * ((P - 1 + s.zc - 1) / s.zc);
@@ -2711,9 +2716,7 @@ void build_batched_plan(mg_ctx *h, char *base) {
         return p;
     };
     // fused first smoothing + restriction of a level (xsh: from the scaled residual)
-    auto sr_ok = [&](int i, int d) {
-        return h->opt.nu1 == 2 && smooth_restrict_ok(h->inst[i].lv[d].P, h->bprec[d], h->inst[i].lv[d].fsrsh);
-    };
+    auto sr_ok = [&](int i, int d) { return batched_fsr(h, h->inst[i].lv[d]); };
     std::vector<Pend> pend;
     for (int d = 0; d + 1 < h->Lmax; ++d) {
         const int pf = h->bprec[d];
@@ -2997,8 +3000,10 @@ hipError_t enq_batched_step(mg_ctx *h, hipStream_t st) { return enq_batched(h, s
 // of the class, in every instance, takes the class's shape, and the choice
 // only changes how the work is cut (every shape forms the same roundings).  A
 // candidate is timed as a whole batched refinement step with every instance
-// active, class by class from the largest pitch, stencil shape first, then the
-// restriction shape.
+// active, class by class from the largest pitch: the stencil shape, then that of
+// the restriction and of the fused smoothing + restriction, each only where a
+// launch reads it (the fused coarse ends read none).  The fused sweep + update
+// keeps its shape: its tiles set the order in which the norms are summed.
 struct BClass {
     int P, prec;
 };
@@ -3054,8 +3059,9 @@ mg_status_t batched_upload(mg_ctx *h) {
     return MG_OK;
 }
 
-// state: per class {P, prec, stencil V, zc, ty, restriction V, tyc, zcc, pipe}
-constexpr int kBClassInts = 9;
+// state: per class {P, prec, stencil V, zc, ty, restriction V, tyc, zcc, pipe,
+// fused smoothing + restriction tyc, zcc (0: not used there)}
+constexpr int kBClassInts = 11;
 
 bool apply_batched_state(mg_ctx *h, const std::vector<int> &v) {
     const std::vector<BClass> cl = batched_classes(h);
@@ -3068,6 +3074,7 @@ bool apply_batched_state(mg_ctx *h, const std::vector<int> &v) {
         const Shape sh{q[2], q[3], 256, 1, q[4]};
         const RShape rs{q[5], q[6], q[7], q[8]};
         if (!stencil_ok(h, probe, sh) || !restrict_ok(h, probe, rs)) return false;
+        if (q[9] && !smooth_restrict_ok(probe.P, probe.prec, RShape{8, q[9], q[10], 3})) return false;
     }
     for (size_t c = 0; c < cl.size(); ++c) {
         const int *q = v.data() + c * kBClassInts;
@@ -3076,6 +3083,7 @@ bool apply_batched_state(mg_ctx *h, const std::vector<int> &v) {
         for_class(h, cl[c], [&](LevelPlan &L) {
             L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = sh;
             L.rsh = rs;
+            if (q[9] && batched_fsr(h, L)) L.fsrsh = RShape{8, q[9], q[10], 3};
         });
     }
     return true;
@@ -3104,32 +3112,61 @@ mg_status_t autotune_batched(mg_ctx *h, hipStream_t st) {
         LevelPlan probe;
         probe.P = c.P, probe.prec = c.prec;
         Shape bs;
-        RShape br;
-        for_class(h, c, [&](LevelPlan &L) { bs = L.shs[SH_SWEEP], br = L.rsh; });
-        float best = step_ms();
+        RShape br, bf{8, 0, 0, 3};
+        bool runs = false, plain = false, fused = false;
+        for (const auto &I : h->inst)
+            for (int l = 0; l < I.lt; ++l) {
+                const LevelPlan &L = I.lv[l];
+                if (L.P != c.P || L.prec != c.prec) continue;
+                runs = true;
+                (batched_fsr(h, L) ? fused : plain) = true;
+            }
+        for_class(h, c, [&](LevelPlan &L) {
+            bs = L.shs[SH_SWEEP], br = L.rsh;
+            if (fused && batched_fsr(h, L)) bf = L.fsrsh;
+        });
+        auto set_stencil = [&](const Shape &s) {
+            for_class(h, c, [&](LevelPlan &L) { L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = s; });
+        };
+        auto set_restrict = [&](const RShape &r) { for_class(h, c, [&](LevelPlan &L) { L.rsh = r; }); };
+        auto set_fsr = [&](const RShape &r) {
+            for_class(h, c, [&](LevelPlan &L) {
+                if (batched_fsr(h, L)) L.fsrsh = r;
+            });
+        };
+        float best = runs ? step_ms() : 0.f;
         for (int V : {4, 8})
             for (int ty : {0, 2, 4, 6, 10, 14})
                 for (int zc : {2, 4, 8, 16, 32}) {
                     const Shape s{V, zc, 256, 1, ty};
-                    if ((ty == 0 && zc < 8) || !stencil_ok(h, probe, s)) continue;
+                    if (!runs || (ty == 0 && zc < 8) || !stencil_ok(h, probe, s)) continue;
                     if (c.prec == P_F64 && V == 8 && ty > 0) continue;  // FP64 rows spill at V = 8
-                    for_class(h, c, [&](LevelPlan &L) { L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = s; });
+                    set_stencil(s);
                     const float t = step_ms();
                     if (t < best) best = t, bs = s;
                 }
-        for_class(h, c, [&](LevelPlan &L) { L.shs[SH_SMOOTH] = L.shs[SH_SWEEP] = L.shs[SH_PROLONG] = bs; });
+        set_stencil(bs);
         for (int V : {4, 8})
             for (int tyc : {1, 2, 3, 5, 7})
                 for (int zcc : {2, 4, 8, 16})
                     for (int pipe : {0, 1, 2}) {
                         const RShape r{V, tyc, zcc, pipe};
-                        if (!restrict_ok(h, probe, r)) continue;
-                        for_class(h, c, [&](LevelPlan &L) { L.rsh = r; });
+                        if (!plain || !restrict_ok(h, probe, r)) continue;
+                        set_restrict(r);
                         const float t = step_ms();
                         if (t < best) best = t, br = r;
                     }
-        for_class(h, c, [&](LevelPlan &L) { L.rsh = br; });
-        v.insert(v.end(), {c.P, c.prec, bs.V, bs.zc, bs.ty, br.V, br.tyc, br.zcc, br.pipe});
+        set_restrict(br);
+        for (int tyc : {2, 3, 4, 5, 6, 8})
+            for (int zcc : {2, 4, 8, 16, 32}) {
+                const RShape r{8, tyc, zcc, 3};
+                if (!fused || zcc > c.P / 2 - 1 || tyc > c.P / 2 - 1 || !smooth_restrict_ok(c.P, c.prec, r)) continue;
+                set_fsr(r);
+                const float t = step_ms();
+                if (t < best) best = t, bf = r;
+            }
+        if (fused) set_fsr(bf);
+        v.insert(v.end(), {c.P, c.prec, bs.V, bs.zc, bs.ty, br.V, br.tyc, br.zcc, br.pipe, bf.tyc, bf.zcc});
     }
     mg_status_t s = batched_upload(h);
     if (s != MG_OK) return s;

@@ -243,3 +243,45 @@ def test_tuned_line_beyond_the_plan_room_is_tuned_anew(dev, tmp_path, monkeypatc
     again = mgir.BatchedSolver(sizes, prec, **kw)
     assert path.read_text().splitlines() == lines
     assert again.get_shape(0, 0, mgir.SHAPE_SWEEP) == s.get_shape(0, 0, mgir.SHAPE_SWEEP)
+
+
+@pytest.mark.parametrize("cols", [False, True])
+@pytest.mark.parametrize("nu1", [2, 3])
+def test_batched_autotuner_times_what_runs(dev, cols, nu1, tmp_path, monkeypatch):
+    """Where the fused smoothing + restriction runs (two pre-sweeps), its tile is the
+    tuned one and the separate restriction keeps its shape, and the other way round;
+    a level inside the fused coarse end keeps all of its shapes.  A line with other
+    tiles of the fused kernel is applied and gives the same solution bit for bit."""
+    n = 63
+    print(f"batched autotuner cols={cols} nu1={nu1}", flush=True)
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("MGIR_TUNE_CACHE", str(path))
+    prec = W.precision_map("f16", W.levels_for(n))
+    make = (lambda **kw: mgir.MultiSolver(n, 8, prec, nu1=nu1, **kw)) if cols else \
+        (lambda **kw: mgir.BatchedSolver([n, n], prec, nu1=nu1, **kw))
+    at = (lambda s, l, k: s.get_shape(l, k)) if cols else (lambda s, l, k: s.get_shape(0, l, k))
+    rng = np.random.default_rng(206)
+    b = torch.from_numpy(rng.uniform(-1, 1, (n, n, n, 8))).to(dev) if cols else \
+        [torch.from_numpy(rng.uniform(-1, 1, (n,) * 3)).to(dev) for _ in range(2)]
+    plain = make()
+    make(autotune=True)
+    key, ints = path.read_text().splitlines()[0].split("\t")
+    v = [int(x) for x in ints.split()]
+    assert len(v) == 33 and v[::11] == [64, 32, 16]
+    kinds = (mgir.SHAPE_SMOOTH, mgir.SHAPE_SWEEP, mgir.SHAPE_PROLONG, mgir.SHAPE_RESTRICT)
+    tuned = make(autotune=True)
+    for k in kinds:
+        assert at(tuned, 2, k) == at(plain, 2, k), k  # pitch 16: in the coarse end
+    for l in range(2):
+        if nu1 == 2:
+            assert v[11 * l + 9] > 0 and at(tuned, l, mgir.SHAPE_RESTRICT) == at(plain, l, mgir.SHAPE_RESTRICT), l
+            v[11 * l + 9 : 11 * l + 11] = [3, 5]
+        else:
+            assert v[11 * l + 9] == 0, l
+    path.write_text(key + "\t" + " ".join(map(str, v)) + "\n")
+    other = make(autotune=True)
+    assert len(path.read_text().splitlines()) == 1
+    u = plain.solve(b)[0]
+    for s in (tuned, other):
+        w = s.solve(b)[0]
+        assert torch.equal(u, w) if cols else all(torch.equal(x, y) for x, y in zip(u, w))
