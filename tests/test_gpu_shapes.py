@@ -386,3 +386,36 @@ def test_autotuner_times_what_runs(dev, dim, n, name, kw, tmp_path, monkeypatch)
     off = mgir.Solver(dim, n, prec, autotune=True, **kw)
     assert all(off.get_shape(l, mgir.SHAPE_FUSE_LEVEL) == [0] for l in range(m - 1))
     assert torch.equal(off.solve(b, check=False)[0], u)
+
+
+@pytest.mark.parametrize("name,n", [("f16", 63), ("f64", 63), ("bf16", 31), ("f32", 127), ("hsd", 127)])
+def test_finest_level_shapes_bitwise(dev, name, n):
+    """The separate kernels of the finest level (which its fused forms replace unless
+    they are off) in every launch shape: they run, and u and the V-cycle are bit for
+    bit those of the built-in shapes and of the fused forms."""
+    prec = W.precision_map(name, W.levels_for(n))
+    b64 = torch.from_numpy(W.uniform_rhs(3, n, seed=13)).to(dev)
+    bl = b64.to(mgir.TORCH_DTYPE[prec[0]])
+    kw = dict(max_iter=3, rtol=0.0)
+    fused = mgir.Solver(3, n, prec, **kw)
+    u_ref = fused.solve(b64, check=False)[0]
+    c_ref = fused.vcycle(bl)
+    s = mgir.Solver(3, n, prec, **kw)
+    for kind in (mgir.SHAPE_FUSE, mgir.SHAPE_FUSE_SR, mgir.SHAPE_FUSE_LEVEL):
+        s.set_shape(0, kind, [0])
+    for kind, shapes in ((mgir.SHAPE_STENCIL, STENCIL), (mgir.SHAPE_RESTRICT, RESTRICT),
+                         (mgir.SHAPE_UPDATE, STENCIL)):
+        default = s.get_shape(0, kind)
+        for shape in [default] + shapes:
+            print(f"finest {name} n={n} kind={kind} shape={shape}", flush=True)
+            try:
+                s.set_shape(0, kind, shape)
+            except mgir.MgError:
+                continue
+            assert torch.equal(s.solve(b64, check=False)[0], u_ref), (kind, shape)
+            assert torch.equal(s.vcycle(bl), c_ref), (kind, shape)
+        s.set_shape(0, kind, default)
+    s.solve(b64, check=False)
+    first = "smooth2" if prec[0] == "f64" and not s.options.residual_scaling else "smooth2_scaled"
+    names = [r[0] for r in s.profile_step() if r[1] == 0]
+    assert names == [first, "resid_restrict", "prolong_sweep", "sweep", "ir_update", "norm_finalize"]
