@@ -192,8 +192,8 @@ def solve_maps(torch, mgir, W, oracle, dev, dim, n, b, maps, steps, tune, defer=
     for name in maps:
         log(f"[bench] {dim}-D n={n} map {name}")
         kw = dict(residual_scaling=name != "f64", autotune=tune and dim == 3, device=dev)
-        if name != "f64" and defer and dim == 3:
-            kw["defer_update"] = defer
+        if name != "f64" and dim == 3:
+            kw["defer_update"] = defer or -1
         s = mgir.Solver(dim, n, W.precision_map(name, L), **kw)
         u = torch.zeros_like(bt)
         ms, res = timed_solves(s, bt, u, steps, 1, torch)
@@ -268,7 +268,7 @@ def extra_workloads(torch, mgir, W, dev, steps, bt=None, n=511, ms64=None, tune=
         # the residual rescaled into the FP16 levels (DSH)
         L = W.levels_for(n)
         entry = {}
-        dk = {"defer_update": defer} if defer else {}
+        dk = {"defer_update": defer or -1}
         for name, kw in (("h_mg", dk), ("hsd", dk), ("dsh", {"rescale_half": True})):
             log(f"[bench] variant {name} at {n}^3")
             s = mgir.Solver(3, n, W.precision_map(name, L), device=dev, autotune=tune, **kw)
@@ -281,7 +281,7 @@ def extra_workloads(torch, mgir, W, dev, steps, bt=None, n=511, ms64=None, tune=
             torch.cuda.synchronize()
             ms = (time.perf_counter() - t0) / steps * 1e3
             entry[name] = {"ms": ms, "iterations": r.iterations, "rel_residual": r.rel_residual,
-                           "status": r.status, "rescale_half": name == "dsh", "defer_update": kw.get("defer_update", 0),
+                           "status": r.status, "rescale_half": name == "dsh", "defer_update": max(0, kw.get("defer_update", 0)),
                            "map": W.precision_map(name, L)}
             if ms64:
                 entry[name]["speedup_vs_f64"] = ms64 / ms
@@ -390,7 +390,7 @@ def extra_workloads(torch, mgir, W, dev, steps, bt=None, n=511, ms64=None, tune=
                 ms = (time.perf_counter() - t0) / steps * 1e3
                 e[name] = {"ms": ms, "dof_per_s": nq**dim / ms * 1e3, "iterations": r.iterations,
                            "rel_residual": r.rel_residual, "status": r.status,
-                           "defer_update": dk.get("defer_update", 0) if name != "f64" else 0,
+                           "defer_update": defer if name != "f64" else 0,
                            "autotune": bool(tune), "lds_shapes": q1sh}
                 del s, u0
                 torch.cuda.empty_cache()
@@ -509,7 +509,7 @@ def main():
         bq = torch.from_numpy(W.q1_load_vector(3, n, seed=12)).to(dev)
         Lq = mgir.full_levels(n)
         s = mgir.Solver(3, n, W.precision_map(args.map, Lq), disc="q1", residual_scaling=args.map != "f64",
-                        device=dev, defer_update=args.defer if args.map != "f64" else 0,
+                        device=dev, defer_update=(args.defer or -1) if args.map != "f64" else 0,
                         autotune=not args.no_autotune)
         for k in range(args.warmup + args.steps):
             torch.cuda.synchronize()
@@ -545,7 +545,7 @@ def main():
     for depth in depths:
         log(f"[bench] setup {args.map} solver (defer_update={depth})")
         s = mgir.Solver(3, n, W.precision_map(args.map, L), residual_scaling=args.map != "f64", device=dev,
-                        autotune=tune, defer_update=depth)
+                        autotune=tune, defer_update=depth or -1)  # (-1: never; 0 leaves it to the library)
         ms, res = timed_solves(s, bt, u, args.steps, args.warmup, torch)
         log(f"[bench] mixed defer={depth}: {ms:.2f} ms/solve, {res[-1].iterations} it, "
             f"rel {res[-1].rel_residual:.2e}")
@@ -658,8 +658,8 @@ def main():
                 if name == args.map:
                     continue
                 log(f"[bench] {n}^3 map {name}")
-                kw = {"defer_update": best_depth} if best_depth else {}
-                s = mgir.Solver(3, n, W.precision_map(name, L), device=dev, autotune=tune, **kw)
+                s = mgir.Solver(3, n, W.precision_map(name, L), device=dev, autotune=tune,
+                                defer_update=best_depth or -1)
                 ms, res = timed_solves(s, bt, u, args.steps, 1, torch)
                 uh = u.cpu().numpy()
                 cfg3[name] = {"ms": round(ms, 3), "dof_per_s": N / (ms * 1e-3), "iterations": res[-1].iterations,
