@@ -365,8 +365,7 @@ RShape pick_rshape(int D, int P, int pf) {
     } else {
         // a block walks its rows with a barrier each: few rows per block until
         // the blocks alone fill the chip (2047^2: 52 us at 16 rows, 10 at two)
-        r.V = P <= 4096 || f64 ? 4 : 8;
-        if (P == 4096 && !f64) r.V = 8;
+        r.V = P < 4096 || f64 ? 4 : 8;
         r.tyc = 1;
         r.zcc = P <= 256 ? 1 : P <= 2048 ? 2 : f64 ? 8 : 4;
     }
@@ -1062,10 +1061,8 @@ mg_status_t ensure_graph(mg_ctx *h) {
 
 void build_batched_plan(mg_ctx *h, char *base);
 hipError_t enq_batched_step(mg_ctx *h, hipStream_t st);
-hipError_t enq_multi_step(mg_ctx *h, hipStream_t st);
 hipError_t batched_flush(mg_ctx *h, const std::vector<char> &sel, hipStream_t st);
 mg_status_t autotune_batched(mg_ctx *h, hipStream_t st);
-mg_status_t autotune_multi(mg_ctx *h, hipStream_t st);
 mg_status_t batched_upload(mg_ctx *h);
 
 mg_status_t need_ws(mg_ctx *h) {
@@ -3665,7 +3662,7 @@ mg_status_t mg_setup_multi(mg_handle *out, int dim, int n, int nrhs, const mg_pr
         }
     for (int l = 0; l < m; ++l)
         if (!columns_ok(prec[l], nrhs))
-            return fail(MG_ERR_ARG, "nrhs = %d is below the %d columns a thread of level %d handles", nrhs,
+            return fail(MG_ERR_ARG, "nrhs = %d is not supported: %d to 64 with the format of level %d", nrhs,
                         prec[l] == P_F64 ? 4 : 8, l);
     int ascale = 0;
     {

@@ -74,7 +74,7 @@ hipError_t launch_outer_update(int D, int prec, int P, const void *c, double *R,
 hipError_t launch_resid_flat(int D, int n, int P, const double *b, const double *U, double *R,
                              double *uout, double inv_h2, double *part, hipStream_t st);
 // Reduce partials: scal = {alpha, 1/alpha, ||r||_2, ||r||_inf}.  scaling 0:
-// alpha = 1; scaling 1 + j: alpha = 2^j ||r||_inf (also for launch_m_finalize).
+// alpha = 1; scaling 1 + j: alpha = 2^j ||r||_inf.
 // A non-null ctr is incremented (the slot counter of postponed updates); a
 // non-null host (pinned host memory) receives the four scalars too.
 hipError_t launch_finalize(const double *part, int nparts, double *scal, int scaling, hipStream_t st,
@@ -364,7 +364,8 @@ struct ColumnsArgs {
 };
 int columns_blocks(int n, int K);  // workgroups, and norm partials per column
 hipError_t launch_columns(const ColumnsArgs &a, hipStream_t st);
-// Fewest columns of a level in format prec (at most 64, a power of two).
+// Whether a handle of K columns takes a level in format prec: powers of two, up to
+// 64, from 4 (FP64) or 8 (narrower formats) on, the numbers mg_setup_multi documents.
 bool columns_ok(int prec, int K);
 
 // ---- the V-cycle on a caller-given scratch array (host side, mg_api.cpp) -----
