@@ -81,11 +81,11 @@ struct mg_ctx {
     int ascale = 0;
     std::vector<LevelPlan> lv;
     size_t off_R = 0, off_U = 0, off_part = 0, off_scal = 0, ws_need = 0;
-    // The workspace ends in what a step is only faster with: a ring of postponed
-    // updates that the options leave to the library, or the second residual array
-    // of a 2-D grid.  A workspace that ends at ws_min is taken without them.
-    size_t ws_min = 0;
-    size_t clear_end = 0;  // the part of the workspace that is cleared whole (the rings: their ghost cells)
+    // What a step is only faster with: rings of postponed updates that the options
+    // leave to the library, or the second residual array of a 2-D grid.  A workspace
+    // without room for them is taken too; what lies behind them then moves up
+    // (place_optional).
+    size_t opt_bytes = 0, opt_cut = 0;
     size_t off_R2_opt = 0;  // where the optional second residual array would be
     size_t vc_bytes = 0;  // the leading part of the workspace a lone V-cycle uses
     size_t off_rs = 0, off_rpart = 0;  // per-level {s, 1/s} and the partial maxima of the rescaling
@@ -1074,22 +1074,25 @@ mg_status_t need_ws(mg_ctx *h) {
 int level_prec_code(int p) { return p; }
 
 
-// Clear the workspace: ghost cells must read zero and padding must be finite.
-// The rings' slots are written before they are read, but for their ghost cells.
+// Clear the part of the workspace in use: ghost cells must read zero and padding
+// must be finite.  One pass, rings and all: clearing only a ring's ghost cells
+// takes as long in launches on small grids, and on large ones the first solve
+// then takes longer by what binding saved (255^3 FP16: 67 us).
 hipError_t clear_ws(mg_ctx *h, hipStream_t st) {
-    hipError_t e = hipMemsetAsync(h->ws, 0, h->clear_end, st);
-    if (e == hipSuccess && h->off_R2_opt && h->off_R2)
-        e = hipMemsetAsync(h->ws + h->off_R2, 0, align_up(h->lv[0].elems * sizeof(double), 256), st);
-    if (e == hipSuccess && h->defer) {
-        const LevelPlan &L = h->lv[0];
-        e = hipMemsetAsync(h->ws + h->off_adef, 0, h->off_cdef - h->off_adef, st);
-        if (e == hipSuccess)
-            e = launch_ring_ghosts(h->dim, L.prec, L.P, h->ws + h->off_cdef, h->cdef_stride, h->defer, st);
-    }
-    for (const auto &I : h->inst)
-        if (e == hipSuccess && I.defer)
-            e = launch_ring_ghosts(3, I.lv[0].prec, I.lv[0].P, h->ws + I.off_cd, I.cstride, I.defer, st);
-    return e;
+    return hipMemsetAsync(h->ws, 0, h->ws_need - h->opt_cut, st);
+}
+
+// Use or leave out the optional parts of the workspace.
+void place_optional(mg_ctx *h, bool full) {
+    const size_t cut = full ? 0 : h->opt_bytes;
+    for (size_t *off : {&h->off_cdef, &h->off_adef, &h->off_dctr, &h->off_part, &h->off_scal, &h->off_bctr,
+                        &h->off_scal_all, &h->off_active, &h->off_bmeta})
+        *off = *off + h->opt_cut - cut;  // (those of a ring that is left out are not used)
+    h->opt_cut = cut;
+    h->defer = full || h->opt.defer_update > 0 ? h->defer_plan : 0;
+    for (auto &I : h->inst) I.defer = full ? I.defer_plan : 0;
+    if (h->off_R2_opt) h->off_R2 = full ? h->off_R2_opt : 0;
+    if (!h->batched && !h->nrhs && h->nl > 1) set_fused(h, h->fused);
 }
 
 // ---- autotuner ------------------------------------------------------------
@@ -1776,6 +1779,25 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
         h->off_R2 = off;
         off += fin;
     }
+    // the 2-D update reads r as the right-hand side on its tiles' halos too
+    if (dim == 2 && prec[0] == P_F64 && !o.residual_scaling && tile2(h, 0)) {
+        h->off_R2 = h->off_R2_opt = off;
+        h->opt_bytes += fin;
+        off += fin;
+    }
+    if ((fusable || q1) && depth > 0) {
+        const LevelPlan &L = h->lv[0];
+        const size_t start = off;
+        h->defer = h->defer_plan = depth;
+        h->cdef_stride = align_up(L.elems * prec_bytes(L.prec), 256) / prec_bytes(L.prec);
+        h->off_cdef = off;
+        off += (size_t)depth * h->cdef_stride * prec_bytes(L.prec);
+        h->off_adef = off;
+        off += align_up((size_t)depth * sizeof(double), 256);
+        h->off_dctr = off;
+        off += 256;
+        if (o.defer_update == 0) h->opt_bytes += off - start;
+    }
     if (m > 1) {
         h->outer_parts = stencil_blocks(dim, h->lv[0].P, h->lv[0].osh);
         // room for the partials of any legal shape: V = 4, zc = 1, 64-thread
@@ -1799,25 +1821,6 @@ mg_status_t mg_setup(mg_handle *out, int dim, int n, int nlevels, const mg_prec_
     off += align_up((size_t)maxp * 2 * sizeof(double), 256);
     h->off_scal = off;
     off += 256;
-    h->clear_end = off;
-    if ((fusable || q1) && depth > 0) {
-        const LevelPlan &L = h->lv[0];
-        h->defer = h->defer_plan = depth;
-        h->off_adef = off;
-        off += align_up((size_t)depth * sizeof(double), 256);
-        h->off_dctr = off;
-        off += 256;
-        h->cdef_stride = align_up(L.elems * prec_bytes(L.prec), 256) / prec_bytes(L.prec);
-        h->off_cdef = off;
-        off += (size_t)depth * h->cdef_stride * prec_bytes(L.prec);
-    }
-    h->ws_min = o.defer_update > 0 ? off : h->clear_end;
-    // the 2-D update reads r as the right-hand side on its tiles' halos too
-    // (such a level is FP64: it has no ring but one that was asked for)
-    if (dim == 2 && prec[0] == P_F64 && !o.residual_scaling && tile2(h, 0)) {
-        h->off_R2 = h->off_R2_opt = off;
-        off += fin;
-    }
     h->ws_need = off;
     if (tail_prepare() != hipSuccess) h->tail_on = false;
     if (m > 1) {
@@ -1849,20 +1852,17 @@ mg_status_t mg_workspace_size(mg_handle h, size_t *bytes) {
 
 mg_status_t mg_bind_workspace(mg_handle h, void *dev_ptr, size_t bytes, void *stream) {
     if (!h || !dev_ptr) return fail(MG_ERR_ARG, "null argument");
-    if (bytes < h->ws_min) return fail(MG_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", bytes, h->ws_min);
+    if (bytes < h->ws_need - h->opt_bytes)
+        return fail(MG_ERR_WORKSPACE, "workspace of %zu bytes < %zu needed", bytes, h->ws_need - h->opt_bytes);
     if (reinterpret_cast<uintptr_t>(dev_ptr) % 256) return fail(MG_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!h->host_scal) HIPCHK(hipHostMalloc((void **)&h->host_scal, 4 * sizeof(double), hipHostMallocCoherent));
     drop_graph(h);
     h->ws = static_cast<char *>(dev_ptr);
     h->ws_bytes = bytes;
-    const bool full = bytes >= h->ws_need;
     h->rpar = h->pending = 0;
     h->open_rhs = -1;
-    h->defer = full || h->opt.defer_update > 0 ? h->defer_plan : 0;
-    for (auto &I : h->inst) I.defer = full ? I.defer_plan : 0;
-    if (h->off_R2_opt) h->off_R2 = full ? h->off_R2_opt : 0;
-    if (!h->batched && !h->nrhs && h->nl > 1) set_fused(h, h->fused);
+    place_optional(h, bytes >= h->ws_need);
     HIPCHK(clear_ws(h, st));
     HIPCHK(hipStreamSynchronize(st));
     for (int l = 0; l < h->nl; ++l) h->cur[l] = 0;
@@ -3239,14 +3239,18 @@ void plan_instances(mg_ctx *h, const std::vector<int> &n) {
     // The rings add 16 bytes per point to the workspace's 16 and the levels', so
     // very large batches go without, and so does a workspace too small for them.
     constexpr int kRing = 8;
+    const size_t before_rings = off;
     if (off <= (size_t)64 << 30 && o.defer_update >= 0) {
         for (auto &I : h->inst) {
             const LevelPlan &L = I.lv[0];
             if (!I.su || prec_bytes(L.prec) != 2) continue;
             I.defer = I.defer_plan = kRing;
             I.cstride = align_up(L.elems * 2, 256) / 2;
+            I.off_cd = off, off += kRing * I.cstride * 2;
+            I.off_adef = off, off += 256;
         }
     }
+    h->opt_bytes = off - before_rings;
     h->off_bctr = off, off += align_up((size_t)ninst * sizeof(int), 256);
     h->max_parts = parts;
     h->off_part = off, off += align_up((size_t)parts * 2 * sizeof(double), 256);
@@ -3258,12 +3262,6 @@ void plan_instances(mg_ctx *h, const std::vector<int> &n) {
     // with shorter plane chunks have more work items)
     h->bmeta_cap = align_up(4 * h->bmeta_bytes, 256);
     off += h->bmeta_cap;
-    h->clear_end = h->ws_min = off;
-    for (auto &I : h->inst) {
-        if (!I.defer) continue;
-        I.off_adef = off, off += 256;
-        I.off_cd = off, off += (size_t)I.defer * I.cstride * 2;
-    }
     h->ws_need = off;
 }
 

@@ -1632,20 +1632,6 @@ __global__ __launch_bounds__(256) void k_defer_flush(const T *__restrict__ cd, s
     defer_flush_body<T>(cd, cstride, adef, count, h2, U, n8, ctr, from_zero);
 }
 
-// Zero the ghost cells of a ring's slots: row 0 and the planes 0, P and P + 1
-// whole, of the other rows the first element.  One row per thread; a handle of
-// 511^3 in FP16 with a ring of eight is bound without writing its 2.1 GB.
-template <class T>
-__global__ __launch_bounds__(256) void k_ring_ghosts(T *ring, size_t stride, int slots, int D, int P, int rows) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)slots * rows) return;
-    const int slot = (int)(t / rows), row = (int)(t % rows);
-    const int z = D == 3 ? row / P : row, y = D == 3 ? row % P : 1;
-    T *p = ring + slot * stride + (size_t)row * P;
-    const int n = (z < 1 || z >= P || y < 1) ? P : 1;
-    for (int x = 0; x < n; ++x) p[x] = T(0);
-}
-
 // The same for up to kGroup grids in a launch (grid blockIdx.y).
 template <class T> __global__ __launch_bounds__(256) void k_group_flush(const GroupFlush g) {
     const int i = blockIdx.y;
@@ -2205,22 +2191,6 @@ hipError_t launch_defer_flush(int prec, const void *cdefer, size_t cstride, cons
     default: return hipErrorInvalidValue;
     }
 #undef MG_FL
-    return hipGetLastError();
-}
-
-hipError_t launch_ring_ghosts(int D, int prec, int P, void *ring, size_t stride, int slots, hipStream_t st) {
-    const int rows = D == 3 ? (P + 2) * P : P + 2;
-    if (slots < 1 || stride < (size_t)rows * P) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)(((size_t)slots * rows + 255) / 256);
-#define MG_RG(T) hipLaunchKernelGGL(k_ring_ghosts<T>, dim3(blocks), dim3(256), 0, st, static_cast<T *>(ring), stride, slots, D, P, rows)
-    switch (prec) {
-    case P_F64: MG_RG(uint64_t); break;
-    case P_F32: MG_RG(uint32_t); break;
-    case P_F16:
-    case P_BF16: MG_RG(uint16_t); break;
-    default: return hipErrorInvalidValue;
-    }
-#undef MG_RG
     return hipGetLastError();
 }
 

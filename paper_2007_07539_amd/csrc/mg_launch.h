@@ -118,9 +118,6 @@ hipError_t launch_sweep_update(int prec, int P, const SweepUpdateArgs &a, const 
 // padded elements each), then *ctr = 0.
 hipError_t launch_defer_flush(int prec, const void *cdefer, size_t cstride, const double *adef, int count, double h2,
                               double *U, size_t elems, int *ctr, hipStream_t st, bool from_zero = false);
-// Zero the ghost cells of a ring's slots (their other cells are written before
-// they are read).
-hipError_t launch_ring_ghosts(int D, int prec, int P, void *ring, size_t stride, int slots, hipStream_t st);
 
 // First pre-smoothing of the finest 3-D level from the FP64 residual (scaled
 // and cast) fused with the residual + full-weighting restriction of its

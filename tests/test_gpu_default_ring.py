@@ -102,8 +102,8 @@ def test_optional_parts_of_the_workspace(dim, n, name, disc):
                                              (3, 31, "f16", "q1"), (3, 13, "f64", "q1"), (2, 13, "bf16", "q1"),
                                              (2, 131, "f16", "q1")])
 def test_ring_in_a_workspace_of_nans(dim, n, name, disc):
-    """Binding clears the ring's ghost cells only: u, and the ghosts that its flush
-    adds to, are finite whatever the workspace held."""
+    """Binding clears the rings too: u is that of updates in every step, whatever the
+    workspace held before."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     print(f"ring in a dirty workspace {dim}-D n={n} {name} {disc}", flush=True)
