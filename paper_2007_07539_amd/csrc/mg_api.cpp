@@ -1143,31 +1143,43 @@ template <class F> float time_ms(hipStream_t st, F &&fn, int reps) {
     return best;
 }
 
-// The same for a comparison of two kernels: an event pair around one short
-// launch reads 5 to 10 us whatever ran, so below 50 us it brackets eight.
-template <class F> float burst_ms(hipStream_t st, F &&fn) {
-    const int n = time_ms(st, fn, 1) < 0.05f ? 8 : 1;
-    return time_ms(st, [&]() -> hipError_t {
-        for (int i = 0; i < n; ++i) {
-            const hipError_t e = fn();
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
-    }, 5) / n;
+// The same for a comparison of two kernels (fn enqueues on the stream it is
+// given): an event pair around one short launch reads 5 to 10 us whatever ran, and
+// launches in a row come no faster than the host issues them, so below 50 us a
+// graph of sixteen is timed, as a solve replays them.
+template <class F> float burst_ms(mg_ctx *h, hipStream_t st, F &&fn) {
+    constexpr int n = 16;
+    auto once = [&]() { return fn(st); };
+    if (time_ms(st, once, 1) >= 0.05f) return time_ms(st, once, 5);
+    if (!h->cap_stream && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess) return 1e30f;
+    if (hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return 1e30f;
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n && e == hipSuccess; ++i) e = fn(h->cap_stream);
+    hipGraph_t g = nullptr;
+    hipGraphExec_t x = nullptr;
+    const hipError_t e2 = hipStreamEndCapture(h->cap_stream, &g);
+    float t = 1e30f;
+    if (e == hipSuccess && e2 == hipSuccess && hipGraphInstantiate(&x, g, nullptr, nullptr, 0) == hipSuccess)
+        t = time_ms(st, [&]() { return hipGraphLaunch(x, st); }, 5) / n;
+    (void)hipStreamSynchronize(st);
+    if (x) (void)hipGraphExecDestroy(x);
+    if (g) (void)hipGraphDestroy(g);
+    return t;
 }
 
 // The fastest of the candidates, but the shape in place (the built-in one) if
 // that is not slower: the luckiest of many readings is checked against it.
 // *ms: the time of the shape returned.
-template <class S, class F> S fastest(hipStream_t st, const S &in_place, const std::vector<S> &cands, F &&run, float *ms) {
+template <class S, class F>
+S fastest(mg_ctx *h, hipStream_t st, const S &in_place, const std::vector<S> &cands, F &&run, float *ms) {
     float best = 1e30f;
     S s = in_place;
     for (const S &c : cands) {
-        const float t = time_ms(st, [&]() { return run(c); }, 3);
+        const float t = time_ms(st, [&]() { return run(c, st); }, 3);
         if (t < best) best = t, s = c;
     }
-    const float t0 = burst_ms(st, [&]() { return run(in_place); });
-    const float t1 = cands.empty() ? 1e30f : burst_ms(st, [&]() { return run(s); });
+    const float t0 = burst_ms(h, st, [&](hipStream_t q) { return run(in_place, q); });
+    const float t1 = cands.empty() ? 1e30f : burst_ms(h, st, [&](hipStream_t q) { return run(s, q); });
     *ms = std::min(t0, t1);
     return t1 < t0 ? s : in_place;
 }
@@ -1376,25 +1388,25 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
         float fam_best[3] = {0.f, 0.f, 0.f};
         for (int fam = 0; fam < 3; ++fam) {
             if (L.P < 8 || in_tail || (tiles && !(warm && fam == SH_SWEEP))) continue;
-            L.shs[fam] = fastest(st, L.shs[fam], stencil_candidates(h, L, false, fam == SH_PROLONG),
-                                 [&](const Shape &s) -> hipError_t {
+            L.shs[fam] = fastest(h, st, L.shs[fam], stencil_candidates(h, L, false, fam == SH_PROLONG),
+                                 [&](const Shape &s, hipStream_t q) -> hipError_t {
                 if (fam == SH_SMOOTH)
                     return scaled0 ? launch_smooth_first(D, L.prec, L.P, nullptr, Rbuf(h), scal(h), bbuf(h, l),
-                                                         cbuf(h, l, 0), h->opt.omega, true, s, st)
+                                                         cbuf(h, l, 0), h->opt.omega, true, s, q)
                                    : launch_smooth_first(D, L.prec, L.P, b0, nullptr, nullptr, nullptr,
-                                                         cbuf(h, l, 0), h->opt.omega, true, s, st);
+                                                         cbuf(h, l, 0), h->opt.omega, true, s, q);
                 if (fam == SH_SWEEP)
-                    return launch_sweep(D, L.prec, L.P, b0, cbuf(h, l, 0), cbuf(h, l, 1), h->opt.omega, s, st);
+                    return launch_sweep(D, L.prec, L.P, b0, cbuf(h, l, 0), cbuf(h, l, 1), h->opt.omega, s, q);
                 return launch_prolong(D, L.prec, h->lv[l + 1].prec, L.P, cbuf(h, l, 1), cbuf(h, l + 1, 0), b0,
-                                      cbuf(h, l, 0), h->opt.omega, true, s, st);
+                                      cbuf(h, l, 0), h->opt.omega, true, s, q);
             }, &fam_best[fam]);
         }
         // the prolongation and two sweeps in one kernel against the two kernels
         float t_p2 = 0.f;
         if (!in_tail && prolong2(h, l, h->opt.nu2)) {
-            t_p2 = burst_ms(st, [&]() {
+            t_p2 = burst_ms(h, st, [&](hipStream_t q) {
                 return launch_prolong_sweep2(L.prec, h->lv[l + 1].prec, L.P, cbuf(h, l, 1), cbuf(h, l + 1, 0), b0,
-                                             cbuf(h, l, 0), h->opt.omega, st);
+                                             cbuf(h, l, 0), h->opt.omega, q);
             });
             L.fuse = t_p2 < fam_best[SH_PROLONG] + fam_best[SH_SWEEP];
         }
@@ -1415,9 +1427,9 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
                             const RShape r{V, tyc, zcc, pipe};
                             if (restrict_ok(h, L, r)) cands.push_back(r);
                         }
-            L.rsh = fastest(st, L.rsh, cands, [&](const RShape &r) {
+            L.rsh = fastest(h, st, L.rsh, cands, [&](const RShape &r, hipStream_t q) {
                 return launch_restrict(D, L.prec, h->lv[l + 1].prec, L.P, bbuf(h, l), cbuf(h, l, 0), bbuf(h, l + 1), r,
-                                       st);
+                                       q);
             }, &best);
         }
         if (restricts && (l == 0 ? fusion_sr_possible(h) : fusion_srb_possible(h, l))) {
@@ -1450,15 +1462,15 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
                         if (smooth_restrict_ok(L.P, L.prec, r)) cands.push_back(r);
                     }
             }
-            const RShape bsr = fastest(st, l == 0 ? h->srsh : L.fsrsh, cands, [&](const RShape &r) {
+            const RShape bsr = fastest(h, st, l == 0 ? h->srsh : L.fsrsh, cands, [&](const RShape &r, hipStream_t q) {
                 if (l == 0 && finest_alias(h))
                     return launch_smooth_restrict_b(L.prec, h->lv[1].prec, L.P, Rbuf(h), cbuf(h, 0, 0), bbuf(h, 1),
-                                                    h->opt.omega, r, st);
+                                                    h->opt.omega, r, q);
                 if (l == 0)
                     return launch_smooth_restrict(L.prec, h->lv[1].prec, L.P, Rbuf(h), scal(h), bbuf(h, 0),
-                                                  cbuf(h, 0, 0), bbuf(h, 1), h->opt.omega, r, st);
+                                                  cbuf(h, 0, 0), bbuf(h, 1), h->opt.omega, r, q);
                 return launch_smooth_restrict_b(L.prec, h->lv[l + 1].prec, L.P, bbuf(h, l), cbuf(h, l, 0),
-                                                bbuf(h, l + 1), h->opt.omega, r, st);
+                                                bbuf(h, l + 1), h->opt.omega, r, q);
             }, &bf);
             const bool win = bf < best + fam_best[SH_SMOOTH];
             if (l == 0) {
@@ -1474,9 +1486,9 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
             const double hh = 1.0 / (double)(L.n + 1);
             for (const Shape &s : stencil_candidates(h, L, true))
                 if (stencil_blocks(D, L.P, s) <= h->max_parts) cands.push_back(s);
-            L.osh = fastest(st, L.osh, cands, [&](const Shape &s) {
+            L.osh = fastest(h, st, L.osh, cands, [&](const Shape &s, hipStream_t q) {
                 return launch_outer_update(D, L.prec, L.P, cbuf(h, 0, 0), Rbuf(h), Ubuf(h), scal(h), hh * hh,
-                                           part(h), s, st);
+                                           part(h), s, q);
             }, &best);
             set_fused(h, h->fused);  // the partials of the update in use
             // the fused last sweep + update against the two kernels it replaces
@@ -1495,14 +1507,14 @@ mg_status_t autotune_timed(mg_ctx *h, hipStream_t st) {
                         }
                 const bool keep_r = h->su_r;
                 float bf = 1e30f;
-                const Su su = fastest(st, Su{h->fsh, keep_r}, forms, [&](const Su &f) {
+                const Su su = fastest(h, st, Su{h->fsh, keep_r}, forms, [&](const Su &f, hipStream_t sq) {
                     const bool was = h->fused;
                     h->fused = true;  // the arguments of the form the step would use
                     h->su_r = f.from_r;
                     const SweepUpdateArgs q = su_args(h, cbuf(h, 0, 0));
                     h->fused = was;
                     h->su_r = keep_r;
-                    return launch_sweep_update(L.prec, L.P, q, f.s, st);
+                    return launch_sweep_update(L.prec, L.P, q, f.s, sq);
                 }, &bf);
                 h->fsh = su.s;
                 h->su_r = su.from_r;
